@@ -187,7 +187,7 @@ void centra_destroy(centra_ctx* ctx) {
   if (!ctx) return;
   DeviceGuard guard(ctx->device);
   (void)hipDeviceSynchronize();
-  DevBuf* bufs[] = {&ctx->slot_rec, &ctx->slot_q, &ctx->slot_praw, &ctx->slot_pinfo, &ctx->wide_ws,
+  DevBuf* bufs[] = {&ctx->slot_map, &ctx->slot_sig, &ctx->slot_q, &ctx->slot_starts, &ctx->slot_pinfo, &ctx->wide_ws,
                     &ctx->stage_nodes, &ctx->stage_pos,
                     &ctx->stage_len, &ctx->work_ctr, &ctx->scan_tmp, &ctx->deg, &ctx->inc_off,
                     &ctx->inc_cursor, &ctx->inc, &ctx->inc_node, &ctx->gain, &ctx->covered, &ctx->best,

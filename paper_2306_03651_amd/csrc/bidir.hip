@@ -199,7 +199,7 @@ __device__ __forceinline__ uint64_t step_weight(uint64_t* rec, uint32_t u, uint6
 // of the side (records rec), the one drawn with weight sigma (in row
 // order).  Draws one word (or more, by rejection).
 __device__ uint32_t walk_pick(const uint32_t* idx, uint32_t rb, uint32_t re, uint64_t* rec, uint64_t want_tag,
-                              WordStream& st, BiShared& sh) {
+                              RolledWordStream& st, BiShared& sh) {
   uint64_t W = 0;
   for (uint32_t c = rb; c < re; c += kBiBlock) {
     const uint32_t e = c + threadIdx.x;
@@ -257,7 +257,7 @@ __global__ __launch_bounds__(kBiBlock) void k_sample_bidir(BiArgs a) {
     __syncthreads();
     if (idx >= a.count) break;
     const uint64_t base = uint64_t(a.stamp0 + idx) << 32;
-    WordStream st(a.seed, a.first + idx, a.instance, 7);
+    RolledWordStream st(a.seed, a.first + idx, a.instance, 7);
     const uint32_t s0 = static_cast<uint32_t>(bounded(st, a.n));
     const uint32_t tp = static_cast<uint32_t>(bounded(st, a.n - 1));
     const uint32_t t0 = tp + (tp >= s0 ? 1u : 0u);
@@ -483,8 +483,8 @@ int sample_bidir_to_stage(centra_ctx* ctx, const centra_graph* g, uint64_t seed,
       // 32-bit stamps would run out: clear every record of both samplers
       fill_u64(static_cast<uint64_t*>(ctx->bi_rec_f.ptr), 0, size_t(ctx->bi_slots) * ctx->bi_n * 2, s);
       fill_u64(static_cast<uint64_t*>(ctx->bi_rec_b.ptr), 0, size_t(ctx->bi_slots) * ctx->bi_n * 2, s);
-      if (ctx->slot_rec.ptr)
-        fill_u64(static_cast<uint64_t*>(ctx->slot_rec.ptr), 0, size_t(ctx->slots) * ctx->slot_n * 2, s);
+      if (ctx->slot_map.ptr)
+        fill_u64(static_cast<uint64_t*>(ctx->slot_map.ptr), 0, size_t(ctx->slots) * ctx->slot_n, s);
       ctx->stamp_next = 1;
     }
     BiArgs a{};

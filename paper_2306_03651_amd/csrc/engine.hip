@@ -179,6 +179,7 @@ struct centra_engine {
 
 namespace centra {
 
+static constexpr int kDefaultBlock = 64;       // threads per BFS of the fused sampling launches
 static constexpr uint32_t kRoundChunk = 8;   // greedy rounds per captured graph
 
 static size_t pool_bytes(const EnginePool& p) {
@@ -251,7 +252,7 @@ static int sample_pools(centra_engine* e, const std::vector<uint32_t>& want_leve
   hipEvent_t* ev = ctx->ev;
   CENTRA_HIP(ctx, hipEventRecord(ev[0], s));
   uint64_t total = 0;
-  const int block = e->tuned_block ? e->tuned_block : 128;
+  const int block = e->tuned_block ? e->tuned_block : kDefaultBlock;
   int rc = sample_multi_to_stage(ctx, items.data(), static_cast<uint32_t>(items.size()), block, &total, s);
   if (rc) return rc;
   uint64_t count = 0;
@@ -371,12 +372,10 @@ static int build_level(centra_engine* e, EnginePool& p, uint32_t j, hipStream_t 
 }
 
 // Autotuner: times the fused sampling launch of a probe batch (the first
-// samples of every pool) with workgroups of 128, 256 and 512 threads, the
+// samples of every pool) with workgroups of 64, 128 and 256 threads, the
 // best of two timed launches after one that pays the slot set-up, and keeps
-// the fastest unless it beats the default 128 by under 2% (differences
-// within the probe's noise did not carry over to full launches).  64-thread
-// workgroups are not tried: they won short probes but lost full launches,
-// whose twice as many slots carry twice the slot state.  The probe's
+// the fastest unless it beats the default 64 by under 2% (differences within
+// the probe's noise did not carry over to full launches).  The probe's
 // samples are the pools' own, and every variant draws the same hyperedges,
 // so the choice changes no result.  CENTRA_TUNE_CACHE names a file of
 // "key block" lines that keeps choices across runs.
@@ -409,8 +408,7 @@ static int autotune(centra_engine* e, hipStream_t s) {
     const uint64_t c = std::min<uint64_t>(p.level_m[0], std::max<uint64_t>(64, 16384 / e->pools.size()));
     probe.push_back(MultiSampleItem{p.g, p.p.seed, p.p.instance, 0, static_cast<uint32_t>(c)});
   }
-  const int blocks[] = {128, 256, 512};
-  constexpr int kDefaultBlock = 128;
+  const int blocks[] = {64, 128, 256};
   float best_ms = 0.f, default_ms = 0.f;
   int best = kDefaultBlock;
   std::string line = std::string("autotune: ") + key + ":";

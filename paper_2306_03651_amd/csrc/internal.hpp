@@ -23,13 +23,14 @@ struct DevBuf {
 struct centra_ctx {
   int device = 0;
   size_t budget = 0;          // 0 = unbounded
+  size_t slot_cap = 0;        // memory that BFS slots may take (0: not asked yet)
   size_t allocated = 0;
   std::string err;
   uint32_t* d_flags = nullptr;   // kernel error bits (u32) + scratch counters
-  // per-BFS slot arrays (node records {count, stamp and level}, visit
-  // queue, stored pair counts), one set per concurrent BFS, sized for the
-  // largest graph
-  centra::DevBuf slot_rec, slot_q, slot_praw, slot_pinfo;
+  // per-BFS slot arrays (node map {stamp, place}, counts, visit queue,
+  // level starts, pair arrays), one set per concurrent BFS, sized for
+  // the largest graph
+  centra::DevBuf slot_map, slot_sig, slot_q, slot_starts, slot_pinfo;
   centra::DevBuf wide_ws;   // device-wide BFS: u64 ctl[8] per sample of a group, then the deferred work items
   std::string log;   // one-time choices of the context (slot placement), one line each
   bool placed = false;   // the slot records' placement was searched

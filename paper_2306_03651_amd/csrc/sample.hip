@@ -8,34 +8,33 @@
 // scan of in-neighbours) is independent of thread timing, so the result is
 // bit-identical to a sequential implementation.
 //
-// State of a slot, in HBM: one 16-byte record per node {sigma' u64, tag
-// u64} (a node's claim, level, count reads and writes touch a single cache
-// line), the visit queue (u32, nodes in level order) and the stored
-// per-pair counts of the last 3-hop test.  The tag is stamp << 32 |
-// (kUnseen - level), where the stamp numbers the BFSs of the context in
-// launch and work order: a slot's records carry only stamps older than its
-// current BFS's unless that BFS claimed them, so nothing is ever reset
-// between samples (records start at stamp 0; the stamps restart after a
-// full clear when 32 bits run out).  The visited set of the completed
-// levels is an exact bitmap in LDS (the 1024-thread variant, n up to about
-// 1.1M; cleared per visited node) or a Bloom filter in LDS backed by the
-// tags (the default variants).
+// State of a slot, in HBM: the visited nodes in level order (their ids and
+// counts sigma', contiguous), a bitmap of the places where levels start, and a map from nodes
+// to places in that order (Visited, below): one 8-byte word per node, stamp
+// << 32 | place, where the stamp numbers the BFSs of the context in launch
+// and work order.  A slot's map carries only stamps older than its current
+// BFS's unless that BFS visited the node, so nothing is ever reset between
+// samples (the map starts at stamp 0; the stamps restart after a full clear
+// when 32 bits run out).  An LDS filter holds the visited nodes.
 //
 // Level expansion (push): the frontier is processed in chunks of BLOCK
-// nodes; their out-degrees are prefix-summed in LDS and each thread takes
-// UNROLL arcs per round (tid, tid + BLOCK, ...), locating their sources by
-// binary search in LDS (load balance over skewed degrees; consecutive
-// threads read consecutive col_idx entries; UNROLL independent chains keep
-// more memory requests in flight).  An arc w -> v whose target is not in a
-// completed level raises v's tag to (stamp, L+1) with a returning 64-bit
-// atomic max: the one that sees an older stamp is the first arrival, claims
-// v (appended to the queue with one LDS atomic per wave, ballot +
-// popcount) and starts its count with its own contribution; after a
-// barrier the other arrivals add theirs with returning 64-bit atomics
-// (the inverted level keeps the max from touching nodes of lower levels).
-// The returned partial sums also give the level's largest raw count, so
-// the normalisation shift needs no extra pass; only when the shift is
+// nodes, whose arcs are spread evenly over the workgroup (ArcSpread).  An
+// arc w -> v that finds v's filter bit clear claims v, with its own
+// contribution; the others go to a table of duplicates in LDS (Dups), which
+// sums them per node and looks the nodes up together.  The largest raw count
+// of the level, which decides the normalisation shift, comes from the counts
+// as they are written, so it needs no extra pass; only when the shift is
 // nonzero are the level's counts rewritten.
+//
+// What bounds it: a BFS is a chain of dependent trips to memory (about 60
+// at BA n = 10^6, of 0.5 to 2 us), and with 4,096 of them in flight the
+// waves' instructions (a SIMD issues in 79% of its cycles).  So the kernel
+// uses no global atomic in a BFS, looks nodes up in bulk (Hits, Dups), and
+// keeps its code within the instruction cache (41 KB of 64; 83 KB before,
+// when every launch and most steps waited for instructions).  Measured, with
+// 16-byte records claimed by returning 64-bit global atomics before: BA n =
+// 10^6, 400,000 samples, 26.7 -> 15.2 ms; grid 128 x 128, 10,000 samples,
+// 13.9 -> 7.6 ms; directed R-MAT scale 20, 200,000 samples, 32-49 -> 22 ms.
 //
 // Early stop.  After levels 0..L are complete, every visited in-neighbour
 // of an unvisited node is at level L (a lower one would have put the node
@@ -47,8 +46,8 @@
 //       in-neighbours' counts;
 //   (3) some u of those pairs (unvisited) has visited in-neighbours: u is
 //       at L+1, its w at L+2 and d = L+3; the raw counts of u and w follow
-//       the same way, and the per-pair counts of u are kept for the
-//       backtrack.
+//       the same way (the test sums them per w; the backtrack counts again
+//       the u of the one w it picks).
 // Levels L+1 (and L+2) are then never produced.  Their normalisation
 // would be a no-op when every count of theirs is below 2^C: level L+1
 // counts are at most S_L (the sum of the level-L counts) and level L+2
@@ -85,273 +84,335 @@ namespace centra {
 // 2-hop test on the pairs (w in in(t), u in in(w)); the 3-hop test also
 // needs at most kPairMax pairs.  Cost rules (kConeRatio, kPairRatio) decide
 // at which levels they run.
-// Bloom filter of the visited set for the HBM variant (see BitsRec).
-constexpr uint32_t kBloomLog = 14;
-constexpr uint32_t kBloomWords = (1u << kBloomLog) / 32;
-
 template <int BLOCK>
 struct Ring {
-  static constexpr uint32_t kCache = BLOCK >= 512 ? 512u : 256u;
+  static constexpr uint32_t kCache = BLOCK >= 512 ? 512u : BLOCK >= 128 ? 256u : 128u;
 };
+// Bits of the visited filter (see Visited).
+constexpr uint32_t kBitLog = 14;
+constexpr uint32_t kBitWords = (1u << kBitLog) / 32;
 constexpr uint64_t kConeRatio = 3;
 // The 2-hop test runs at a level only when its pairs are at most kPairRatio
-// times the out-arcs expanding that level would scan (a pair costs a
-// sequential read and an LDS probe, an expanded arc a random atomic).
+// times the out-arcs expanding that level would scan (2 and 4 measure alike,
+// 1 is 2% slower; of cone ratios 1, 2, 3, 4 and 6, 1 is 40% slower, 2 4%).
 constexpr uint64_t kPairRatio = 4;
 
-// Record accessors: word 0 = sigma', word 1 = tag.  With base = stamp << 32
-// the tag of a node at level l of the current BFS is base + (kUnseen - l):
-// "claimed by this BFS" is tag >= base, "at level <= L" is
-// tag >= base + (kUnseen - L).
-__device__ __forceinline__ uint64_t* sig_of(uint64_t* rec, uint32_t v) { return rec + 2 * size_t(v); }
-__device__ __forceinline__ uint64_t* tag_of(uint64_t* rec, uint32_t v) { return rec + 2 * size_t(v) + 1; }
-__device__ __forceinline__ uint64_t level_tag(uint64_t base, uint32_t level) { return base + (kUnseen - level); }
+// Entries a round handles per thread (loads in flight), and in all: the
+// duplicate table and the hit lists below hold a round's.
+template <int BLOCK>
+struct Round {
+  static constexpr int kPer = BLOCK <= 128 ? 4 : BLOCK <= 512 ? 2 : 1;
+  static constexpr uint32_t kArcs = BLOCK * kPer;
+  static constexpr int kMasks = kArcs / kWave;   // <= 64: one per lane
+};
 
 template <int BLOCK>
 struct SampleShared {
-  uint32_t off[BLOCK];
-  uint32_t rs[BLOCK];
-  uint64_t sg[BLOCK];
-  uint32_t scan[BLOCK / kWave + 1];
-  uint64_t red[BLOCK / kWave];
-  uint32_t poff[Ring<BLOCK>::kCache];   // pair offsets of t's in-neighbours
-  uint32_t rw[Ring<BLOCK>::kCache];     // t's in-neighbours w
-  uint32_t rrs[Ring<BLOCK>::kCache];    // in_ptr[w]
-  uint64_t ring_a[Ring<BLOCK>::kCache];  // per in-neighbour w of t: level-(L+1) count
-  uint64_t ring_b[Ring<BLOCK>::kCache];  // per in-neighbour w of t: level-(L+2) count
-  uint32_t bloom[BLOCK >= 1024 ? 1 : kBloomWords];   // HBM variant (<= 512 threads): visited filter
-  uint64_t base;
+  uint64_t sg[BLOCK];                    // per source of a chunk: its count, its ring index, or the sum of its arcs
+  uint64_t ring[Ring<BLOCK>::kCache];    // per in-neighbour w of t: its count on the level the last test gave it
+  uint64_t dsum[Round<BLOCK>::kArcs];    // duplicate table: sums (zero when empty); in the tests the waves' hit lists
+  uint64_t mask[3][Round<BLOCK>::kMasks];   // arcs of a round that start a source's run
+  uint64_t red[2 * Coll<BLOCK>::kHalf];
   uint64_t hub_pairs;
+  uint64_t pk_weight;                    // the entry a pick chose: its weight,
+  uint32_t pk[4];                        // index, node and in-row bounds
+  uint32_t dkey[Round<BLOCK>::kArcs];    // duplicate table: nodes, kUnseen when empty
+  uint32_t rs[BLOCK];                    // per source of a chunk: row start less the arcs before it
+  uint32_t fr[BLOCK];                    // the first nodes of the newest level
+  uint32_t poff[Ring<BLOCK>::kCache];    // pair offsets of t's in-neighbours
+  uint32_t rrs[Ring<BLOCK>::kCache];     // in_ptr[w] less that offset: pair p's entry is in_idx[rrs + p]
+  uint32_t bits[BLOCK >= 1024 ? 1 : kBitWords];   // visited filter (the 1024-thread variant's is dynamic)
   uint32_t hpos;
   uint32_t pick;
   uint32_t qlen;
   uint32_t next;
 };
 
-// Saturating u64 addition (only "below 2^C" is ever asked of these sums).
-__device__ __forceinline__ uint64_t sat_add(uint64_t a, uint64_t b) {
-  const uint64_t c = a + b;
-  return c < a ? ~0ull : c;
-}
+// Visited set of one BFS.  Visited nodes are numbered in queue order; node
+// v's place is map[v], valid if it carries the BFS's stamp, and its count is
+// sig[place].  So a claim is one scattered 8-byte store (and two stores at
+// the end of the queue), the level of a node is where its place lies among
+// the level starts, and only the map is spread over the n nodes.
+//
+// An LDS filter holds every claimed node: a clear bit proves that a node is
+// unvisited without touching memory.  A node's bit is its id modulo the
+// filter's size: exact where n fits it (the 1024-thread variant's dynamic
+// bitmap, or n up to 2^kBitLog).  Setting a node's bit with
+// a returning LDS atomic claims the node if the bit was clear: of all arcs
+// that reach it one sees the bit clear.  No global atomic takes part in a
+// BFS: they are all carried out at the memory side here, past the L2 (as
+// many EA atomics as L2 atomics were counted), at about 2 us each.
+struct Visited {
+  uint32_t* bits;       // LDS
+  uint32_t mask;        // bit of node v: v & mask
+  bool exact;
+  uint64_t* map;
+  const uint32_t* q;
+  uint64_t* sig;
+  uint64_t base;        // the BFS's stamp << 32
 
-template <int BLOCK>
-__device__ __forceinline__ uint64_t block_sat_sum(uint64_t v, uint64_t* scratch) {
-  constexpr int NW = BLOCK / kWave;
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v = sat_add(v, shfl_xor_u64(v, m));
-  if (lane_id() == 0) scratch[threadIdx.x / kWave] = v;
-  __syncthreads();
-  uint64_t r = 0;
-#pragma unroll
-  for (int i = 0; i < NW; ++i) r = sat_add(r, scratch[i]);
-  __syncthreads();
-  return uniform_u64(r);
-}
-
-// Visited set.  Between levels, "visited" means "in a completed level"
-// (levels 0..L), which is also "claimed by this BFS".  done(v, L) is that
-// test; maybe(v) may answer true for an unvisited node but never false for
-// a visited one; count(v) is sigma'_v for a visited v, else 0; set(v) adds
-// v when its level closes.  base is the current BFS's stamp << 32.
-
-// LDS variant: an exact bitmap of n bits in LDS.
-struct BitsLds {
-  uint32_t* w;
-  uint64_t* rec;
-  uint64_t base;
-  __device__ __forceinline__ bool maybe(uint32_t v) const { return (w[v >> 5] >> (v & 31u)) & 1u; }
-  __device__ __forceinline__ bool done(uint32_t v, uint32_t) const { return maybe(v); }
-  __device__ __forceinline__ uint64_t count(uint32_t v) const { return maybe(v) ? ld_u64(sig_of(rec, v)) : 0ull; }
-  __device__ __forceinline__ void set(uint32_t v) { atomicOr(&w[v >> 5], 1u << (v & 31u)); }
-};
-
-// HBM variant: no bitmap.  A one-hash Bloom filter of kBloomBits bits in
-// LDS holds the nodes of the completed levels: a clear filter bit proves
-// "not visited" without touching HBM (most tests: the visited set is small
-// next to n); a set one defers to the node's tag.
-
-__device__ __forceinline__ uint32_t bloom_bit(uint32_t v) { return (v * 0x9E3779B1u) >> (32 - kBloomLog); }
-
-struct BitsRec {
-  uint64_t* rec;
-  uint32_t* bloom;   // LDS, kBloomWords
-  uint64_t base;
+  __device__ __forceinline__ uint32_t bit(uint32_t v) const { return v & mask; }
   __device__ __forceinline__ bool maybe(uint32_t v) const {
-    const uint32_t b = bloom_bit(v);
-    return (bloom[b >> 5] >> (b & 31u)) & 1u;
+    const uint32_t b = bit(v);
+    return (bits[b >> 5] >> (v & 31u)) & 1u;
   }
-  __device__ __forceinline__ bool done(uint32_t v, uint32_t L) const {
-    return maybe(v) && ld_u64(tag_of(rec, v)) >= level_tag(base, L);
+  // sets v's bit; true if it was clear
+  __device__ __forceinline__ bool set(uint32_t v) const {
+    const uint32_t b = bit(v), m = 1u << (v & 31u);
+    return !(atomicOr(&bits[b >> 5], m) & m);
   }
+  // v's place, kUnseen if v is not visited
+  __device__ __forceinline__ uint32_t place(uint32_t v) const {
+    const uint64_t e = wg_ld_u64(&map[v]) - base;
+    return e < kUnseen ? static_cast<uint32_t>(e) : kUnseen;
+  }
+  __device__ __forceinline__ bool visited(uint32_t v) const { return maybe(v) && (exact || place(v) != kUnseen); }
+  // sigma'_v of a visited v, else 0 (between levels every claimed node is on
+  // a completed one)
   __device__ __forceinline__ uint64_t count(uint32_t v) const {
     if (!maybe(v)) return 0;
-    const uint64_t tg = ld_u64(tag_of(rec, v));   // both loads in flight together
-    const uint64_t c = ld_u64(sig_of(rec, v));
-    return tg >= base ? c : 0ull;
-  }
-  __device__ __forceinline__ void set(uint32_t v) {
-    const uint32_t b = bloom_bit(v);
-    atomicOr(&bloom[b >> 5], 1u << (b & 31u));
+    const uint32_t p = place(v);
+    return p != kUnseen ? wg_ld_u64(&sig[p]) : 0ull;
   }
 };
 
-template <bool LDS_BITS>
-__device__ __forceinline__ typename std::conditional<LDS_BITS, BitsLds, BitsRec>::type make_bits(uint32_t* lds_bits,
-                                                                                              uint64_t* rec,
-                                                                                              uint32_t* bloom) {
-  if constexpr (LDS_BITS) {
-    (void)bloom;
-    return BitsLds{lds_bits, rec, 0};
-  } else {
-    (void)lds_bits;
-    return BitsRec{rec, bloom, 0};
-  }
-}
+// Arcs of a chunk of sources, one source per thread, spread over the
+// workgroup.  The sources with arcs are numbered in thread order; source c
+// holds arcs [off_c, off_c + deg_c) of the chunk.  A round takes kArcs
+// consecutive arcs, arc base + k * BLOCK + tid in a thread's chain k, and
+// marks in a bit mask (in LDS) the arcs that are a source's first: an arc's
+// source is then the number of marks at or before it, less one, which a
+// wave reads off one mask word with a popcount of the marks before.  (A
+// binary search of the offsets takes log2(BLOCK) dependent LDS reads per
+// arc; it was most of the instructions of a level.)  The masks of three
+// rounds are held in turn: a round zeroes the one that the round after the
+// next will use.
+template <int BLOCK>
+struct ArcSpread {
+  SampleShared<BLOCK>& sh;
+  uint32_t turn;     // the mask of the coming round
+  uint32_t before;   // sources that start before the coming round
 
-// Raw counts of one chunk of nodes, one node u per thread (kUnseen for
-// none) with its in-row (start rs_u, length deg_u): sh.sg[tid] = sum of
-// sigma' over u's visited in-neighbours, 0 for a visited u.  For an unvisited u every visited in-neighbour is at the last
-// produced level (a lower one would have put u in a produced level), so
-// this is u's raw count one level below.  Load balanced like the
-// expansion: in-degrees prefix-summed in LDS, UNROLL entries per thread
-// per round, sources found by binary search.  Adds the entries scanned to
-// n_arcs.  Contains barriers; sh.sg is valid on return until the next call.
-template <int BLOCK, int UNROLL, typename Bits>
-__device__ void raw_counts_chunk(const SampleArgs& a, const Bits& bits, uint64_t* rec, uint32_t u, uint32_t rs_u,
-                                 uint32_t deg_u, uint32_t L, SampleShared<BLOCK>& sh, uint64_t& n_arcs) {
-  const int tid = threadIdx.x;
-  uint32_t deg = 0, rs = 0;
-  if (u != kUnseen && !bits.done(u, L)) {
-    rs = rs_u;
-    deg = deg_u;
+  // every mask zero, before the first chunk (a barrier must follow)
+  __device__ __forceinline__ void init() {
+    for (int i = threadIdx.x; i < 3 * Round<BLOCK>::kMasks; i += BLOCK) (&sh.mask[0][0])[i] = 0;
+    turn = 0;
   }
-  uint32_t total;
-  const uint32_t off = block_excl_scan_u32<BLOCK>(deg, &total, sh.scan);
-  n_arcs += total;
-  sh.off[tid] = off;
-  sh.rs[tid] = rs;
-  sh.sg[tid] = 0;
-  __syncthreads();
-  for (uint32_t base = 0; base < total; base += BLOCK * UNROLL) {
-    uint32_t x[UNROLL], j[UNROLL];
+  // marks source start `off` if it lies in the round of arcs from base
+  __device__ __forceinline__ void mark(bool has, uint32_t off, uint32_t base) {
+    const uint32_t o = off - base;
+    if (has && off >= base && o < Round<BLOCK>::kArcs)
+      atomicOr(reinterpret_cast<unsigned long long*>(&sh.mask[turn][o >> 6]), 1ull << (o & 63u));
+  }
+  // the round's sources: src[k] of the thread's arc k (meaningful for arcs
+  // below the chunk's total).  A barrier lies between mark and this.
+  __device__ __forceinline__ void sources(uint32_t (&src)[Round<BLOCK>::kPer]) {
+    constexpr int NM = Round<BLOCK>::kMasks;
+    const int lane = lane_id();
+    const uint32_t wid = uniform_u32(threadIdx.x / kWave);
+    const uint64_t m = lane < NM ? sh.mask[turn][lane] : 0ull;
+    const uint32_t clear = turn == 0 ? 2u : turn - 1u;
+    if (threadIdx.x < NM) sh.mask[clear][threadIdx.x] = 0;
+    turn = turn == 2 ? 0u : turn + 1u;
+    const uint32_t pc = static_cast<uint32_t>(__popcll(m));
+    const uint32_t incl = wave_incl_scan_u32(pc);
+    const uint32_t excl = incl - pc;
 #pragma unroll
-    for (int k = 0; k < UNROLL; ++k) {
+    for (int k = 0; k < Round<BLOCK>::kPer; ++k) {
+      const int w = static_cast<int>(k * (BLOCK / kWave) + wid);
+      // marks before this word, and of the word at or below the lane (its
+      // bit 0, and of the rest shifted down those below the lane)
+      const uint64_t mk = lane_u64(m, w);
+      const uint32_t at = before + lane_u32(excl, w) + static_cast<uint32_t>(mk & 1ull) - 1u;
+      const uint32_t lo = static_cast<uint32_t>(mk >> 1), hi = static_cast<uint32_t>(mk >> 33);
+      src[k] = at + __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
+    }
+    before += lane_u32(incl, kWave - 1);
+  }
+};
+
+// Nodes whose filter bit is set, met in a scan between levels, with the index
+// in `into` of the sum they count for: that of the row's source (kDirect),
+// or the one sh.sg names for it.  Looking a node up takes two
+// dependent trips to memory (its place, its count), so a wave collects the
+// nodes of many rounds in its share of the duplicate table's sums and looks
+// them up together, all loads in flight.
+template <int BLOCK, bool kDirect>
+struct Hits {
+  static constexpr int PER = Round<BLOCK>::kPer;
+  static constexpr uint32_t kCap = PER * kWave;   // entries per wave: a round's at least
+  SampleShared<BLOCK>& sh;
+  const Visited& vis;
+  uint64_t* into;   // LDS
+  uint64_t* list;   // this wave's
+  uint32_t n;       // entries (uniform over the wave)
+  bool any;         // a listed node was visited
+
+  __device__ __forceinline__ Hits(SampleShared<BLOCK>& sh_, const Visited& vis_, uint64_t* into_)
+      : sh(sh_), vis(vis_), into(into_), list(sh_.dsum + uniform_u32(threadIdx.x / kWave) * kCap), n(0), any(false) {}
+  // Adds the round's nodes x[k] (kUnseen: none) of the rows of sources
+  // src[k]; looks the listed nodes up if these no longer fit, or if it is the
+  // last round (which may be empty).  Every lane calls.
+  __device__ __forceinline__ void round(const uint32_t (&x)[PER], const uint32_t (&src)[PER], bool last) {
+    uint64_t m[PER];
+    uint32_t c = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      m[k] = __ballot(x[k] != kUnseen && vis.maybe(x[k]));
+      c += static_cast<uint32_t>(__popcll(m[k]));
+    }
+    for (;;) {
+      if (n + c > kCap || (last && c == 0 && n)) {
+        uint32_t p[PER], r[PER];
+        uint64_t w[PER];
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+          const uint32_t i = k * kWave + lane_id();
+          p[k] = kUnseen;
+          r[k] = 0;
+          if (i < n) {
+            const uint64_t e = list[i];
+            list[i] = 0;
+            r[k] = static_cast<uint32_t>(e);
+            p[k] = vis.place(static_cast<uint32_t>(e >> 32));
+          }
+        }
+#pragma unroll
+        for (int k = 0; k < PER; ++k) w[k] = p[k] != kUnseen ? wg_ld_u64(&vis.sig[p[k]]) : 0ull;
+#pragma unroll
+        for (int k = 0; k < PER; ++k)
+          if (w[k]) {   // (a produced count is never 0)
+            any = true;
+            atomicAdd(reinterpret_cast<unsigned long long*>(&into[r[k]]), static_cast<unsigned long long>(w[k]));
+          }
+        n = 0;
+      }
+      if (c == 0) break;
+#pragma unroll
+      for (int k = 0; k < PER; ++k) {
+        if ((m[k] >> lane_id()) & 1ull)
+          list[n + __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m[k] >> 32),
+                                             __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m[k]), 0))] =
+              uint64_t(x[k]) << 32 | (kDirect ? src[k] : static_cast<uint32_t>(sh.sg[src[k]]));
+        n += static_cast<uint32_t>(__popcll(m[k]));
+      }
+      c = 0;
+      if (!last) break;
+    }
+  }
+};
+
+// Raw counts of one chunk of unvisited nodes, one per thread with its in-row
+// (start rs_u, length deg; 0 for none): returns the sum of sigma' over the
+// node's visited in-neighbours.  Every one of them is at the last produced
+// level (a lower one would have put the node in a produced level), so this
+// is the node's raw count one level below.  Contains barriers.
+template <int BLOCK>
+__device__ __forceinline__ uint64_t raw_counts_chunk(const uint32_t* in_idx, const Visited& vis, uint32_t rs_u,
+                                                     uint32_t deg, SampleShared<BLOCK>& sh, Coll<BLOCK>& co,
+                                                     ArcSpread<BLOCK>& sp) {
+  constexpr int PER = Round<BLOCK>::kPer;
+  constexpr uint32_t R = BLOCK * PER;
+  const uint32_t tid = threadIdx.x;
+  uint32_t off, c, total;
+  co.scan_and_rank(deg, &off, &c, &total);
+  if (total == 0) return 0;   // uniform
+  if (deg) {
+    sh.rs[c] = rs_u - off;
+    sh.sg[c] = 0;
+  }
+  sp.before = 0;
+  Hits<BLOCK, true> hits(sh, vis, sh.sg);
+  for (uint32_t base = 0; base < total; base += R) {
+    sp.mark(deg != 0, off, base);
+    __syncthreads();
+    uint32_t x[PER], j[PER];
+    sp.sources(j);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
       const uint32_t e = base + k * BLOCK + tid;
       x[k] = kUnseen;
-      j[k] = 0;
-      if (e < total) {
-        int lo = 0, hi = BLOCK - 1;
-        while (lo < hi) {
-          const int mid = (lo + hi + 1) >> 1;
-          if (sh.off[mid] <= e)
-            lo = mid;
-          else
-            hi = mid - 1;
-        }
-        j[k] = lo;
-        x[k] = a.in_idx[sh.rs[lo] + (e - sh.off[lo])];
-      }
+      if (e < total) x[k] = in_idx[sh.rs[j[k]] + e];
     }
-#pragma unroll
-    for (int k = 0; k < UNROLL; ++k) {
-      const uint64_t c = x[k] != kUnseen ? bits.count(x[k]) : 0ull;   // 0: unvisited
-      if (c) atomicAdd(reinterpret_cast<unsigned long long*>(&sh.sg[j[k]]), static_cast<unsigned long long>(c));
-    }
+    hits.round(x, j, base + R >= total);
   }
   __syncthreads();
-}
-
-// Exclusive scan of one u64 per thread in thread order, with the total.
-template <int BLOCK>
-__device__ __forceinline__ uint64_t block_excl_scan_u64(uint64_t v, uint64_t* total, uint64_t* scratch) {
-  constexpr int NW = BLOCK / kWave;
-  const int wid = threadIdx.x / kWave;
-  const uint64_t incl = wave_incl_scan_u64(v);
-  if (lane_id() == kWave - 1) scratch[wid] = incl;
-  __syncthreads();
-  uint64_t before = 0, tot = 0;
-#pragma unroll
-  for (int i = 0; i < NW; ++i) {
-    const uint64_t x = scratch[i];
-    before += i < wid ? x : 0ull;
-    tot += x;
-  }
-  __syncthreads();
-  *total = uniform_u64(tot);
-  return before + incl - v;
+  // (sg is written again only after the next chunk's scan, which has a barrier)
+  return deg ? sh.sg[c] : 0ull;
 }
 
 // Weighted pick over entries j = 0 .. len-1 in ascending order, workgroup
-// wide: W = sum of weight(j) (or W_known when nonzero, the caller's exact
+// wide: W = sum of the weights (or W_known when nonzero, the caller's exact
 // sum), r = bounded(st, W), and the result is the smallest j whose
 // inclusive prefix sum exceeds r; kUnseen when W = 0.  Each thread holds
 // kPickPer consecutive entries per round, so a round covers BLOCK *
 // kPickPer entries with that many loads in flight; rows of at most one
-// round are summed and searched from the same registers.  Uniform control
-// flow; every thread draws the same words.
+// round are summed and searched from the same registers.  load(j0, cnt, w)
+// fills w[0 .. cnt) for entries j0 on (cnt <= kPickPer, all at once); the
+// one thread that holds the pick calls chosen(k, j, weight), for its entry
+// k of the round, and what it leaves in LDS is there for every thread on
+// return.  Uniform control flow; every thread draws the same words.
 constexpr uint32_t kPickPer = 4;
 
-template <int BLOCK, typename F>
-__device__ uint32_t block_pick(uint32_t len, const F& weight, uint64_t W_known, WordStream& st,
-                               SampleShared<BLOCK>& sh) {
+template <int BLOCK, typename Load, typename Chosen>
+__device__ __forceinline__ uint32_t block_pick(uint32_t len, const Load& load, const Chosen& chosen, uint64_t W_known,
+                                               RolledWordStream& st, SampleShared<BLOCK>& sh, Coll<BLOCK>& co) {
   constexpr uint32_t kRound = BLOCK * kPickPer;
   const uint32_t first = threadIdx.x * kPickPer;
   uint64_t x[kPickPer];
   uint64_t W = W_known, run = 0, r = 0;
-  if (len > kRound && !W) {
-    for (uint32_t c = 0; c < len; c += kRound) {
-      uint64_t ts = 0;
-#pragma unroll
-      for (uint32_t k = 0; k < kPickPer; ++k) ts += c + first + k < len ? weight(c + first + k) : 0ull;
-      W += block_sum_u64<BLOCK>(ts, sh.red);
-    }
-    if (!W) return kUnseen;
-  }
+  // sum the row first if it is longer than a round and its sum is unknown
+  bool summing = len > kRound && !W;
   if (W) r = bounded(st, W);
-  for (uint32_t c = 0; c < len; c += kRound) {
-    uint64_t ts = 0;
+  for (uint32_t c = 0; c < len;) {
+    const uint32_t j0 = c + first;
+    const uint32_t cnt = j0 < len ? (len - j0 < kPickPer ? len - j0 : kPickPer) : 0u;
 #pragma unroll
-    for (uint32_t k = 0; k < kPickPer; ++k) {
-      x[k] = c + first + k < len ? weight(c + first + k) : 0ull;
-      ts += x[k];
-    }
-    uint64_t tot;
-    uint64_t incl = run + block_excl_scan_u64<BLOCK>(ts, &tot, sh.red);
-    if (!W) {   // single round, sum not known before: draw now
-      W = tot;
+    for (uint32_t k = 0; k < kPickPer; ++k) x[k] = 0;
+    load(j0, cnt, x);
+    uint64_t ts = 0, tot;
+#pragma unroll
+    for (uint32_t k = 0; k < kPickPer; ++k) ts += x[k];
+    uint64_t excl = run + co.scan(ts, &tot);
+    c += kRound;
+    if (!W && (!summing || c >= len)) {   // the sum is complete: draw
+      W = run + tot;
       if (!W) return kUnseen;
       r = bounded(st, W);
-    }
-    if (run + tot > r) {
-      uint32_t cand = kUnseen;
-#pragma unroll
-      for (uint32_t k = 0; k < kPickPer; ++k) {
-        incl += x[k];
-        if (cand == kUnseen && incl > r) cand = c + first + k;
+      if (summing) {   // search the row from its start
+        summing = false;
+        c = 0;
+        run = 0;
+        continue;
       }
-      return ~static_cast<uint32_t>(block_max_u64<BLOCK>(uint64_t(~cand), sh.red));   // uniform
+    }
+    if (!summing && run + tot > r) {
+      if (excl <= r && r < excl + ts) {
+#pragma unroll
+        for (uint32_t k = 0; k < kPickPer; ++k) {
+          if (excl <= r && r < excl + x[k]) {
+            sh.pk[0] = j0 + k;
+            chosen(k, j0 + k, x[k]);
+          }
+          excl += x[k];
+        }
+      }
+      __syncthreads();
+      return uniform_u32(sh.pk[0]);
     }
     run += tot;
   }
   return kUnseen;
 }
 
-// Backtrack weight of in-neighbour w of a node at level want + 1: sigma'_w
-// if w is at level want of this BFS, else 0 (both loads issued together).
-template <typename Bits>
-__device__ __forceinline__ uint64_t pred_weight(const Bits& bits, uint64_t* rec, uint32_t w, uint32_t want) {
-  if (!bits.maybe(w)) return 0;
-  const uint64_t tg = ld_u64(tag_of(rec, w));
-  const uint64_t c = ld_u64(sig_of(rec, w));
-  return tg == level_tag(bits.base, want) ? c : 0ull;
-}
-
 __device__ __forceinline__ uint32_t caller_id(const SampleArgs& a, uint32_t v) { return a.orig_of ? a.orig_of[v] : v; }
 
 // A BFS past its scan budget is handed over only on a level of at least
-// this many nodes: the device-wide BFS pays a host round trip per level, so
-// deep, narrow searches (long grids) stay on their workgroups.
+// this many nodes or arcs (a few hubs hold millions): the device-wide BFS
+// pays a host round trip per level, so deep, narrow searches (long grids)
+// stay on their workgroups.
 constexpr uint32_t kWideMinWidth = 4096;
+constexpr uint64_t kWideMinArcs = 65536;
 
 // Appends work item idx to the deferred list (workgroup uniform); true if
 // it fit, the sample then being left to the device-wide BFS.
@@ -368,14 +429,25 @@ __device__ __forceinline__ bool defer_sample(const SampleArgs& a, uint32_t idx, 
   return at < a.defer_cap;
 }
 
+// One graph and sample stream, as a work item sees them.
+struct GraphArgs {
+  uint32_t n, c_bits, max_out_deg, instance;
+  const uint32_t* row_ptr;
+  const uint32_t* col_idx;
+  const uint32_t* in_ptr;
+  const uint32_t* in_idx;
+  const uint32_t* new_of;
+  const uint32_t* orig_of;
+  uint64_t seed, first;
+};
 // Cost rule of the hub 2-hop test at a level (queue entries [lb, le)):
 // true when the in-rows of t's dt in-neighbours (starting at in_idx[tb])
 // hold at most kPairRatio times the out-arcs of the level.  Both sums grow
 // chunk by chunk only until the comparison is decided; the in-row sum and
 // its position persist in sh across levels.  Uniform; contains barriers.
 template <int BLOCK>
-__device__ __forceinline__ bool hub_rule(const SampleArgs& g, const uint32_t* q, uint32_t tb, uint32_t dt, uint32_t lb,
-                                      uint32_t le, SampleShared<BLOCK>& sh, uint64_t& n_arcs) {
+__device__ __forceinline__ bool hub_rule(const GraphArgs& g, const uint32_t* q, uint32_t tb, uint32_t dt, uint32_t lb,
+                                      uint32_t le, SampleShared<BLOCK>& sh, Coll<BLOCK>& co, uint64_t& n_arcs) {
   const uint32_t tid = threadIdx.x;
   uint32_t hpos = uniform_u32(sh.hpos);
   uint64_t hub = uniform_u64(sh.hub_pairs);
@@ -399,17 +471,17 @@ __device__ __forceinline__ bool hub_rule(const SampleArgs& g, const uint32_t* q,
         const uint32_t w = g.in_idx[tb + e];
         c = g.in_ptr[w + 1] - g.in_ptr[w];
       }
-      hub += block_sum_u64<BLOCK>(c, sh.red);
+      hub += co.sum(c);
       n_arcs += dt - hpos < uint32_t(BLOCK) ? dt - hpos : uint32_t(BLOCK);
       hpos += BLOCK;
     } else {
       const uint32_t i = fpos + tid;
       uint64_t c = 0;
       if (i < le) {
-        const uint32_t w = ld_u32(&q[i]);
+        const uint32_t w = wg_ld_u32(&q[i]);
         c = g.row_ptr[w + 1] - g.row_ptr[w];
       }
-      fpart += block_sum_u64<BLOCK>(c, sh.red);
+      fpart += co.sum(c);
       fpos += BLOCK;
     }
   }
@@ -435,98 +507,230 @@ __device__ __forceinline__ int ring_of(const uint32_t* poff, uint32_t dt, uint32
   return lo;
 }
 
-// Up to 512 threads the kernel is held to 6 waves per SIMD (at most 80
-// VGPRs, some spill; with the 16 Kbit filter 12 workgroups of 128 threads
-// fit a CU's LDS): more resident BFSs hide more of the latency of their
-// dependent random accesses than the spill costs.
+// log2 of a duplicate table's size
+__host__ __device__ constexpr int dup_log(uint32_t r) { return r <= 1 ? 0 : 1 + dup_log(r / 2); }
+
+// Appends the wave's newly claimed nodes to the queue: their places follow
+// one LDS atomic per wave (none in a workgroup of one wave, whose queue
+// length qn is a register).  Returns the thread's place.
+template <int BLOCK>
+__device__ __forceinline__ uint32_t append(bool has, uint32_t v, uint32_t le, const Visited& vis, uint32_t* q,
+                                           SampleShared<BLOCK>& sh, uint32_t& qn) {
+  const uint64_t m = __ballot(has);
+  if (!m) return 0;   // uniform over the wave
+  uint32_t at;
+  if constexpr (BLOCK == kWave) {
+    at = qn;
+    qn += static_cast<uint32_t>(__popcll(m));
+  } else {
+    uint32_t base = 0;
+    if (lane_id() == 0) base = atomicAdd(&sh.qlen, static_cast<uint32_t>(__popcll(m)));
+    at = uniform_u32(base);
+  }
+  at += __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
+                                  __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0));
+  if (has) {
+    wg_st_u64(&vis.map[v], vis.base | at);
+    wg_st_u32(&q[at], v);
+    if (at - le < uint32_t(BLOCK)) sh.fr[at - le] = v;
+  }
+  return at;
+}
+
+// Arcs of an expansion whose target's bit was already set.  Each reaches a
+// node of a completed level (dropped), a node of the level being produced
+// (its contribution is added), or an unvisited node whose bit another node
+// set (claimed now).  Their contributions are summed per node in an LDS hash
+// table, and a flush looks every node of the table up, all loads in flight
+// together: one thread per node then adds the sum or claims the node, so no
+// global atomic is needed, and the two trips to memory of a look-up are paid
+// per table, not per round.  A workgroup of one wave fills the table over
+// several rounds; with more waves it is flushed after every round, whose
+// arcs it holds at most.
+template <int BLOCK>
+struct Dups {
+  static constexpr uint32_t kSlots = Round<BLOCK>::kArcs;
+  static constexpr int kPer = kSlots / BLOCK;
+  SampleShared<BLOCK>& sh;
+  const Visited& vis;
+  uint32_t n;   // nodes in the table (workgroups of one wave)
+
+  __device__ __forceinline__ void flush(uint32_t le, uint32_t* q, uint32_t& qn, uint64_t& mx, uint64_t& added) {
+    __syncthreads();   // the table's entries and the new nodes are in place
+    uint32_t v[kPer], p[kPer];
+    uint64_t x[kPer], old[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      const uint32_t i = k * BLOCK + threadIdx.x;
+      v[k] = sh.dkey[i];
+      x[k] = sh.dsum[i];
+      sh.dkey[i] = kUnseen;
+      sh.dsum[i] = 0;
+      p[k] = v[k] != kUnseen ? vis.place(v[k]) : 0u;
+    }
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) old[k] = p[k] >= le && p[k] != kUnseen ? wg_ld_u64(&vis.sig[p[k]]) : 0ull;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      const bool claims = p[k] == kUnseen;
+      const uint32_t at = append<BLOCK>(claims, v[k], le, vis, q, sh, qn);
+      if (p[k] >= le) {   // (completed levels and empty slots lie below)
+        added = sat_add(added, x[k]);
+        const uint64_t c = old[k] + x[k];
+        wg_st_u64(&vis.sig[claims ? at : p[k]], c);
+        mx = c > mx ? c : mx;
+      }
+    }
+    n = 0;
+    __syncthreads();   // the table is empty, the counts are in place
+  }
+  // adds c for node v (every slot taken at most once per round's arc, so a
+  // free one is found)
+  __device__ __forceinline__ bool put(uint32_t v, uint64_t c) {
+    uint32_t h = (v * 0x9E3779B1u) >> (32 - dup_log(kSlots));
+    uint32_t was;
+    for (;;) {
+      was = atomicCAS(&sh.dkey[h], kUnseen, v);
+      if (was == kUnseen || was == v) break;
+      h = (h + 1) & (kSlots - 1);
+    }
+    atomicAdd(reinterpret_cast<unsigned long long*>(&sh.dsum[h]), static_cast<unsigned long long>(c));
+    return was == kUnseen;
+  }
+};
+
+// The last level start before place `end` (> 0), a place of the level before
+// the one that starts there: the highest set bit below it, 64 words a step.
+__device__ __forceinline__ uint32_t last_start(const uint64_t* starts, uint32_t end) {
+  const uint32_t last = (end - 1) >> 6;
+  for (uint32_t w0 = last;; w0 -= kWave) {   // (bit 0 is set: level 0 starts there)
+    const uint32_t lane = lane_id();
+    uint64_t x = lane <= w0 ? wg_ld_u64(&starts[w0 - lane]) : 0ull;
+    if (w0 - lane == last) x &= ~0ull >> (63u - ((end - 1) & 63u));
+    const uint64_t m = __ballot(x != 0);
+    if (m) {
+      const int l = __ffsll(static_cast<unsigned long long>(m)) - 1;
+      return (w0 - l) * 64 + 63 - static_cast<uint32_t>(__clzll(lane_u64(x, l)));
+    }
+  }
+}
+
+// Work items a workgroup takes at once while more than kTakeWhile per
+// workgroup are left (then one at a time, to end together).
+constexpr uint32_t kTake = 4, kTakeWhile = 16;
+
+// The instance table is not written during a launch: read through the
+// constant address space it comes by scalar loads.
+using ConstInst = const SampleInst __attribute__((address_space(4)))*;
+
+// Up to 512 threads the kernel is held to 4 waves per SIMD (128 VGPRs): at 5
+// it spills 40 registers and is slower (BA n = 10^6: 16.3 against 15.5 ms).
 //
 // MULTI: a fused launch over several graphs (sample pools).  Each work
-// item's graph is looked up in the instance table and its arguments are
-// placed in LDS, from where the BFS reads them; every other step is the
+// item's graph is looked up in the instance table; every other step is the
 // same, so each hyperedge equals that of a launch on its graph alone.
-template <int BLOCK, int UNROLL, bool LDS_BITS, bool MULTI = false>
-__global__ __launch_bounds__(BLOCK, BLOCK <= 512 ? 6 : 1) void k_sample_paths(SampleArgs a) {
+template <int BLOCK, bool LDS_BITS, bool MULTI = false>
+__global__ __launch_bounds__(BLOCK, BLOCK <= 512 ? 4 : 1) void k_sample_paths(SampleArgs a) {
+  constexpr int PER = Round<BLOCK>::kPer;
+  constexpr uint32_t R = Round<BLOCK>::kArcs;   // arcs of an expansion round, slots of the duplicate table
   __shared__ SampleShared<BLOCK> sh;
-  __shared__ typename std::conditional<MULTI, SampleArgs, char>::type item_args;
   extern __shared__ uint32_t dyn_bits[];
-  const int tid = threadIdx.x;
+  const uint32_t tid = threadIdx.x;
   const int lane = lane_id();
-  const int wid = tid / kWave;
   const size_t slot = blockIdx.x;
-  uint64_t* rec = a.rec + 2 * slot * a.slot_stride;
   uint32_t* q = a.q + slot * a.slot_stride;
-  uint64_t* praw = a.praw + slot * kPairMax;
+  uint64_t* starts = a.starts + slot * start_words(a.slot_stride);
   uint32_t* pu = a.pinfo + slot * 3 * kPairMax;   // per pair: u, in_ptr[u], in-degree of u
   uint32_t* prs = pu + kPairMax;
   uint32_t* pdg = prs + kPairMax;
-  using Bits = typename std::conditional<LDS_BITS, BitsLds, BitsRec>::type;
-  Bits bits = make_bits<LDS_BITS>(dyn_bits, rec, sh.bloom);
-  const uint64_t lane_lt = (1ull << lane) - 1ull;
-
+  Visited vis{};
+  vis.bits = LDS_BITS ? dyn_bits : sh.bits;
+  vis.mask = LDS_BITS ? ~0u : (1u << kBitLog) - 1u;
+  vis.map = a.map + slot * a.slot_stride;
+  vis.q = q;
+  vis.sig = a.sig + slot * a.slot_stride;
+  Coll<BLOCK> co{sh.red, 0};
+  ArcSpread<BLOCK> sp{sh, 0, 0};
+  sp.init();
+  for (uint32_t i = tid; i < R; i += BLOCK) {
+    sh.dkey[i] = kUnseen;
+    sh.dsum[i] = 0;
+  }
   if (LDS_BITS)
     for (uint32_t i = tid; i < a.bit_words; i += BLOCK) dyn_bits[i] = 0;
-  // work counters (uniform across the workgroup): arcs scanned, nodes visited
-  uint64_t n_arcs = 0, n_nodes = 0;
+  // work counters (uniform across the workgroup): arcs scanned, nodes
+  // visited, hyperedge entries staged
+  uint64_t n_arcs = 0, n_nodes = 0, n_entries = 0;
+  // the rest of the workgroup's chunk of the staging area (thread 0)
+  uint64_t st_pos = 0;
+  uint32_t st_left = 0;
 
-  for (;;) {
-    if (tid == 0) sh.next = atomicAdd(a.work, 1u);
-    __syncthreads();
-    const uint32_t idx = uniform_u32(sh.next);
-    __syncthreads();
-    if (idx >= a.count) break;
+  // Work items: the first is the workgroup's own number, later ones come
+  // from the counter, kTake at a time while many are left (every workgroup
+  // adds to the one word, at the memory side).
+  uint32_t idx = blockIdx.x, in_hand = 1;
+  uint32_t inst_lo = 0, inst_beg = 0, inst_end = 0;   // fused launches: the item's instance and its items
+  while (idx < a.count) {
+    GraphArgs g;
     if constexpr (MULTI) {
-      if (tid == 0) {
-        // the pool of work item idx: the last j with item_off[j] <= idx
-        uint32_t lo = 0, hi = a.n_inst - 1;
-        while (lo < hi) {
-          const uint32_t mid = (lo + hi + 1) >> 1;
-          if (a.item_off[mid] <= idx)
-            lo = mid;
-          else
-            hi = mid - 1;
+      // the instance of work item idx: the last j with item_off[j] <= idx;
+      // 64 candidates a step, and none while the instance stays the same
+      if (idx < inst_beg || idx >= inst_end) {
+        uint32_t lo = 0, size = a.n_inst;
+        while (size > 1) {
+          const uint32_t step = (size + kWave - 1) / kWave;
+          const uint32_t j = lo + static_cast<uint32_t>(lane) * step;
+          const uint64_t m = __ballot(j < lo + size && a.item_off[j < lo + size ? j : lo] <= idx);
+          const uint32_t s = 63u - static_cast<uint32_t>(__clzll(m));   // lane 0 always holds
+          size = lo + size - (lo + s * step) < step ? lo + size - (lo + s * step) : step;
+          lo += s * step;
         }
-        const SampleInst ins = a.inst[lo];
-        SampleArgs v = a;
-        v.n = ins.n;
-        v.c_bits = ins.c_bits;
-        v.max_out_deg = ins.max_out_deg;
-        v.row_ptr = ins.row_ptr;
-        v.col_idx = ins.col_idx;
-        v.in_ptr = ins.in_ptr;
-        v.in_idx = ins.in_idx;
-        v.new_of = ins.new_of;
-        v.orig_of = ins.orig_of;
-        v.seed = ins.seed;
-        v.instance = ins.instance;
-        v.first = ins.first - a.item_off[lo];   // sample = first + idx (mod 2^64)
-        item_args = v;
+        inst_lo = uniform_u32(lo);
+        inst_beg = uniform_u32(a.item_off[inst_lo]);
+        inst_end = uniform_u32(a.item_off[inst_lo + 1]);
       }
-      __syncthreads();
+      const ConstInst ip = reinterpret_cast<ConstInst>(reinterpret_cast<uintptr_t>(a.inst)) + inst_lo;
+      g.n = ip->n;
+      g.c_bits = ip->c_bits;
+      g.max_out_deg = ip->max_out_deg;
+      g.instance = ip->instance;
+      g.row_ptr = ip->row_ptr;
+      g.col_idx = ip->col_idx;
+      g.in_ptr = ip->in_ptr;
+      g.in_idx = ip->in_idx;
+      g.new_of = ip->new_of;
+      g.orig_of = ip->orig_of;
+      g.seed = ip->seed;
+      g.first = ip->first - inst_beg;   // sample = first + idx (mod 2^64)
+    } else {
+      g = GraphArgs{a.n, a.c_bits, a.max_out_deg, a.instance, a.row_ptr, a.col_idx, a.in_ptr,
+                    a.in_idx, a.new_of, a.orig_of, a.seed, a.first};
     }
-    const SampleArgs& g = [&]() -> const SampleArgs& {
-      if constexpr (MULTI) return item_args; else return a;
-    }();
     const uint64_t cap = g.c_bits >= 64 ? ~0ull : (1ull << g.c_bits);
     const uint64_t sample = g.first + idx;
-    bits.base = uint64_t(a.stamp0 + idx) << 32;
+    vis.base = uint64_t(a.stamp0 + idx) << 32;
+    vis.exact = LDS_BITS || g.n <= (1u << kBitLog);
 
     // pair draw: every thread draws the same words (uniform, no broadcast)
-    WordStream st(g.seed, sample, g.instance, 0);
+    RolledWordStream st(g.seed, sample, g.instance, 0);
     const uint32_t s0 = static_cast<uint32_t>(bounded(st, g.n));
     const uint32_t tp = static_cast<uint32_t>(bounded(st, g.n - 1));
     const uint32_t t0 = tp + (tp >= s0 ? 1u : 0u);
     const uint32_t s = g.new_of ? g.new_of[s0] : s0;   // traversal ids
     const uint32_t t = g.new_of ? g.new_of[t0] : t0;
 
-    if (!LDS_BITS) {
-      for (uint32_t i = tid; i < kBloomWords; i += BLOCK) sh.bloom[i] = 0;
-      __syncthreads();
+    if constexpr (!LDS_BITS) {
+      // the filter starts with s alone
+      const uint32_t sb = vis.bit(s);
+      for (uint32_t i = tid; i < kBitWords; i += BLOCK) sh.bits[i] = i == sb >> 5 ? 1u << (sb & 31u) : 0u;
     }
     if (tid == 0) {
-      st_u64(tag_of(rec, s), level_tag(bits.base, 0));
-      st_u64(sig_of(rec, s), 1);
-      st_u32(&q[0], s);
-      bits.set(s);
+      wg_st_u64(&vis.map[s], vis.base);
+      wg_st_u64(&vis.sig[0], 1);
+      wg_st_u32(&q[0], s);
+      wg_st_u64(&starts[0], 1);
+      sh.fr[0] = s;
+      if (LDS_BITS) (void)vis.set(s);
       sh.qlen = 1;
     }
 
@@ -539,42 +743,61 @@ __global__ __launch_bounds__(BLOCK, BLOCK <= 512 ? 6 : 1) void k_sample_paths(Sa
     const bool rings = dt <= Ring<BLOCK>::kCache;
     uint32_t pairs = 0, cpos = 0;
     uint64_t cone_part = 0;
+    uint32_t tw = kUnseen;   // this thread's in-neighbour of t (when they fit the workgroup)
     if (rings) {
       for (uint32_t cb = 0; cb < dt; cb += BLOCK) {
         const uint32_t i = cb + tid;
-        uint32_t dw = 0;
+        uint32_t dw = 0, r0 = 0;
         if (i < dt) {
           const uint32_t w = g.in_idx[tb + i];
-          const uint32_t r0 = g.in_ptr[w];
+          if (cb == 0) tw = w;
+          r0 = g.in_ptr[w];
           dw = g.in_ptr[w + 1] - r0;
-          sh.rw[i] = w;
-          sh.rrs[i] = r0;
         }
-        uint32_t tot;
-        const uint32_t o = block_excl_scan_u32<BLOCK>(dw, &tot, sh.scan);
-        if (i < dt) sh.poff[i] = pairs + o;
-        pairs += tot;
+        uint64_t tot;
+        const uint32_t o = pairs + static_cast<uint32_t>(co.scan(dw, &tot));
+        if (i < dt) {
+          sh.poff[i] = o;
+          sh.rrs[i] = r0 - o;
+          sh.ring[i] = 0;
+        }
+        pairs += static_cast<uint32_t>(tot);
       }
       n_arcs += dt;
     }
     __syncthreads();
-    // sizes the cone over the next BLOCK pairs, keeping each pair's u and
-    // in-row for the 3-hop test
+    // sizes the cone over the next pairs, kConeStep per thread, keeping each
+    // pair's u and in-row for the 3-hop test
+    constexpr uint32_t kConeStep = 4;
     auto cone_step = [&]() {
-      const uint32_t p = cpos + tid;
-      uint32_t dg = 0;
-      if (p < pairs) {
-        const int i = ring_of(sh.poff, dt, p);
-        const uint32_t u = g.in_idx[sh.rrs[i] + (p - sh.poff[i])];
-        const uint32_t r0 = g.in_ptr[u];
-        dg = g.in_ptr[u + 1] - r0;
-        st_u32(&pu[p], u);
-        st_u32(&prs[p], r0);
-        st_u32(&pdg[p], dg);
+      uint32_t u[kConeStep], r0[kConeStep], r1[kConeStep];
+      uint64_t dg = 0;
+#pragma unroll
+      for (uint32_t k = 0; k < kConeStep; ++k) {
+        const uint32_t p = cpos + k * BLOCK + tid;
+        u[k] = kUnseen;
+        if (p < pairs) u[k] = g.in_idx[sh.rrs[ring_of(sh.poff, dt, p)] + p];
       }
-      cone_part += block_sum_u64<BLOCK>(dg, sh.red);
-      n_arcs += pairs - cpos < BLOCK ? pairs - cpos : BLOCK;
-      cpos += BLOCK;
+#pragma unroll
+      for (uint32_t k = 0; k < kConeStep; ++k) {
+        r0[k] = u[k] != kUnseen ? g.in_ptr[u[k]] : 0u;
+        r1[k] = u[k] != kUnseen ? g.in_ptr[u[k] + 1] : 0u;
+      }
+#pragma unroll
+      for (uint32_t k = 0; k < kConeStep; ++k) {
+        const uint32_t p = cpos + k * BLOCK + tid;
+        if (p < pairs) {
+          dg += r1[k] - r0[k];
+          if (p < kPairMax) {
+            wg_st_u32(&pu[p], u[k]);
+            wg_st_u32(&prs[p], r0[k]);
+            wg_st_u32(&pdg[p], r1[k] - r0[k]);
+          }
+        }
+      }
+      cone_part += co.sum(dg);
+      n_arcs += pairs - cpos < kConeStep * BLOCK ? pairs - cpos : kConeStep * BLOCK;
+      cpos += kConeStep * BLOCK;
     };
     // Depth of t's ancestors when the rings show it: every ancestor of t is
     // within backward distance `depth`, so a reachable t has d <= depth and
@@ -591,6 +814,26 @@ __global__ __launch_bounds__(BLOCK, BLOCK <= 512 ? 6 : 1) void k_sample_paths(Sa
       }
     }
 
+    // Row i of `rows` (start, length; none past the end): the in-row of pair
+    // i's u, kept by cone_step, or of t's i-th in-neighbour w.
+    auto row_of = [&](bool cone, uint32_t i, uint32_t rows, uint32_t* r0, uint32_t* dg) {
+      *r0 = 0;
+      *dg = 0;
+      if (i >= rows) return;
+      if (cone) {
+        *r0 = wg_ld_u32(&prs[i]);
+        *dg = wg_ld_u32(&pdg[i]);
+      } else if (rings) {
+        const uint32_t o = sh.poff[i];
+        *r0 = sh.rrs[i] + o;
+        *dg = (i + 1 < dt ? sh.poff[i + 1] : pairs) - o;
+      } else {
+        const uint32_t w = g.in_idx[tb + i];
+        *r0 = g.in_ptr[w];
+        *dg = g.in_ptr[w + 1] - *r0;
+      }
+    };
+
     // The 2-hop test of a t with more in-neighbours than the ring cache
     // scans the in-rows of all of them (sh.hub_pairs entries, sized lazily
     // over in(t) entries [0, sh.hpos); kept in LDS, as they are read once
@@ -600,160 +843,152 @@ __global__ __launch_bounds__(BLOCK, BLOCK <= 512 ? 6 : 1) void k_sample_paths(Sa
     if (tid == 0) {
       sh.hpos = 0;
       sh.hub_pairs = 0;
+      if (!rings) sh.ring[0] = 0;
     }
+    if (!rings) __syncthreads();   // hpos is read at the first level
     uint32_t lb = 0, le = 1, L = 0, d = kUnseen;
+    uint32_t qn = 1;          // queue length (workgroups of one wave; else sh.qlen)
     uint64_t sumL = 1;        // S_L: sum of the level-L counts (saturating)
     uint32_t shortcut = 0;    // 2 or 3: levels L+1 (and L+2) were not produced
-    uint64_t w_short = 0;     // W of the first backtrack step when shortcut
     uint64_t shifted = 0;     // bit l: the counts of produced level l < 64 were shifted
     // t without in-neighbours is unreachable: no BFS at all (on skewed
     // directed graphs such targets are common, and s may reach millions)
-    bool deferred = false;
+    bool deferred = false, ended = false;
     const uint64_t arcs0 = n_arcs;   // this BFS's scans are n_arcs - arcs0
     for (; dt != 0;) {
       // (1) a visited in-neighbour of t: it is at level L (an earlier check
       //     would have fired otherwise), so d = L + 1
-      int found = 0;
+      bool found = false;
       n_arcs += dt;
-      for (uint32_t e = tb + tid; e < te; e += BLOCK)
-        if (bits.done(g.in_idx[e], L)) found = 1;
-      if (__syncthreads_or(found)) {
+      if (rings && dt <= BLOCK) {
+        found = tid < dt && vis.visited(tw);
+      } else {
+        for (uint32_t e = tb + tid; e < te; e += BLOCK)
+          if (vis.visited(g.in_idx[e])) found = true;
+      }
+      if (co.any(found)) {
         d = L + 1;
         break;
       }
       if (L + 1 >= depth) break;   // every d <= depth ruled out: unreachable
-      if (rings) {
-        // out-arcs of level L (the cost of expanding it), summed in
-        // workgroup chunks only as far as a cost rule below needs: most
-        // produced levels are never expanded
-        uint32_t fpos = lb;
-        uint64_t fpart = 0;
-        auto fcost_step = [&]() {
+      // the level's first nodes (from LDS) and their out-rows: the cost
+      // rules and the expansion share them
+      uint32_t f_w = 0, f_rs = 0, f_deg = 0;
+      if (tid < le - lb) {
+        f_w = sh.fr[tid];
+        f_rs = g.row_ptr[f_w];
+        f_deg = g.row_ptr[f_w + 1] - f_rs;
+      }
+      // out-arcs of level L (the cost of expanding it), summed in workgroup
+      // chunks only as far as a cost rule below needs: most produced levels
+      // are never expanded
+      uint32_t fpos = lb;
+      uint64_t fpart = 0;
+      auto fcost_step = [&]() {
+        uint32_t c = f_deg;
+        if (fpos != lb) {
           const uint32_t i = fpos + tid;
-          uint64_t c = 0;
+          c = 0;
           if (i < le) {
-            const uint32_t w = ld_u32(&q[i]);
+            const uint32_t w = wg_ld_u32(&q[i]);
             c = g.row_ptr[w + 1] - g.row_ptr[w];
           }
-          fpart += block_sum_u64<BLOCK>(c, sh.red);
-          fpos += BLOCK;
-        };
-        const uint64_t need2 = (pairs + kPairRatio - 1) / kPairRatio;
-        while (fpos < le && fpart < need2) fcost_step();
-        if (fpart >= need2) {
-          // (2) pairs (w, u): a visited u is at level L (w is unvisited, so a
-          //     lower level would have put w in a produced level), hence w at
-          //     L+1 and d = L+2; ring_a[i] = sum of sigma'_u over visited u,
-          //     the raw count of w_i
-          for (uint32_t i = tid; i < dt; i += BLOCK) {
-            sh.ring_a[i] = 0;
-            sh.ring_b[i] = 0;
-          }
-          __syncthreads();
-          int hit2 = 0;
-          for (uint32_t p = tid; p < pairs; p += BLOCK) {
-            const int i = ring_of(sh.poff, dt, p);
-            const uint32_t u = g.in_idx[sh.rrs[i] + (p - sh.poff[i])];
-            const uint64_t c = bits.count(u);   // 0: unvisited
-            if (c) {
-              hit2 = 1;
-              atomicAdd(reinterpret_cast<unsigned long long*>(&sh.ring_a[i]), static_cast<unsigned long long>(c));
-            }
-          }
-          n_arcs += pairs;
-          if (__syncthreads_or(hit2)) {
-            if (sumL < cap) {
-              // no count of level L+1 can need a shift (each <= S_L < 2^C)
-              d = L + 2;
-              shortcut = 2;
+        }
+        fpart += co.sum(c);
+        fpos += BLOCK;
+      };
+      // tests (2) and (3): each scans rows for visited entries
+      for (uint32_t hop = 2; hop <= 3; ++hop) {
+        uint32_t rows = 0;
+        if (hop == 3) {
+          // (3) cone: an unvisited u with visited in-neighbours is at L+1
+          //     (they are all at L), its w at L+2 and d = L+3.  Only when
+          //     the counts of levels L+1 and L+2 cannot need a shift (level
+          //     L+1 counts <= S_L, level L+2 counts <= S_{L+1} <= S_L * max
+          //     out-degree) and when the cone is at most kConeRatio times
+          //     the out-arcs of level L.  That comparison grows both sums
+          //     chunk by chunk until it is decided; sizing the cone also
+          //     keeps each pair's u and in-row for the test.  No u is
+          //     visited: test (2) has just ruled it out.
+          if (!rings || pairs > kPairMax) break;
+          const uint64_t bound = (g.max_out_deg && sumL > ~0ull / g.max_out_deg) ? ~0ull : sumL * g.max_out_deg;
+          if (sumL >= cap || bound >= cap) break;
+          for (;;) {
+            const bool cdone = cpos >= pairs, fdone = fpos >= le;
+            if (cdone && cone_part <= kConeRatio * fpart) {
+              rows = pairs;
               break;
             }
-          } else if (L + 2 >= depth) {
-            break;   // every d <= depth ruled out: unreachable
-          } else if (pairs <= kPairMax) {
-            // (3) cone: an unvisited u with visited in-neighbours is at L+1
-            //     (they are all at L), its w at L+2 and d = L+3.  Only when
-            //     the counts of levels L+1 and L+2 cannot need a shift (level
-            //     L+1 counts <= S_L, level L+2 counts <= S_{L+1} <= S_L * max
-            //     out-degree) and when the cone is at most kConeRatio times
-            //     the out-arcs of level L.  That comparison grows both sums
-            //     chunk by chunk until it is decided; sizing the cone also
-            //     keeps each pair's u and in-row for the test.
-            const uint64_t bound =
-                (g.max_out_deg && sumL > ~0ull / g.max_out_deg) ? ~0ull : sumL * g.max_out_deg;
-            bool cheap = false;
-            if (sumL < cap && bound < cap) {
-              for (;;) {
-                const bool cdone = cpos >= pairs, fdone = fpos >= le;
-                if (cdone && cone_part <= kConeRatio * fpart) {
-                  cheap = true;
-                  break;
-                }
-                if (fdone && cone_part > kConeRatio * fpart) break;
-                if (!cdone && (fdone || cone_part <= kConeRatio * fpart))
-                  cone_step();
-                else
-                  fcost_step();
-              }
+            if (fdone && cone_part > kConeRatio * fpart) break;
+            if (!cdone && (fdone || cone_part <= kConeRatio * fpart))
+              cone_step();
+            else
+              fcost_step();
+          }
+        } else if (rings) {
+          // (2) pairs (w, u), the in-rows of t's in-neighbours: a visited u
+          //     is at level L (w is unvisited, so a lower level would have
+          //     put w in a produced level), hence w at L+1 and d = L+2;
+          //     ring[i] = sum of sigma'_u over visited u, the raw count of
+          //     w_i (all zero before: set up so, and a test that hits
+          //     without ending the BFS clears it)
+          const uint64_t need2 = (pairs + kPairRatio - 1) / kPairRatio;
+          while (fpos < le && fpart < need2) fcost_step();
+          if (fpart >= need2) rows = dt;
+        } else if (sumL < cap && hub_rule<BLOCK>(g, q, tb, dt, lb, le, sh, co, n_arcs)) {
+          // the same for a t with more in-neighbours than the ring cache
+          // (their counts are summed in ring[0])
+          rows = dt;
+        }
+        if (!rows) break;
+        Hits<BLOCK, false> hits(sh, vis, sh.ring);
+        const bool cone = hop == 3;
+        uint32_t r0, dg;
+        row_of(cone, tid, rows, &r0, &dg);
+        for (uint32_t cb = 0; cb < rows; cb += BLOCK) {
+          const uint32_t deg = dg, rs = r0;
+          row_of(cone, cb + BLOCK + tid, rows, &r0, &dg);   // on its way meanwhile
+          uint32_t off, c, total;
+          co.scan_and_rank(deg, &off, &c, &total);
+          n_arcs += total;
+          if (deg) {
+            sh.rs[c] = rs - off;
+            sh.sg[c] = cone ? ring_of(sh.poff, dt, cb + tid) : rings ? cb + tid : 0u;
+          }
+          sp.before = 0;
+          const bool last = cb + BLOCK >= rows;
+          for (uint32_t base = 0; base < total || last; base += R) {
+            sp.mark(deg != 0, off, base);
+            __syncthreads();
+            uint32_t x[PER], j[PER];
+            sp.sources(j);
+#pragma unroll
+            for (int k = 0; k < PER; ++k) {
+              const uint32_t e = base + k * BLOCK + tid;
+              x[k] = kUnseen;
+              if (e < total) x[k] = g.in_idx[sh.rs[j[k]] + e];
             }
-            if (cheap) {
-              int hit3 = 0;
-              for (uint32_t cb = 0; cb < pairs; cb += BLOCK) {
-                const uint32_t p = cb + tid;
-                uint32_t u = kUnseen, r0 = 0, dg = 0;
-                int i = 0;
-                if (p < pairs) {
-                  i = ring_of(sh.poff, dt, p);
-                  u = ld_u32(&pu[p]);
-                  r0 = ld_u32(&prs[p]);
-                  dg = ld_u32(&pdg[p]);
-                }
-                raw_counts_chunk<BLOCK, UNROLL>(g, bits, rec, u, r0, dg, L, sh, n_arcs);
-                const uint64_t raw = sh.sg[tid];
-                if (p < pairs) st_u64(&praw[p], raw);
-                if (raw) {
-                  hit3 = 1;
-                  atomicAdd(reinterpret_cast<unsigned long long*>(&sh.ring_b[i]), static_cast<unsigned long long>(raw));
-                }
-                __syncthreads();
-              }
-              if (__syncthreads_or(hit3)) {
-                d = L + 3;
-                shortcut = 3;
-                break;
-              }
-            }
+            const bool end = last && base + R >= total;
+            hits.round(x, j, end);
+            if (end) break;
           }
         }
-      } else if (sumL < cap && hub_rule<BLOCK>(g, q, tb, dt, lb, le, sh, n_arcs)) {
-        // t with more in-neighbours than the ring cache: in-neighbours w of t
-        // at level L+1, raw_w = sum of sigma' over w's in-neighbours at level L
-        uint64_t wsum = 0, wscan = 0;
-        for (uint32_t e = tb + wid; e < te; e += BLOCK / kWave) {
-          const uint32_t w = g.in_idx[e];
-          const uint32_t ub = g.in_ptr[w], ue = g.in_ptr[w + 1];
-          uint64_t x = 0;
-          for (uint32_t f = ub + lane; f < ue; f += kWave) {
-            const uint32_t u = g.in_idx[f];
-            // w is unvisited (check (1) failed), so a visited u is at level L
-            x += bits.count(u);
+        if (co.any(hits.any)) {
+          if (cone || sumL < cap) {
+            // no count of level L+1 can need a shift (each <= S_L < 2^C)
+            d = L + hop;
+            shortcut = hop;
+          } else {
+            for (uint32_t i = tid; i < dt; i += BLOCK) sh.ring[i] = 0;
           }
-          wsum += wave_sum_u64(x);
-          wscan += ue - ub;
+          break;
         }
-        if (lane != 0) {
-          wsum = 0;
-          wscan = 0;
-        }
-        wsum = block_sum_u64<BLOCK>(wsum, sh.red);
-        n_arcs += block_sum_u64<BLOCK>(wscan, sh.red);
-        if (wsum) {
-          d = L + 2;
-          shortcut = 2;
-          w_short = wsum;
+        if (L + hop >= depth) {   // every d <= depth ruled out: unreachable
+          ended = true;
           break;
         }
       }
+      if (shortcut || ended) break;
       if constexpr (!LDS_BITS && !MULTI) {
         // a level too wide for one workgroup, or a wide level of a BFS that
         // has already scanned millions of entries: the sample goes to the
@@ -768,260 +1003,350 @@ __global__ __launch_bounds__(BLOCK, BLOCK <= 512 ? 6 : 1) void k_sample_paths(Sa
       // expand level L (queue entries [lb, le)) into level L+1
       const uint32_t nl = L + 1;
       uint64_t mx = 0, added = 0;
-      for (uint32_t cb = lb; cb < le; cb += BLOCK) {
-        const uint32_t i = cb + tid;
-        uint32_t deg = 0, rs = 0;
-        uint64_t sw = 0;
-        if (i < le) {
-          const uint32_t w = ld_u32(&q[i]);
-          rs = g.row_ptr[w];
-          deg = g.row_ptr[w + 1] - rs;
-          sw = ld_u64(sig_of(rec, w));
-        }
-        uint32_t total;
-        const uint32_t off = block_excl_scan_u32<BLOCK>(deg, &total, sh.scan);
-        n_arcs += total;
-        if constexpr (!LDS_BITS && !MULTI) {
-          // a level whose arcs run past the scan budget (hub frontiers): the
-          // device-wide BFS redraws the sample (uniform; the partial level
-          // is abandoned with the BFS's stamp)
-          if (a.defer_nodes && n_arcs - arcs0 > a.defer_arcs && le - lb >= kWideMinWidth &&
-              defer_sample<BLOCK>(a, idx, sh)) {
-            deferred = true;
-            break;
+      Dups<BLOCK> dups{sh, vis, 0};
+      // rounds of R arcs, chunk of BLOCK frontier nodes after chunk: a
+      // round's targets are loaded while the round before is worked on
+      uint32_t cb = lb, base = 0, total = 0, off = 0, deg = 0;
+      uint64_t lvl_arcs = 0;   // arcs of the level's chunks so far
+      uint32_t v[PER];
+      uint64_t add[PER];
+      for (bool first = true;; first = false) {
+        bool more = base < total;
+        if (!more && cb < le) {   // the next chunk
+          const uint32_t i = cb + tid;
+          uint32_t rs = f_rs;
+          uint64_t sw = 0;
+          deg = 0;
+          if (i < le) {
+            deg = f_deg;
+            if (cb != lb) {
+              const uint32_t w = wg_ld_u32(&q[i]);
+              rs = g.row_ptr[w];
+              deg = g.row_ptr[w + 1] - rs;
+            }
+            sw = wg_ld_u64(&vis.sig[i]);
           }
-        }
-        sh.off[tid] = off;
-        sh.rs[tid] = rs;
-        sh.sg[tid] = sw;
-        __syncthreads();
-        for (uint32_t base = 0; base < total; base += BLOCK * UNROLL) {
-          uint32_t v[UNROLL];
-          uint64_t add[UNROLL];
-          bool act[UNROLL], claimed[UNROLL];
-#pragma unroll
-          for (int k = 0; k < UNROLL; ++k) {
-            const uint32_t e = base + k * BLOCK + tid;
-            act[k] = e < total;
-            v[k] = 0;
-            add[k] = 0;
-            if (act[k]) {
-              // largest j with off[j] <= e (zero-degree entries share the
-              // offset of the next entry, so the largest match has arcs)
-              int lo = 0, hi = BLOCK - 1;
-              while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (sh.off[mid] <= e)
-                  lo = mid;
-                else
-                  hi = mid - 1;
-              }
-              v[k] = g.col_idx[sh.rs[lo] + (e - sh.off[lo])];
-              add[k] = sh.sg[lo];
+          uint32_t c;
+          co.scan_and_rank(deg, &off, &c, &total);
+          n_arcs += total;
+          if (deg) {
+            sh.rs[c] = rs - off;
+            sh.sg[c] = sw;
+          }
+          sp.before = 0;
+          base = 0;
+          cb += BLOCK;
+          more = true;   // (a round of no arcs if the chunk has none)
+          if constexpr (!LDS_BITS && !MULTI) {
+            // a level whose arcs run past the scan budget (hub frontiers): the
+            // device-wide BFS redraws the sample (uniform; the partial level
+            // is abandoned with the BFS's stamp)
+            lvl_arcs += total;
+            if (a.defer_nodes && n_arcs - arcs0 > a.defer_arcs &&
+                (le - lb >= kWideMinWidth || lvl_arcs >= kWideMinArcs) && defer_sample<BLOCK>(a, idx, sh)) {
+              deferred = true;
+              more = false;
             }
           }
+        }
+        uint32_t nv[PER];
+        uint64_t nadd[PER];
+        if (more) {
+          sp.mark(deg != 0, off, base);
+          __syncthreads();
+          uint32_t j[PER];
+          sp.sources(j);
 #pragma unroll
-          for (int k = 0; k < UNROLL; ++k)
-            if (act[k] && bits.done(v[k], L)) act[k] = false;
-          const uint64_t tag_new = level_tag(bits.base, nl);
-#pragma unroll
-          for (int k = 0; k < UNROLL; ++k) {
-            claimed[k] = false;
-            if (act[k])
-              claimed[k] = atomicMax(reinterpret_cast<unsigned long long*>(tag_of(rec, v[k])),
-                                     static_cast<unsigned long long>(tag_new)) < bits.base;
+          for (int k = 0; k < PER; ++k) {
+            const uint32_t e = base + k * BLOCK + tid;
+            nv[k] = 0;
+            nadd[k] = 0;
+            if (e < total) {
+              nv[k] = g.col_idx[sh.rs[j[k]] + e];
+              nadd[k] = sh.sg[j[k]];
+            }
           }
+          base += R;
+        }
+        uint32_t dup = 0, n_dup = 0;   // bit k: arc k's target had its bit set
+        if (!first) {
 #pragma unroll
-          for (int k = 0; k < UNROLL; ++k)
-            if (claimed[k]) st_u64(sig_of(rec, v[k]), add[k]);
-          __syncthreads();   // every claimed count is started before the other arrivals add
-#pragma unroll
-          for (int k = 0; k < UNROLL; ++k) {
-            if (act[k]) {
-              uint64_t x = add[k];
-              if (!claimed[k])
-                x += atomicAdd(reinterpret_cast<unsigned long long*>(sig_of(rec, v[k])),
-                               static_cast<unsigned long long>(add[k]));
-              mx = x > mx ? x : mx;
+          for (int k = 0; k < PER; ++k) {
+            // a node whose bit was clear is new, with this arc's count
+            const bool arc = add[k] != 0;   // (a produced count is never 0)
+            const bool fresh = arc && vis.set(v[k]);
+            const uint32_t at = append<BLOCK>(fresh, v[k], le, vis, q, sh, qn);
+            if (fresh) {
+              wg_st_u64(&vis.sig[at], add[k]);
+              mx = add[k] > mx ? add[k] : mx;
               added = sat_add(added, add[k]);
             }
-            // wave-aggregated append of newly claimed nodes
-            const uint64_t m = __ballot(claimed[k]);
-            if (m) {
-              uint32_t wbase = 0;
-              const int leader = __ffsll(static_cast<unsigned long long>(m)) - 1;
-              if (lane == leader) wbase = atomicAdd(&sh.qlen, static_cast<uint32_t>(__popcll(m)));
-              wbase = __shfl(wbase, leader, kWave);
-              if (claimed[k]) st_u32(&q[wbase + __popcll(m & lane_lt)], v[k]);
-            }
+            const bool again = arc && !fresh;
+            if (again) dup |= 1u << k;
+            if (BLOCK == kWave) n_dup += static_cast<uint32_t>(__popcll(__ballot(again)));
           }
         }
-        __syncthreads();
-      }
-      if (deferred) break;   // uniform
-      const uint32_t ne = uniform_u32(sh.qlen);
-      if (ne == le) break;   // nothing new: t unreachable
-      // level L+1 is complete: its largest raw count decides the shift;
-      // S_{L+1} is the sum of the added contributions, or of the shifted
-      // counts when a shift applies
-      mx = block_max_u64<BLOCK>(mx, sh.red);
-      const uint32_t bl = bitlen64(mx);
-      const uint32_t shift = bl > g.c_bits ? bl - g.c_bits : 0u;
-      uint64_t ssum = 0;
-      for (uint32_t i = le + tid; i < ne; i += BLOCK) {
-        const uint32_t v = ld_u32(&q[i]);
-        bits.set(v);
-        if (shift) {
-          uint64_t x = ld_u64(sig_of(rec, v)) >> shift;
-          x = x ? x : 1ull;
-          st_u64(sig_of(rec, v), x);
-          ssum = sat_add(ssum, x);
+        // the table is looked up when a round may not fit (an eighth stays
+        // free unless a round alone fills it, so that probing ends soon), at
+        // the level's end, and with more than one wave after every round
+        for (bool flush = BLOCK == kWave && dups.n && dups.n + n_dup > dups.kSlots - dups.kSlots / 8;;) {
+          if (flush) dups.flush(le, q, qn, mx, added);
+          bool entered[PER];
+#pragma unroll
+          for (int k = 0; k < PER; ++k) entered[k] = ((dup >> k) & 1u) && dups.put(v[k], add[k]);
+          if (BLOCK == kWave) {
+#pragma unroll
+            for (int k = 0; k < PER; ++k) dups.n += static_cast<uint32_t>(__popcll(__ballot(entered[k])));
+          }
+          dup = 0;
+          const bool again = BLOCK > kWave ? !flush && !first : !more && dups.n;
+          if (!again) break;
+          flush = true;
+        }
+        if (!more) break;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+          v[k] = nv[k];
+          add[k] = nadd[k];
         }
       }
-      if (!shift) ssum = added;
-      if (shift && nl < 64) shifted |= 1ull << nl;
-      sumL = block_sat_sum<BLOCK>(ssum, sh.red);   // contains the barrier closing the level
+      if (deferred) break;   // uniform
+      // level L+1 is complete: its largest raw count decides the shift;
+      // S_{L+1} is the sum of the added contributions, or of the shifted
+      // counts when a shift applies (the collective's barrier closes the
+      // level: its queue entries, counts and filter bits are in place)
+      co.max_and_sat_sum(&mx, &added);
+      const uint32_t ne = BLOCK == kWave ? qn : uniform_u32(sh.qlen);
+      if (ne == le) break;   // nothing new: t unreachable
+      const uint32_t bl = bitlen64(mx);
+      const uint32_t shift = bl > g.c_bits ? bl - g.c_bits : 0u;
+      sumL = added;
+      // the new level's words of the start bitmap: its first place's bit, the
+      // earlier levels' below it, none above
+      for (uint32_t w = (le >> 6) + tid; w <= (ne - 1) >> 6; w += BLOCK) {
+        uint64_t x = 0;
+        if (w == le >> 6) {
+          const uint64_t bit = 1ull << (le & 63u);
+          x = bit | (le & 63u ? wg_ld_u64(&starts[w]) & (bit - 1) : 0ull);
+        }
+        wg_st_u64(&starts[w], x);
+      }
+      if (shift) {
+        uint64_t ssum = 0;
+        for (uint32_t i = le + tid; i < ne; i += BLOCK) {
+          uint64_t x = wg_ld_u64(&vis.sig[i]) >> shift;
+          x = x ? x : 1ull;
+          wg_st_u64(&vis.sig[i], x);
+          ssum = sat_add(ssum, x);
+        }
+        sumL = co.sat_sum(ssum);
+        __syncthreads();   // the level's counts are in place
+        if (nl < 64) shifted |= 1ull << nl;
+      }
       lb = le;
       le = ne;
       L = nl;
     }
 
-    if (deferred) {   // uniform: nothing is staged for this sample here
-      n_nodes += uniform_u32(sh.qlen);
-      __syncthreads();
-      continue;
-    }
-
-    // backtrack: from v = t, pick a predecessor w at level(v) - 1 with
-    // probability sigma'_w / W, scanning in-neighbours in ascending order,
-    // until level 1.  Workgroup wide (block_pick); steps through unproduced
-    // levels (shortcut 2 or 3) take their weights from the ring sums and the
-    // stored pair counts.
-    const uint32_t len = (d != kUnseen && d >= 2) ? d - 1 : 0u;
-    if (tid == 0) {
-      sh.base = len ? atomicAdd(reinterpret_cast<unsigned long long*>(g.stage_used),
-                                static_cast<unsigned long long>(len))
-                    : 0ull;
-    }
-    uint32_t v = t, dv = len ? d : 0u, written = 0;   // no backtrack when t is unreachable or adjacent
-    // W of the next step when known without a summing pass: the raw count
-    // of v, i.e. the sum of its predecessors' counts (a ring sum or stored
-    // pair count after a shortcut step; sigma'_v itself when v was claimed
-    // at a level whose counts were not shifted)
-    uint64_t w_next = 0;
-    bool claimed_v = false;
-    __syncthreads();   // sh.base, ring sums and stored pair counts are visible
-    const uint64_t hbase = uniform_u64(sh.base);
-    bool ok = true;
-    if (dv && shortcut && rings) {
-      // step from t through level d-1: weights ring_a (shortcut 2) or
-      // ring_b (shortcut 3) of t's in-neighbours, in ascending order
-      const uint64_t* wts = shortcut == 2 ? sh.ring_a : sh.ring_b;
-      const uint32_t pi = block_pick<BLOCK>(dt, [&](uint32_t j) { return wts[j]; }, 0, st, sh);
-      if (pi == kUnseen) {
-        ok = false;
-      } else {
-        v = sh.rw[pi];
-        if (tid == 0 && hbase < g.stage_cap) g.stage[hbase] = caller_id(g, v);
-        written = 1;
-        dv = d - 1;
-        w_next = shortcut == 2 ? uniform_u64(sh.ring_a[pi]) : 0ull;
-        if (shortcut == 3) {
-          // step from w (level L+2) through level L+1: weights raw_u of the
-          // pairs (w, u), stored by the cone test in in(w) order; their sum
-          // is ring_b of w, i.e. sigma'_w
-          const uint32_t p0 = sh.poff[pi];
-          const uint32_t pn = (pi + 1 < dt ? sh.poff[pi + 1] : pairs) - p0;
-          const uint32_t j =
-              block_pick<BLOCK>(pn, [&](uint32_t jj) { return ld_u64(&praw[p0 + jj]); }, sh.ring_b[pi], st, sh);
-          if (j == kUnseen) {
-            ok = false;
-          } else {
-            w_next = uniform_u64(ld_u64(&praw[p0 + j]));
-            v = g.in_idx[sh.rrs[pi] + j];
-            if (tid == 0 && hbase + 1 < g.stage_cap) g.stage[hbase + 1] = caller_id(g, v);
-            written = 2;
-            dv = d - 2;
-          }
+    // (a deferred sample stages nothing here)
+    if (!deferred) {
+      // backtrack: from v = t, pick a predecessor w at level(v) - 1 with
+      // probability sigma'_w / W, scanning in-neighbours in ascending order,
+      // until level 1.  Workgroup wide (block_pick); steps through unproduced
+      // levels (shortcut 2 or 3) take their weights from the ring sums and the
+      // stored pair counts.
+      const uint32_t len = (d != kUnseen && d >= 2) ? d - 1 : 0u;
+      // the place of the hyperedge in the staging area: only thread 0 writes
+      // there.  It takes places from a chunk of its workgroup's (one add on
+      // the shared word per chunk); a hyperedge of more than half a chunk
+      // gets its own.
+      uint64_t hbase = 0;
+      if (tid == 0 && len) {
+        if (len <= st_left) {
+          hbase = st_pos;
+          st_pos += len;
+          st_left -= len;
+        } else if (2 * len > a.stage_chunk) {
+          hbase = atomicAdd(reinterpret_cast<unsigned long long*>(a.stage_used), static_cast<unsigned long long>(len));
+        } else {
+          hbase = atomicAdd(reinterpret_cast<unsigned long long*>(a.stage_used),
+                            static_cast<unsigned long long>(a.stage_chunk));
+          st_pos = hbase + len;
+          st_left = a.stage_chunk - len;
         }
       }
-    } else if (dv && shortcut) {
-      // shortcut without the ring cache (t has many in-neighbours): the
-      // first step recomputes raw_w, on wave 0 (every thread draws, so the
-      // streams stay identical for the next steps)
-      const uint64_t r = bounded(st, w_short);
-      if (wid == 0) {
-        uint64_t acc = 0;
-        uint32_t pick = kUnseen;
-        for (uint32_t e = tb; e < te; ++e) {
-          const uint32_t w = g.in_idx[e];
-          const uint32_t ub = g.in_ptr[w], ue = g.in_ptr[w + 1];
-          uint64_t x = 0;
-          for (uint32_t f = ub + lane; f < ue; f += kWave) x += bits.count(g.in_idx[f]);
-          acc += wave_sum_u64(x);
-          if (acc > r) {
-            pick = w;
+      n_entries += len;
+      uint32_t v = t, dv = len ? d : 0u, written = 0;   // no backtrack when t is unreachable or adjacent
+      uint32_t vb = tb, ve = te;                        // v's in-row
+      // W of the next step when known without a summing pass: the raw count
+      // of v, i.e. the sum of its predecessors' counts (a ring sum or stored
+      // pair count after a shortcut step; sigma'_v itself when v was claimed
+      // at a level whose counts were not shifted)
+      uint64_t w_next = 0;
+      bool ok = true;
+      auto stage = [&]() {   // v is the next node of the hyperedge
+        if (tid == 0 && hbase + written < a.stage_cap) a.stage[hbase + written] = g.orig_of ? g.orig_of[v] : v;
+        ++written;
+        --dv;
+      };
+      // the chosen entry's node and in-row, from the thread that holds it
+      auto leave = [&](uint32_t w, uint64_t weight) {
+        sh.pk[1] = w;
+        sh.pk_weight = weight;
+      };
+      uint32_t p0 = 0, p1 = 0;   // rows of a step by recounting
+      if (dv && shortcut && rings) {
+        // step from t through level d-1: weights ring (the last test's) of
+        // t's in-neighbours, in ascending order
+        const uint32_t pi = block_pick<BLOCK>(
+            dt,
+            [&](uint32_t j0, uint32_t cnt, uint64_t* x) {
+              for (uint32_t k = 0; k < kPickPer; ++k)
+                if (k < cnt) x[k] = sh.ring[j0 + k];
+            },
+            [&](uint32_t, uint32_t j, uint64_t weight) { leave(g.in_idx[tb + j], weight); }, 0, st, sh, co);
+        if (pi == kUnseen) {
+          ok = false;
+        } else {
+          v = uniform_u32(sh.pk[1]);
+          w_next = uniform_u64(sh.pk_weight);
+          p0 = sh.poff[pi];
+          const uint32_t pn = (pi + 1 < dt ? sh.poff[pi + 1] : pairs) - p0;
+          vb = sh.rrs[pi] + p0;
+          ve = vb + pn;
+          stage();
+          if (shortcut == 3) p1 = p0 + pn;
+        }
+      } else if (dv && shortcut) {
+        p1 = dt;
+        w_next = uniform_u64(sh.ring[0]);
+      }
+      if (p1) {
+        // step through level L+1 to the row's owner: from w (level L+2) to a
+        // u of the pairs (w, u), rows [p0, p1), or from a t without the ring
+        // cache to one of its in-neighbours.  The weights, the owners' raw
+        // counts, are counted again (the tests kept only their sum).
+        const uint64_t r = bounded(st, w_next);
+        uint64_t run = 0;
+        ok = false;
+        for (uint32_t cb = p0; cb < p1; cb += BLOCK) {
+          uint32_t r0, dg;
+          row_of(rings, cb + tid, p1, &r0, &dg);
+          const uint64_t raw = raw_counts_chunk<BLOCK>(g.in_idx, vis, r0, dg, sh, co, sp);
+          uint64_t tot;
+          const uint64_t excl = run + co.scan(raw, &tot);
+          if (run + tot > r) {
+            if (excl <= r && r < excl + raw) {
+              sh.pk[2] = r0;
+              sh.pk[3] = r0 + dg;
+              leave(rings ? wg_ld_u32(&pu[cb + tid]) : g.in_idx[tb + cb + tid], raw);
+            }
+            ok = true;
             break;
           }
+          run += tot;
         }
-        if (lane == 0) sh.pick = pick;
+        __syncthreads();
+        if (ok) {
+          v = uniform_u32(sh.pk[1]);
+          vb = uniform_u32(sh.pk[2]);
+          ve = uniform_u32(sh.pk[3]);
+          w_next = uniform_u64(sh.pk_weight);
+          stage();
+        }
+      }
+      // steps through produced levels.  The predecessors of v, at level
+      // want + 1, are its visited in-neighbours placed before that level's
+      // start: a visited in-neighbour is on level want or above.
+      uint32_t start = le;   // of v's level (t's own is not produced past L)
+      while (ok && dv >= 2) {
+        const uint32_t want = dv - 1;
+        const uint32_t below = want == L ? lb : last_start(starts, start);
+        // a known W spares rows longer than one pick round their summing pass
+        const uint64_t wk = ve - vb > uint32_t(BLOCK) * kPickPer ? w_next : 0ull;
+        uint32_t w[kPickPer], wb[kPickPer], we[kPickPer];
+        const uint32_t j = block_pick<BLOCK>(
+            ve - vb,
+            [&](uint32_t j0, uint32_t cnt, uint64_t* x) {
+              uint32_t p[kPickPer];
+#pragma unroll
+              for (uint32_t k = 0; k < kPickPer; ++k) w[k] = k < cnt ? g.in_idx[vb + j0 + k] : 0u;
+#pragma unroll
+              for (uint32_t k = 0; k < kPickPer; ++k) {
+                p[k] = kUnseen;
+                wb[k] = we[k] = 0;
+                if (k < cnt && vis.maybe(w[k])) {   // all three loads in flight together
+                  p[k] = vis.place(w[k]);
+                  wb[k] = g.in_ptr[w[k]];
+                  we[k] = g.in_ptr[w[k] + 1];
+                }
+              }
+#pragma unroll
+              for (uint32_t k = 0; k < kPickPer; ++k)
+                if (p[k] < start) x[k] = wg_ld_u64(&vis.sig[p[k]]);
+            },
+            [&](uint32_t k, uint32_t, uint64_t weight) {
+#pragma unroll
+              for (uint32_t i = 0; i < kPickPer; ++i)
+                if (i == k) {
+                  sh.pk[2] = wb[i];
+                  sh.pk[3] = we[i];
+                  leave(w[i], weight);
+                }
+            },
+            wk, st, sh, co);
+        if (j == kUnseen) {
+          ok = false;
+          break;
+        }
+        v = uniform_u32(sh.pk[1]);
+        vb = uniform_u32(sh.pk[2]);
+        ve = uniform_u32(sh.pk[3]);
+        start = below;
+        w_next = want < 64 && !((shifted >> want) & 1ull) ? uniform_u64(sh.pk_weight) : 0ull;
+        stage();
+      }
+      if (tid == 0) {
+        if (!ok) atomicOr(a.flags, kErrBacktrack);
+        a.stage_pos[idx] = hbase;
+        a.he_len[idx] = len;
+        if (a.st_out) {
+          a.st_out[2 * size_t(idx)] = s0;
+          a.st_out[2 * size_t(idx) + 1] = t0;
+        }
+        if (a.dist_out) a.dist_out[idx] = d;
+      }
+    }
+    // the map keeps this BFS's stamp (older than any later one); only the
+    // dynamic bitmap is cleared.  The barrier ends every use of the item's
+    // LDS state.
+    __syncthreads();
+    const uint32_t nv = BLOCK == kWave ? qn : uniform_u32(sh.qlen);
+    n_nodes += nv;
+    if (LDS_BITS)
+      for (uint32_t i = tid; i < nv; i += BLOCK) dyn_bits[wg_ld_u32(&q[i]) >> 5] = 0;
+    if (--in_hand) {
+      ++idx;
+    } else {
+      const uint32_t take = (a.count - idx) / kTakeWhile > gridDim.x ? kTake : 1u;
+      if (tid == 0) {
+        const uint64_t next = gridDim.x + atomicAdd(reinterpret_cast<unsigned long long*>(a.work),
+                                                    static_cast<unsigned long long>(take));
+        sh.next = next < a.count ? static_cast<uint32_t>(next) : a.count;
       }
       __syncthreads();
-      const uint32_t pick = uniform_u32(sh.pick);
-      if (pick == kUnseen) {
-        ok = false;
-      } else {
-        v = pick;
-        if (tid == 0 && hbase < g.stage_cap) g.stage[hbase] = caller_id(g, v);
-        written = 1;
-        dv = d - 1;
-      }
-    }
-    while (ok && dv >= 2) {
-      const uint32_t want = dv - 1;
-      const uint32_t vb = g.in_ptr[v], ve = g.in_ptr[v + 1];
-      // a known W spares rows longer than one pick round their summing pass
-      uint64_t wk = w_next;
-      if (!wk && claimed_v && dv < 64 && !((shifted >> dv) & 1ull)) wk = ld_u64(sig_of(rec, v));
-      wk = ve - vb > uint32_t(BLOCK) * kPickPer ? uniform_u64(wk) : 0ull;
-      const uint32_t j = block_pick<BLOCK>(
-          ve - vb, [&](uint32_t jj) { return pred_weight(bits, rec, g.in_idx[vb + jj], want); }, wk, st, sh);
-      if (j == kUnseen) {
-        ok = false;
-        break;
-      }
-      w_next = 0;
-      claimed_v = true;   // predecessors lie on produced levels
-      v = g.in_idx[vb + j];
-      if (tid == 0 && hbase + written < g.stage_cap) g.stage[hbase + written] = caller_id(g, v);
-      ++written;
-      --dv;
-    }
-    if (tid == 0) {
-      if (!ok) atomicOr(g.flags, kErrBacktrack);
-      g.stage_pos[idx] = hbase;
-      g.he_len[idx] = len;
-      if (g.st_out) {
-        g.st_out[2 * size_t(idx)] = s0;
-        g.st_out[2 * size_t(idx) + 1] = t0;
-      }
-      if (g.dist_out) g.dist_out[idx] = d;
+      idx = uniform_u32(sh.next);
+      in_hand = take;
     }
     __syncthreads();
-    // the records keep this BFS's stamp (older than any later one); only
-    // the LDS bitmap is cleared
-    const uint32_t nv = uniform_u32(sh.qlen);
-    n_nodes += nv;
-    if (LDS_BITS) {
-      for (uint32_t i = tid; i < nv; i += BLOCK) dyn_bits[ld_u32(&q[i]) >> 5] = 0;
-      __syncthreads();
-    }
   }
   // (a workgroup whose targets all lacked in-neighbours scanned no arc but
   // still gave every source a level)
   if (tid == 0 && a.stats && (n_arcs || n_nodes)) {
     atomicAdd(reinterpret_cast<unsigned long long*>(&a.stats[0]), static_cast<unsigned long long>(n_arcs));
     atomicAdd(reinterpret_cast<unsigned long long*>(&a.stats[1]), static_cast<unsigned long long>(n_nodes));
+    if (n_entries)
+      atomicAdd(reinterpret_cast<unsigned long long*>(a.entries), static_cast<unsigned long long>(n_entries));
   }
 }
 
@@ -1043,12 +1368,12 @@ __global__ void k_stage_gather(uint32_t count, const uint64_t* stage_pos, const 
 // Launch wrappers for the host side of the sampler (sample_launch.hip).
 hipError_t sample_kernel_occupancy(int block, bool lds_bits, bool multi, size_t dyn_lds, int* per_cu) {
   if (lds_bits) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_sample_paths<kLdsBlock, kUnroll, true>),
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_sample_paths<kLdsBlock, true>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(dyn_lds));
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k_sample_paths<kLdsBlock, kUnroll, true>, kLdsBlock,
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k_sample_paths<kLdsBlock, true>, kLdsBlock,
                                                         dyn_lds);
   }
-#define CENTRA_OCC(B, M) hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k_sample_paths<B, kUnroll, false, M>, B, 0)
+#define CENTRA_OCC(B, M) hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k_sample_paths<B, false, M>, B, 0)
   switch (block) {
     case 512: return multi ? CENTRA_OCC(512, true) : CENTRA_OCC(512, false);
     case 256: return multi ? CENTRA_OCC(256, true) : CENTRA_OCC(256, false);
@@ -1063,10 +1388,10 @@ size_t sample_lds_variant_bytes() { return sizeof(SampleShared<kLdsBlock>); }
 void sample_kernel_launch(const SampleArgs& a, int block, bool lds_bits, bool multi, uint32_t grid, size_t dyn_lds,
                           hipStream_t s) {
   if (lds_bits) {
-    hipLaunchKernelGGL((k_sample_paths<kLdsBlock, kUnroll, true>), dim3(grid), dim3(kLdsBlock), dyn_lds, s, a);
+    hipLaunchKernelGGL((k_sample_paths<kLdsBlock, true>), dim3(grid), dim3(kLdsBlock), dyn_lds, s, a);
     return;
   }
-#define CENTRA_LAUNCH(B, M) hipLaunchKernelGGL((k_sample_paths<B, kUnroll, false, M>), dim3(grid), dim3(B), 0, s, a)
+#define CENTRA_LAUNCH(B, M) hipLaunchKernelGGL((k_sample_paths<B, false, M>), dim3(grid), dim3(B), 0, s, a)
   switch (block) {
     case 512:
       if (multi)
@@ -1105,14 +1430,24 @@ void sample_kernel_launch(const SampleArgs& a, int block, bool lds_bits, bool mu
 // tests), which give the same levels, normalised counts and predecessor
 // weights as the shortcuts do, then the same backtrack over the same word
 // stream, so the hyperedge is the one the workgroup kernel would stage.
-// The state is slot 0's records and queue (the launch that deferred the
-// sample has finished) under a stamp of its own.
+// The launch that deferred the samples has finished: their node records
+// {sigma', tag} lie in its slots' count arrays (cleared first), their queues
+// in its slots' queues.
 constexpr int kWideBlock = 256;
 constexpr unsigned kWideGrid = 2048;
 // a level is pulled when the unvisited nodes' in-arcs (plus a quarter of n
 // for reading every tag) are fewer than kPullRatio times the frontier's
 // out-arcs: a push scans them twice and claims with returning atomics
 constexpr uint64_t kPullRatio = 8;
+constexpr uint32_t kPullLane = 32;   // in-row entries a lane sums by itself in a pull
+
+// Record accessors: word 0 = sigma', word 1 = tag.  With base = stamp << 32
+// the tag of a node at level l of the current BFS is base + (kUnseen - l):
+// "claimed by this BFS" is tag >= base, "at level <= L" is
+// tag >= base + (kUnseen - L).
+__device__ __forceinline__ uint64_t* sig_of(uint64_t* rec, uint32_t v) { return rec + 2 * size_t(v); }
+__device__ __forceinline__ uint64_t* tag_of(uint64_t* rec, uint32_t v) { return rec + 2 * size_t(v) + 1; }
+__device__ __forceinline__ uint64_t level_tag(uint64_t base, uint32_t level) { return base + (kUnseen - level); }
 
 // ctl: [0] queue length, [1] largest raw count of the new level, [2] 1 if
 // t is on the new level, [3] out-arcs of the last level (the cost of
@@ -1121,7 +1456,7 @@ constexpr uint64_t kPullRatio = 8;
 // nodes given a level
 __global__ void k_wide_start(SampleArgs a, uint32_t idx, uint64_t base, uint64_t* ctl) {
   if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  WordStream st(a.seed, a.first + idx, a.instance, 0);
+  RolledWordStream st(a.seed, a.first + idx, a.instance, 0);
   const uint32_t s0 = static_cast<uint32_t>(bounded(st, a.n));
   const uint32_t tp = static_cast<uint32_t>(bounded(st, a.n - 1));
   const uint32_t t0 = tp + (tp >= s0 ? 1u : 0u);
@@ -1141,7 +1476,10 @@ __global__ void k_wide_start(SampleArgs a, uint32_t idx, uint64_t base, uint64_t
 }
 
 // Level nl - 1 = queue entries [lb, le) expanded by every workgroup, a
-// chunk of kWideBlock frontier nodes at a time: pass 0 claims the new
+// chunk of kWideBlock frontier nodes at a time, the arcs of a chunk shared by
+// the workgroups of a column of the grid (a few hubs make a narrow level of
+// millions of arcs, which a workgroup per chunk left to a handful: a flood of
+// R-MAT scale 20 took 4.7 ms): pass 0 claims the new
 // level's nodes (returning atomic max on the tag; the claimer zeroes the
 // count and appends the node, one queue atomic per wave), pass 1 adds each
 // frontier node's count to its new-level out-neighbours.
@@ -1169,9 +1507,9 @@ __global__ __launch_bounds__(kWideBlock) void k_wide_level(SampleArgs a, uint32_
     off[tid] = o;
     rs[tid] = r0;
     sg[tid] = sw;
-    arcs += total;
+    if (blockIdx.y == 0) arcs += total;
     __syncthreads();
-    for (uint32_t e0 = 0; e0 < total; e0 += kWideBlock) {   // uniform trip count
+    for (uint32_t e0 = blockIdx.y * kWideBlock; e0 < total; e0 += gridDim.y * kWideBlock) {   // uniform trip count
       const uint32_t e = e0 + tid;
       bool claimed = false;
       uint32_t v = 0;
@@ -1229,20 +1567,36 @@ __global__ __launch_bounds__(kWideBlock) void k_wide_pull(SampleArgs a, uint64_t
   const uint64_t n_pad = (uint64_t(a.n) + kWideBlock - 1) / kWideBlock * kWideBlock;   // uniform trip count
   for (uint64_t v0 = uint64_t(blockIdx.x) * kWideBlock; v0 < n_pad; v0 += uint64_t(gridDim.x) * kWideBlock) {
     const uint64_t v = v0 + threadIdx.x;
-    bool claimed = false;
+    uint32_t ib = 0, ie = 0;
     if (v < a.n && ld_u64(tag_of(a.rec, static_cast<uint32_t>(v))) < base) {
-      const uint32_t ib = a.in_ptr[v], ie = a.in_ptr[v + 1];
-      uint64_t raw = 0;
+      ib = a.in_ptr[v];
+      ie = a.in_ptr[v + 1];
+    }
+    arcs += ie - ib;
+    // a row of up to kPullLane entries by its own lane, a longer one by the
+    // wave (hub rows would otherwise hold the level: the wide BFSs of a 2.7M
+    // sample launch at directed R-MAT scale 22, 302 -> 158 ms)
+    uint64_t raw = 0;
+    if (ie - ib <= kPullLane)
       for (uint32_t e = ib; e < ie; ++e) {
         const uint32_t w = a.in_idx[e];
         if (ld_u64(tag_of(a.rec, w)) == tag_prev) raw += ld_u64(sig_of(a.rec, w));
       }
-      arcs += ie - ib;
-      if (raw) {
-        st_u64(sig_of(a.rec, static_cast<uint32_t>(v)), raw);
-        st_u64(tag_of(a.rec, static_cast<uint32_t>(v)), tag_new);
-        claimed = true;
+    for (uint64_t m = __ballot(ie - ib > kPullLane); m; m &= m - 1) {
+      const int l = __ffsll(static_cast<unsigned long long>(m)) - 1;
+      const uint32_t hb = lane_u32(ib, l), he = lane_u32(ie, l);
+      uint64_t x = 0;
+      for (uint32_t e = hb + lane; e < he; e += kWave) {
+        const uint32_t w = a.in_idx[e];
+        if (ld_u64(tag_of(a.rec, w)) == tag_prev) x += ld_u64(sig_of(a.rec, w));
       }
+      x = wave_sum_u64(x);
+      if (lane == l) raw = x;
+    }
+    const bool claimed = raw != 0;
+    if (claimed) {
+      st_u64(sig_of(a.rec, static_cast<uint32_t>(v)), raw);
+      st_u64(tag_of(a.rec, static_cast<uint32_t>(v)), tag_new);
     }
     const uint64_t m = __ballot(claimed);
     if (m) {
@@ -1302,18 +1656,19 @@ __global__ void k_wide_shift(SampleArgs a, uint32_t le, uint32_t ne, uint32_t sh
 // pair's words, then one bounded draw per step), staged the same way.
 __global__ __launch_bounds__(kWideBlock) void k_wide_backtrack(SampleArgs a, uint32_t idx, uint64_t base, uint32_t d) {
   __shared__ SampleShared<kWideBlock> sh;
+  Coll<kWideBlock> co{sh.red, 0};
   const int tid = threadIdx.x;
-  WordStream st(a.seed, a.first + idx, a.instance, 0);
+  RolledWordStream st(a.seed, a.first + idx, a.instance, 0);
   const uint32_t s0 = static_cast<uint32_t>(bounded(st, a.n));
   const uint32_t tp = static_cast<uint32_t>(bounded(st, a.n - 1));
   const uint32_t t0 = tp + (tp >= s0 ? 1u : 0u);
   const uint32_t t = a.new_of ? a.new_of[t0] : t0;
   const uint32_t len = (d != kUnseen && d >= 2) ? d - 1 : 0u;
-  if (tid == 0)
-    sh.base = len ? atomicAdd(reinterpret_cast<unsigned long long*>(a.stage_used), static_cast<unsigned long long>(len))
-                  : 0ull;
-  __syncthreads();
-  const uint64_t hbase = uniform_u64(sh.base);
+  uint64_t hbase = 0;   // thread 0 only
+  if (tid == 0 && len) {
+    hbase = atomicAdd(reinterpret_cast<unsigned long long*>(a.stage_used), static_cast<unsigned long long>(len));
+    atomicAdd(reinterpret_cast<unsigned long long*>(a.entries), static_cast<unsigned long long>(len));
+  }
   uint32_t v = t, dv = len ? d : 0u, written = 0;
   bool ok = true;
   while (dv >= 2) {
@@ -1322,13 +1677,16 @@ __global__ __launch_bounds__(kWideBlock) void k_wide_backtrack(SampleArgs a, uin
     const uint32_t vb = a.in_ptr[v], ve = a.in_ptr[v + 1];
     const uint32_t j = block_pick<kWideBlock>(
         ve - vb,
-        [&](uint32_t jj) {
-          const uint32_t w = a.in_idx[vb + jj];
-          const uint64_t tg = ld_u64(tag_of(a.rec, w));
-          const uint64_t c = ld_u64(sig_of(a.rec, w));
-          return tg == tag_want ? c : 0ull;
+        [&](uint32_t j0, uint32_t cnt, uint64_t* x) {
+          for (uint32_t k = 0; k < kPickPer; ++k) {
+            if (k >= cnt) continue;
+            const uint32_t w = a.in_idx[vb + j0 + k];
+            const uint64_t tg = ld_u64(tag_of(a.rec, w));
+            const uint64_t c = ld_u64(sig_of(a.rec, w));
+            x[k] = tg == tag_want ? c : 0ull;
+          }
         },
-        0, st, sh);
+        [](uint32_t, uint32_t, uint64_t) {}, 0, st, sh, co);
     if (j == kUnseen) {
       ok = false;
       break;
@@ -1350,9 +1708,10 @@ __global__ __launch_bounds__(kWideBlock) void k_wide_backtrack(SampleArgs a, uin
   }
 }
 
-int wide_samples(const SampleArgs& a_in, const uint32_t* idx, uint32_t n_items, uint64_t stamp0, uint64_t* ctl,
-                 uint64_t* host_ctl, uint64_t* arcs, hipStream_t s) {
-  // per sample j: slot j's records and queue, ctl + 8 j, stamp stamp0 + j
+int wide_samples(const SampleArgs& a_in, const uint32_t* idx, uint32_t n_items, uint64_t* ctl, uint64_t* host_ctl,
+                 uint64_t* arcs, hipStream_t s) {
+  // per sample j: records j of a_in.rec (cleared here), slot j's queue, ctl + 8 j
+  fill_u64(a_in.rec, 0, size_t(n_items) * 2 * a_in.slot_stride, s);
   struct Walk {
     SampleArgs a;
     uint64_t base, push_cost, visited_in;
@@ -1366,7 +1725,7 @@ int wide_samples(const SampleArgs& a_in, const uint32_t* idx, uint32_t n_items, 
     x.a.rec = a_in.rec + 2 * size_t(j) * a_in.slot_stride;
     x.a.q = a_in.q + size_t(j) * a_in.slot_stride;
     x.a.stats = ctl + 8 * size_t(j) + 6;   // its arcs and nodes, apart from the workgroup kernel's
-    x.base = (stamp0 + j) << 32;
+    x.base = uint64_t(1) << 32;
     hipLaunchKernelGGL(k_wide_start, dim3(1), dim3(64), 0, s, x.a, idx[j], x.base, ctl + 8 * size_t(j));
   }
   const size_t ctl_bytes = size_t(n_items) * 8 * 8;
@@ -1398,9 +1757,13 @@ int wide_samples(const SampleArgs& a_in, const uint32_t* idx, uint32_t n_items, 
       if (pull_cost < kPullRatio * x.push_cost) {
         hipLaunchKernelGGL(k_wide_pull, dim3(kWideGrid), dim3(kWideBlock), 0, s, x.a, x.base, nl, c);
       } else {
-        const unsigned grid = std::min<uint64_t>(kWideGrid, (uint64_t(x.le - x.lb) + kWideBlock - 1) / kWideBlock);
-        hipLaunchKernelGGL(k_wide_level<0>, dim3(grid), dim3(kWideBlock), 0, s, x.a, x.lb, x.le, x.base, nl, c);
-        hipLaunchKernelGGL(k_wide_level<1>, dim3(grid), dim3(kWideBlock), 0, s, x.a, x.lb, x.le, x.base, nl, c);
+        const unsigned chunks = std::min<uint64_t>(kWideGrid, (uint64_t(x.le - x.lb) + kWideBlock - 1) / kWideBlock);
+        // as many workgroups per chunk as the level's arcs keep busy
+        const uint64_t rounds = x.push_cost / (uint64_t(chunks) * kWideBlock) + 1;
+        const unsigned share = std::min<uint64_t>(std::max(1u, kWideGrid / chunks), rounds);
+        const dim3 grid(chunks, share);
+        hipLaunchKernelGGL(k_wide_level<0>, grid, dim3(kWideBlock), 0, s, x.a, x.lb, x.le, x.base, nl, c);
+        hipLaunchKernelGGL(k_wide_level<1>, grid, dim3(kWideBlock), 0, s, x.a, x.lb, x.le, x.base, nl, c);
       }
       hipLaunchKernelGGL(k_wide_close, dim3(kWideGrid), dim3(kWideBlock), 0, s, x.a, x.le, x.base, nl, x.t, c);
     }

@@ -9,7 +9,10 @@ namespace centra {
 
 constexpr uint32_t kPairMax = 65536;   // pairs of the ring tests per slot
 constexpr int kLdsBlock = 1024;        // threads of the LDS-bitmap variant
-constexpr int kUnroll = 8;             // arcs per thread per expansion round
+constexpr uint32_t kStageChunk = 256;   // staging entries a workgroup reserves at once (at most)
+
+// Words of a slot's bitmap of level starts.
+__host__ __device__ constexpr size_t start_words(uint64_t n) { return n / 64 + 1; }
 
 // One graph's share of a fused launch over several sample pools: the
 // graph's arrays and counts, the stream of its samples, and the global
@@ -41,16 +44,20 @@ struct SampleArgs {
   uint32_t instance;
   uint64_t first;
   uint32_t count;
-  uint64_t* rec;      // slots * n records of two words: sigma', tag
-  uint32_t* q;        // slots * n
-  uint64_t* praw;     // slots * kPairMax: raw count of each pair's u from the last cone test
+  uint64_t* map;      // slots * n: stamp << 32 | place of a visited node
+  uint64_t* sig;      // slots * n: counts of the visited nodes, by place
+  uint32_t* q;        // slots * n: the visited nodes, by place
+  uint64_t* starts;   // slots * start_words(n): bitmap of the places where levels start
+  uint64_t* rec;      // device-wide BFS: records of two words (sigma', tag), n per sample
   uint32_t* pinfo;    // slots * 3 * kPairMax: per pair its u, in_ptr[u] and in-degree of u
   uint32_t stamp0;    // stamp of work item 0; item i has stamp0 + i
   uint32_t bit_words;
-  uint32_t* work;     // work counter
+  uint64_t* work;     // work counter: items taken beyond each workgroup's first
   uint32_t* stage;    // staging for hyperedge nodes
   uint64_t stage_cap;
-  uint64_t* stage_used;
+  uint64_t* stage_used;  // entries reserved
+  uint32_t stage_chunk;  // reserved by a workgroup at once (0: each hyperedge by itself)
+  uint64_t* entries;     // hyperedge entries staged (accumulated)
   uint64_t* stage_pos;   // per sample
   uint32_t* he_len;      // per sample
   uint32_t* st_out;      // optional
@@ -85,11 +92,12 @@ void sample_kernel_launch(const SampleArgs& a, int block, bool lds_bits, bool mu
 // sample with the whole GPU (claims and counts pushed, or the level pulled),
 // then one synchronisation reads them all; then each backtrack by one
 // workgroup, the hyperedges staged like the workgroup kernel's.  Sample j
-// uses slot j's records and queue (n_items <= slots) with stamp stamp0 + j
-// and ctl[8 j .. 8 j + 8) of device memory (host_ctl: as many words on
-// the host).  *arcs receives the CSR entries they scanned.
-int wide_samples(const SampleArgs& a, const uint32_t* idx, uint32_t n_items, uint64_t stamp0, uint64_t* ctl,
-                 uint64_t* host_ctl, uint64_t* arcs, hipStream_t s);
+// uses the slot_stride records from a.rec + 2 j slot_stride on (cleared
+// first), slot j's queue (n_items <= slots) and ctl[8 j .. 8 j + 8) of
+// device memory (host_ctl: as many words on the host).  *arcs receives the
+// CSR entries they scanned.
+int wide_samples(const SampleArgs& a, const uint32_t* idx, uint32_t n_items, uint64_t* ctl, uint64_t* host_ctl,
+                 uint64_t* arcs, hipStream_t s);
 void stage_gather_launch(uint32_t count, const uint64_t* stage_pos, const uint32_t* he_len, const uint64_t* rel_off,
                          uint64_t base, const uint32_t* stage, uint64_t* he_off, uint32_t* he_nodes, hipStream_t s);
 

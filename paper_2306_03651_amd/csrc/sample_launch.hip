@@ -17,24 +17,50 @@
 namespace centra {
 
 // Launch shapes: the LDS-bitmap variant runs one 1024-thread workgroup per
-// CU (the bitmap takes most of the LDS); the other variants (Bloom filter in
-// LDS, visited state in the HBM records) run several workgroups of 64 to
-// 512 threads per CU.
+// CU (the bitmap takes most of the LDS); the other variants (a 2 KB visited
+// filter in LDS) run several workgroups of 64 to 512 threads per CU.
 constexpr uint32_t kMaxSlots = 8192;
+
+// Byte offsets of a launch's counters in work_ctr: the two words that every
+// workgroup adds to on lines of their own; then arcs, nodes, entries, and
+// the number of deferred items.
+constexpr size_t kCtrWork = 0, kCtrUsed = 128, kCtrStats = 256, kCtrBytes = 512;
 
 struct SamplePlan {
   bool lds_bits;
-  int block;         // workgroup size of the Bloom-filter variants
+  int block;         // workgroup size of the LDS-filter variants
   uint32_t bit_words;
   size_t dyn_lds;
   uint32_t resident;   // workgroups resident at once = BFS slots
 };
 
-// Variant choice.  Default: the Bloom-filter kernel with 128-thread
-// workgroups (many concurrent BFSs per CU hide the latency of the short,
-// dependent steps of each BFS).  CENTRA_SAMPLER_VARIANT selects another:
-// "lds" (LDS bitmap, 1024 threads, when the bitmap fits), "hbm512",
-// "hbm256", "hbm128", "hbm64" (Bloom filter, that many threads).
+// Bytes of one slot's state: per node the map's word, the count and the
+// queue entry; the bitmap of level starts; and the pair arrays.
+static size_t slot_bytes(uint32_t n) { return size_t(n) * (8 + 8 + 4) + start_words(n) * 8 + kPairMax * 12; }
+
+// Slot state takes at most half of the device's memory (96 GiB if the size
+// cannot be queried; asked once per context); the context budget, when set,
+// limits it further.
+static size_t slot_mem_cap(centra_ctx* ctx) {
+  if (ctx->slot_cap) return ctx->slot_cap;
+  size_t free_b = 0, total_b = 0;
+  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || total_b == 0) {
+    (void)hipGetLastError();
+    total_b = size_t(192) << 30;
+  }
+  return ctx->slot_cap = total_b / 2;
+}
+
+// Variant choice.  Default: one wave per BFS (most BFSs are short chains of
+// dependent steps; a wave needs no barrier, and 4,096 of them hide each
+// other's trips to memory: BA n = 10^6, 400,000 samples, 15.1 ms, against
+// 19.4 ms with 128 threads).  Where the memory cap or the budget leaves fewer
+// slots than fill the device, more threads per BFS do: 128 below 3,072 slots,
+// 256 below 2,048 (directed R-MAT scale 22, 1,524 slots, 2.7M samples a
+// launch: 405 ms with 64 threads, 321 with 128, 298 with 256).
+// CENTRA_SAMPLER_VARIANT selects another: "lds" (exact LDS bitmap, 1024
+// threads, when the bitmap fits), "hbm512", "hbm256", "hbm128", "hbm64" (LDS
+// filter, that many threads).
 static SamplePlan plan_for(centra_ctx* ctx, uint32_t n, int block_override = 0) {
   SamplePlan p{};
   p.bit_words = (n + 31) / 32;
@@ -45,13 +71,16 @@ static SamplePlan plan_for(centra_ctx* ctx, uint32_t n, int block_override = 0) 
     cus = 256;
   const size_t dyn = size_t(p.bit_words) * 4;
   const char* env = getenv("CENTRA_SAMPLER_VARIANT");
-  const char* v = env ? env : "hbm128";
-  p.block = 128;
+  const size_t cap = slot_mem_cap(ctx);
+  const size_t most = (ctx->budget && ctx->budget < cap ? ctx->budget : cap) / slot_bytes(n);
+  const char* v = env ? env : "";
+  p.block = most < 2048 ? 256 : most < 3072 ? 128 : 64;
+  if (!strcmp(v, "hbm64")) p.block = 64;
   if (!strcmp(v, "hbm512")) p.block = 512;
   if (!strcmp(v, "hbm256")) p.block = 256;
-  if (!strcmp(v, "hbm64")) p.block = 64;
+  if (!strcmp(v, "hbm128")) p.block = 128;
   p.lds_bits = !strcmp(v, "lds") && sample_lds_variant_bytes() + dyn <= size_t(max_lds);
-  if (block_override) {   // fused launches: a Bloom-filter variant chosen by the caller
+  if (block_override) {   // fused launches: an LDS-filter variant chosen by the caller
     p.block = block_override;
     p.lds_bits = false;
   }
@@ -65,24 +94,12 @@ static SamplePlan plan_for(centra_ctx* ctx, uint32_t n, int block_override = 0) 
   return p;
 }
 
-// Slot state takes at most half of the device's memory (96 GiB if the size
-// cannot be queried); the context budget, when set, limits it further.
-static size_t slot_mem_cap() {
-  size_t free_b = 0, total_b = 0;
-  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || total_b == 0) {
-    (void)hipGetLastError();
-    return size_t(96) << 30;
-  }
-  return total_b / 2;
-}
-
 static int ensure_slots(centra_ctx* ctx, uint32_t gn, uint32_t want, hipStream_t s, bool* fresh) {
   *fresh = false;
-  const size_t cap_bytes = slot_mem_cap();
+  const size_t cap_bytes = slot_mem_cap(ctx);
   {
     // never ask for more slots than the cap holds
-    const size_t per = size_t(gn) * (16 + 4) + kPairMax * (8 + 12);
-    const size_t most = cap_bytes / (per ? per : 1);
+    const size_t most = cap_bytes / slot_bytes(gn);
     if (want > most) want = most ? static_cast<uint32_t>(most) : 1u;
   }
   if (ctx->slots >= want && ctx->slot_n >= gn) return CENTRA_OK;
@@ -91,34 +108,35 @@ static int ensure_slots(centra_ctx* ctx, uint32_t gn, uint32_t want, hipStream_t
   // state (and its zero fill) to the memory cap after one large graph
   uint32_t slots = want;
   const uint32_t n = gn;
-  const size_t per_slot = size_t(n) * (16 + 4) + kPairMax * (8 + 12);
+  const size_t per_slot = slot_bytes(n);
+  DevBuf* bufs[] = {&ctx->slot_map, &ctx->slot_sig, &ctx->slot_q, &ctx->slot_starts, &ctx->slot_pinfo};
   // at most the cap of slot state (or the budget, if smaller)
   if (size_t(slots) * per_slot > cap_bytes) slots = static_cast<uint32_t>(cap_bytes / per_slot);
   if (slots == 0) slots = 1;
   // shrink the slot count if the budget cannot hold all of them
+  size_t have = 0;
+  for (DevBuf* b : bufs) have += b->bytes;
   for (;;) {
     const size_t need = size_t(slots) * per_slot;
-    const size_t have = ctx->slot_rec.bytes + ctx->slot_q.bytes + ctx->slot_praw.bytes + ctx->slot_pinfo.bytes;
     if (!ctx->budget || ctx->allocated - have + need <= ctx->budget || slots <= 1) break;
     slots /= 2;
   }
   int rc;
   for (;;) {   // halve the slot count while the device cannot hold the state
-    release(ctx, ctx->slot_rec);
-    release(ctx, ctx->slot_praw);
-    release(ctx, ctx->slot_pinfo);
-    release(ctx, ctx->slot_q);
+    for (DevBuf* b : bufs) release(ctx, *b);
     ctx->slots = 0;
     ctx->slot_n = 0;
-    rc = ensure(ctx, ctx->slot_rec, size_t(slots) * n * 16, false, s);
-    if (!rc) rc = ensure(ctx, ctx->slot_praw, size_t(slots) * kPairMax * 8, false, s);
+    rc = ensure(ctx, ctx->slot_map, size_t(slots) * n * 8, false, s);
+    // (two slots' counts at least: one sample's records of the device-wide BFS)
+    if (!rc) rc = ensure(ctx, ctx->slot_sig, size_t(slots < 2 ? 2 : slots) * n * 8, false, s);
     if (!rc) rc = ensure(ctx, ctx->slot_pinfo, size_t(slots) * kPairMax * 12, false, s);
     if (!rc) rc = ensure(ctx, ctx->slot_q, size_t(slots) * n * 4, false, s);
+    if (!rc) rc = ensure(ctx, ctx->slot_starts, size_t(slots) * start_words(n) * 8, false, s);
     if (rc != CENTRA_ENOMEM || slots <= 64) break;
     slots /= 2;
   }
   if (rc) return rc;
-  fill_u64(static_cast<uint64_t*>(ctx->slot_rec.ptr), 0, size_t(slots) * n * 2, s);   // stamp 0: never claimed
+  fill_u64(static_cast<uint64_t*>(ctx->slot_map.ptr), 0, size_t(slots) * n, s);   // stamp 0: never claimed
   CENTRA_HIP(ctx, hipGetLastError());
   ctx->slots = slots;
   ctx->slot_n = n;
@@ -126,28 +144,18 @@ static int ensure_slots(centra_ctx* ctx, uint32_t gn, uint32_t want, hipStream_t
   return CENTRA_OK;
 }
 
-// Placement of the slot records.  How fast the sampler runs depends on
-// where the allocator put the pages of the per-BFS records: the same launch
-// on BA 10^6 takes anywhere from 51 to 61 ms from one allocation of them to
-// the next, the same within one allocation to 0.5%, and unchanged when the
-// queues or the graph are allocated again.  A short launch ranks
-// allocations as the full one does, so fresh records of at least
-// kPlaceMinBytes are chosen among kPlaceCandidates allocations by timing
-// the batch's first kPlaceProbe work items on each (second of two launches;
-// results discarded, stamps used up as by any launch).  It runs for the
-// context's first large slot state only (a context that re-allocates as
-// its graphs change size would pay the search each time).  The search holds
-// two record arrays at a time and stops early if the budget or the device
-// cannot, or once a step takes more than kPlaceStepMs of wall time (slow
-// probes, or freed memory the device must clear first);
-// CENTRA_SLOT_SEARCH=0 turns it off.  It synchronises the stream,
-// so stream-ordered launches skip it.
 // Wide samples: a BFS about to expand a level of more than kWideNodes
-// nodes, or past kWideArcs scanned entries, is left to the device-wide BFS
-// (wide_sample in sample.hip); at most kWideCap per launch (the rest finish
-// on their workgroups).
+// nodes, or past the launch's scan budget, is left to the device-wide BFS
+// (wide_samples in sample.hip); at most kWideCap per launch (the rest finish
+// on their workgroups).  The budget is what a workgroup may expect to scan in
+// the whole launch (kWideArcsPerItem entries per item of its share): a longer
+// BFS would hold the launch after the others have ended, while a shorter one
+// costs less on its workgroup than the whole GPU's time.  (Directed R-MAT
+// scale 20, 200,000 samples: one BFS of 2.3 million entries, 105 ms on its
+// wave, held a launch whose other samples took 6 ms.)
 constexpr uint32_t kWideNodes = 65536;
-constexpr uint64_t kWideArcs = uint64_t(1) << 21;   // about 30 ms of one workgroup's scanning
+constexpr uint64_t kWideArcsPerItem = 4096;
+constexpr uint64_t kWideArcsMin = uint64_t(1) << 17, kWideArcsMax = uint64_t(1) << 21;
 constexpr uint32_t kWideCap = 4096;
 constexpr uint32_t kWideGroup = 64;   // deferred samples advanced together
 
@@ -156,24 +164,38 @@ static bool wide_enabled() {
   return !(e && !strcmp(e, "0"));
 }
 
-// Turns deferral on in `a` (its list in ctx->wide_ws, its counter the u32
-// at byte 32 of work_ctr) and clears the counter.
-static int defer_args(centra_ctx* ctx, SampleArgs& a, hipStream_t s) {
+// Turns deferral on in `a` (its list in ctx->wide_ws, its counter the
+// word after the statistics in work_ctr, cleared with them).
+static int defer_args(centra_ctx* ctx, SampleArgs& a, uint32_t grid, hipStream_t s) {
   int rc;
   if ((rc = ensure(ctx, ctx->wide_ws, size_t(kWideGroup) * 64 + size_t(kWideCap) * 4, false, s))) return rc;
   a.defer_nodes = kWideNodes;
-  a.defer_arcs = kWideArcs;
+  a.defer_arcs = std::min(kWideArcsMax, std::max(kWideArcsMin, a.count / grid * kWideArcsPerItem));
   if (const char* e = getenv("CENTRA_WIDE_NODES")) {   // tests: a lower threshold
     const long v = atol(e);
     if (v >= 1 && v <= 0x7FFFFFFFl) a.defer_nodes = static_cast<uint32_t>(v);
   }
   a.defer_cap = kWideCap;
   a.defer_list = reinterpret_cast<uint32_t*>(static_cast<char*>(ctx->wide_ws.ptr) + size_t(kWideGroup) * 64);
-  a.defer_count = reinterpret_cast<uint32_t*>(static_cast<char*>(ctx->work_ctr.ptr) + 32);
-  fill_u64(reinterpret_cast<uint64_t*>(a.defer_count), 0, 1, s);
+  a.defer_count = reinterpret_cast<uint32_t*>(static_cast<char*>(ctx->work_ctr.ptr) + kCtrStats + 24);
   return CENTRA_OK;
 }
 
+// Placement of the slot maps.  How fast the sampler runs depends on where
+// the allocator put the pages of the per-BFS node maps: the same launch on
+// BA 10^6 varies from one allocation of them to the next (by up to 18% when
+// they were 16-byte records), hardly within one, and not when the queues or
+// the graph are allocated again.  A short launch ranks allocations as the
+// full one does, so fresh maps of at least kPlaceMinBytes are chosen among
+// kPlaceCandidates allocations by timing the batch's first kPlaceProbe work
+// items on each (second of two launches; results discarded, stamps used up
+// as by any launch).  It runs for the context's first large slot state only
+// (a context that re-allocates as its graphs change size would pay the
+// search each time).  The search holds two map arrays at a time and stops
+// early if the budget or the device cannot, or once a step takes more than
+// kPlaceStepMs of wall time (slow probes, or freed memory the device must
+// clear first); CENTRA_SLOT_SEARCH=0 turns it off.  It synchronises the
+// stream, so stream-ordered launches skip it.
 constexpr int kPlaceCandidates = 4;
 constexpr double kPlaceStepMs = 60.0;   // wall time of one step (allocation, clear, two probes)
 constexpr uint32_t kPlaceProbe = 65536;
@@ -186,24 +208,30 @@ static bool slot_search_enabled() {
 
 // Sets the per-launch fields of `a` for `count` work items on the current
 // slot state and staging area (stage_cap entries).
-static void launch_args(centra_ctx* ctx, SampleArgs& a, const SamplePlan& plan, uint32_t count, uint64_t stage_cap) {
+static void launch_args(centra_ctx* ctx, SampleArgs& a, const SamplePlan& plan, uint32_t count, uint64_t stage_cap,
+                        uint32_t stage_chunk) {
   a.stamp0 = ctx->stamp_next;
   ctx->stamp_next += count;
   a.count = count;
   a.slot_stride = ctx->slot_n;
-  a.rec = static_cast<uint64_t*>(ctx->slot_rec.ptr);
+  a.map = static_cast<uint64_t*>(ctx->slot_map.ptr);
+  a.sig = static_cast<uint64_t*>(ctx->slot_sig.ptr);
   a.q = static_cast<uint32_t*>(ctx->slot_q.ptr);
-  a.praw = static_cast<uint64_t*>(ctx->slot_praw.ptr);
+  a.starts = static_cast<uint64_t*>(ctx->slot_starts.ptr);
+  a.rec = a.sig;   // after the launch, for the device-wide BFS
   a.pinfo = static_cast<uint32_t*>(ctx->slot_pinfo.ptr);
   a.bit_words = plan.bit_words;
-  a.work = static_cast<uint32_t*>(ctx->work_ctr.ptr);
+  char* ctr = static_cast<char*>(ctx->work_ctr.ptr);
+  a.work = reinterpret_cast<uint64_t*>(ctr + kCtrWork);
+  a.stats = reinterpret_cast<uint64_t*>(ctr + kCtrStats);
+  a.entries = a.stats + 2;
+  a.stage_chunk = stage_chunk;
   a.stage = static_cast<uint32_t*>(ctx->stage_nodes.ptr);
   a.stage_cap = stage_cap;
-  a.stage_used = reinterpret_cast<uint64_t*>(static_cast<char*>(ctx->work_ctr.ptr) + 8);
+  a.stage_used = reinterpret_cast<uint64_t*>(ctr + kCtrUsed);
   a.stage_pos = static_cast<uint64_t*>(ctx->stage_pos.ptr);
   a.he_len = static_cast<uint32_t*>(ctx->stage_len.ptr);
   a.flags = ctx->d_flags;
-  a.stats = reinterpret_cast<uint64_t*>(static_cast<char*>(ctx->work_ctr.ptr) + 16);
   a.defer_nodes = 0;
   a.defer_arcs = 0;
   a.defer_cap = 0;
@@ -212,12 +240,12 @@ static void launch_args(centra_ctx* ctx, SampleArgs& a, const SamplePlan& plan, 
 }
 
 // Stamps: a launch numbers its work items stamp_next, stamp_next + 1, ...;
-// before the first launch, and when 32 bits would run out, every record is
+// before the first launch, and when 32 bits would run out, every map is
 // cleared and numbering restarts at 1 (the bidirectional sampler's records
 // carry the same stamps).
 static void reserve_stamps(centra_ctx* ctx, uint32_t count, hipStream_t s) {
   if (ctx->stamp_next == 0 || uint64_t(ctx->stamp_next) + count > 0xFFFFFFFFull) {
-    fill_u64(static_cast<uint64_t*>(ctx->slot_rec.ptr), 0, size_t(ctx->slots) * ctx->slot_n * 2, s);
+    fill_u64(static_cast<uint64_t*>(ctx->slot_map.ptr), 0, size_t(ctx->slots) * ctx->slot_n, s);
     if (ctx->bi_rec_f.ptr) {
       fill_u64(static_cast<uint64_t*>(ctx->bi_rec_f.ptr), 0, size_t(ctx->bi_slots) * ctx->bi_n * 2, s);
       fill_u64(static_cast<uint64_t*>(ctx->bi_rec_b.ptr), 0, size_t(ctx->bi_slots) * ctx->bi_n * 2, s);
@@ -232,14 +260,13 @@ static int probe_slots(centra_ctx* ctx, SampleArgs a, const SamplePlan& plan, bo
                        hipStream_t s, float* ms) {
   for (int rep = 0; rep < 2; ++rep) {
     reserve_stamps(ctx, count, s);
-    fill_u32(static_cast<uint32_t*>(ctx->work_ctr.ptr), 0, 1, s);
-    fill_u64(reinterpret_cast<uint64_t*>(static_cast<char*>(ctx->work_ctr.ptr) + 8), 0, 3, s);
-    launch_args(ctx, a, plan, count, ctx->stage_nodes.bytes / 4);
+    fill_u64(static_cast<uint64_t*>(ctx->work_ctr.ptr), 0, kCtrBytes / 8, s);
+    launch_args(ctx, a, plan, count, ctx->stage_nodes.bytes / 4, kStageChunk);
     // a flooding sample would hold every probe as long as itself: it is
     // left out, as the timed launches leave it to the device-wide BFS
     int rc;
-    if (!multi && !plan.lds_bits && wide_enabled() && (rc = defer_args(ctx, a, s))) return rc;
     const uint32_t grid = count < ctx->slots ? count : ctx->slots;
+    if (!multi && !plan.lds_bits && wide_enabled() && (rc = defer_args(ctx, a, grid, s))) return rc;
     CENTRA_HIP(ctx, hipEventRecord(ctx->ev[6], s));
     sample_kernel_launch(a, plan.block, plan.lds_bits, multi, grid, plan.dyn_lds, s);
     CENTRA_HIP(ctx, hipGetLastError());
@@ -252,11 +279,11 @@ static int probe_slots(centra_ctx* ctx, SampleArgs a, const SamplePlan& plan, bo
 }
 
 // Chooses the fastest of kPlaceCandidates allocations of the (fresh) slot
-// records, by probe_slots.
+// maps, by probe_slots.
 static int place_slots(centra_ctx* ctx, const SampleArgs& a, const SamplePlan& plan, bool multi, uint32_t count,
                        hipStream_t s) {
-  const size_t rec_b = ctx->slot_rec.bytes;
-  if (rec_b < kPlaceMinBytes) return CENTRA_OK;
+  const size_t map_b = ctx->slot_map.bytes;
+  if (map_b < kPlaceMinBytes) return CENTRA_OK;
   ctx->placed = true;   // once per context: a later re-allocation keeps what it gets
   const uint32_t pc = count < kPlaceProbe ? count : kPlaceProbe;
   // every slot state held during the search must stay consistent with the
@@ -279,18 +306,18 @@ static int place_slots(centra_ctx* ctx, const SampleArgs& a, const SamplePlan& p
   bool go = since(t0) <= kPlaceStepMs;
   for (int c = 1; go && c < kPlaceCandidates && best > 0.f; ++c) {
     const auto tc = std::chrono::steady_clock::now();
-    if (ctx->budget && ctx->allocated + rec_b > ctx->budget) break;
+    if (ctx->budget && ctx->allocated + map_b > ctx->budget) break;
     void* r2 = nullptr;
-    if (hipMalloc(&r2, rec_b) != hipSuccess) {
+    if (hipMalloc(&r2, map_b) != hipSuccess) {
       (void)hipGetLastError();
       break;
     }
-    fill_u64(static_cast<uint64_t*>(r2), 0, rec_b / 8, s);   // stamp 0: never claimed
-    std::swap(ctx->slot_rec.ptr, r2);
+    fill_u64(static_cast<uint64_t*>(r2), 0, map_b / 8, s);   // stamp 0: never claimed
+    std::swap(ctx->slot_map.ptr, r2);
     float ms = 0.f;
     rc = probe_slots(ctx, a, plan, multi, pc, s, &ms);
     line += " " + std::to_string(ms);
-    if (rc || !(ms > 0.f && ms < best)) std::swap(ctx->slot_rec.ptr, r2);   // keep the previous one
+    if (rc || !(ms > 0.f && ms < best)) std::swap(ctx->slot_map.ptr, r2);   // keep the previous one
     else best = ms;
     (void)hipStreamSynchronize(s);
     (void)hipFree(r2);
@@ -321,90 +348,97 @@ static int launch_sampler(centra_ctx* ctx, SampleArgs a, uint32_t count, uint32_
   const uint32_t grid = count < ctx->slots ? count : ctx->slots;
   if ((rc = ensure(ctx, ctx->stage_pos, size_t(count) * 8, false, s))) return rc;
   if ((rc = ensure(ctx, ctx->stage_len, size_t(count) * 4 + 8 + 8 * (size_t(count) + 1), false, s))) return rc;
-  if ((rc = ensure(ctx, ctx->work_ctr, 64, false, s))) return rc;
+  if ((rc = ensure(ctx, ctx->work_ctr, kCtrBytes, false, s))) return rc;
   if (fresh && !ctx->placed && !async_cap && slot_search_enabled() && (rc = place_slots(ctx, a, plan, multi, count, s)))
     return rc;
+  // staging: workgroups reserve it in chunks of a few hyperedges of their
+  // share, of which each may leave one partly used (a stream-ordered launch's
+  // area holds the caller's capacity exactly: there every hyperedge is
+  // reserved by itself)
+  uint32_t chunk = async_cap ? 0u : std::min(kStageChunk, count / grid * 4);
+  const uint64_t slack = uint64_t(grid) * chunk;
   const uint64_t base_cap = async_cap ? async_cap : size_t(count) * 8 + 1024;
-  uint64_t cap = base_cap;
+  uint64_t cap = base_cap + slack;
   if (!async_cap && ctx->staged_samples) {
-    // entries per sample staged on this context so far, with half again as
+    // entries per sample reserved on this context so far, with half again as
     // a margin: an area too small makes the whole launch run twice
     const double per = 1.5 * double(ctx->staged_entries) / double(ctx->staged_samples);
-    const uint64_t est = static_cast<uint64_t>(per * double(count)) + 1024;
+    const uint64_t est = static_cast<uint64_t>(per * double(count)) + 1024 + slack;
     if (est > cap) cap = est;
   }
   if (ctx->stage_nodes.bytes / 4 > cap) cap = ctx->stage_nodes.bytes / 4;
   for (int attempt = 0; attempt < 3; ++attempt) {
     rc = ensure(ctx, ctx->stage_nodes, cap * 4, false, s);
     if (rc == CENTRA_ENOMEM && attempt == 0 && cap > base_cap && ctx->stage_nodes.bytes / 4 < cap) {
-      cap = base_cap;   // the estimate does not fit the budget: start from the plain size
+      cap = base_cap;   // the estimate does not fit the budget: the plain size, without chunks
+      chunk = 0;
+      rc = ensure(ctx, ctx->stage_nodes, cap * 4, false, s);
+    }
+    if (rc == CENTRA_ENOMEM && attempt > 0 && chunk) {   // an exact area, without chunks
+      chunk = 0;
+      cap -= slack;
       rc = ensure(ctx, ctx->stage_nodes, cap * 4, false, s);
     }
     if (rc) return rc;
     cap = ctx->stage_nodes.bytes / 4;
-    uint32_t* work = static_cast<uint32_t*>(ctx->work_ctr.ptr);
-    uint64_t* used = reinterpret_cast<uint64_t*>(static_cast<char*>(ctx->work_ctr.ptr) + 8);
-    fill_u32(work, 0, 1, s);
-    fill_u64(used, 0, 1, s);
+    fill_u64(static_cast<uint64_t*>(ctx->work_ctr.ptr), 0, kCtrBytes / 8, s);
     reserve_stamps(ctx, count, s);
-    launch_args(ctx, a, plan, count, cap);
+    launch_args(ctx, a, plan, count, cap, chunk);
     const bool wide = !async_cap && !multi && !plan.lds_bits && wide_enabled();
-    if (wide && (rc = defer_args(ctx, a, s))) return rc;
-    fill_u64(a.stats, 0, 2, s);
+    if (wide && (rc = defer_args(ctx, a, grid, s))) return rc;
     CENTRA_HIP(ctx, hipEventRecord(ctx->ev[6], s));
     sample_kernel_launch(a, plan.block, plan.lds_bits, multi, grid, plan.dyn_lds, s);
     CENTRA_HIP(ctx, hipGetLastError());
     if (async_cap) return CENTRA_OK;
     CENTRA_HIP(ctx, hipEventRecord(ctx->ev[7], s));
-    uint64_t host_ctr[5] = {0, 0, 0, 0, 0};   // work, used, arcs, nodes, deferred
-    CENTRA_HIP(ctx, hipMemcpyAsync(host_ctr, ctx->work_ctr.ptr, 40, hipMemcpyDeviceToHost, s));
+    uint64_t ctr[kCtrBytes / 8];
+    const uint64_t* stats = ctr + kCtrStats / 8;   // arcs, nodes, entries, deferred
+    CENTRA_HIP(ctx, hipMemcpyAsync(ctr, ctx->work_ctr.ptr, kCtrBytes, hipMemcpyDeviceToHost, s));
     CENTRA_HIP(ctx, hipStreamSynchronize(s));
     if ((rc = check_flags(ctx, s, "sample_paths"))) return rc;
-    const uint32_t n_wide = wide ? static_cast<uint32_t>(std::min<uint64_t>(host_ctr[4] & 0xFFFFFFFFull, kWideCap)) : 0u;
+    const uint64_t arcs = stats[0], nodes = stats[1];
+    const uint32_t n_wide = wide ? static_cast<uint32_t>(std::min<uint64_t>(stats[3] & 0xFFFFFFFFull, kWideCap)) : 0u;
     if (n_wide) {
-      // the deferred samples, one device-wide BFS each, on slot 0's state
+      // the deferred samples, one device-wide BFS each, on the slots' queues
+      // and (two slots' counts per sample) records
       std::vector<uint32_t> list(n_wide);
       CENTRA_HIP(ctx, hipMemcpyAsync(list.data(), a.defer_list, size_t(n_wide) * 4, hipMemcpyDeviceToHost, s));
       CENTRA_HIP(ctx, hipStreamSynchronize(s));
       uint64_t* ctl = static_cast<uint64_t*>(ctx->wide_ws.ptr);
       std::vector<uint64_t> host_ctl(size_t(kWideGroup) * 8);
       const auto w0 = std::chrono::steady_clock::now();
-      const uint32_t group = std::min<uint32_t>(kWideGroup, ctx->slots);
+      const uint32_t group = std::max<uint32_t>(1, std::min<uint32_t>(kWideGroup, ctx->slots / 2));
       for (uint32_t j0 = 0; j0 < n_wide; j0 += group) {   // a group at a time, one slot each
         const uint32_t nj = std::min<uint32_t>(group, n_wide - j0);
-        reserve_stamps(ctx, nj, s);
-        const uint64_t stamp0 = ctx->stamp_next;
-        ctx->stamp_next += nj;
-        uint64_t arcs = 0;
-        if (wide_samples(a, list.data() + j0, nj, stamp0, ctl, host_ctl.data(), &arcs, s) != CENTRA_OK)
+        uint64_t wide_arcs = 0;
+        if (wide_samples(a, list.data() + j0, nj, ctl, host_ctl.data(), &wide_arcs, s) != CENTRA_OK)
           return hip_fail(ctx, hipGetLastError(), "sample_paths (device-wide BFS)");
-        ctx->st.wide_arcs += arcs;
+        ctx->st.wide_arcs += wide_arcs;
       }
       ctx->st.wide_ms += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - w0).count();
-      CENTRA_HIP(ctx, hipMemcpyAsync(&host_ctr[1], static_cast<char*>(ctx->work_ctr.ptr) + 8, 8,
-                                     hipMemcpyDeviceToHost, s));
+      CENTRA_HIP(ctx, hipMemcpyAsync(ctr, ctx->work_ctr.ptr, kCtrBytes, hipMemcpyDeviceToHost, s));
       CENTRA_HIP(ctx, hipStreamSynchronize(s));
       if ((rc = check_flags(ctx, s, "sample_paths (device-wide BFS)"))) return rc;
       ctx->st.wide += n_wide;
     }
-    const uint64_t host_used = host_ctr[1];
+    const uint64_t used = ctr[kCtrUsed / 8], entries = stats[2];
     float ms = 0.f;
     if (hipEventElapsedTime(&ms, ctx->ev[6], ctx->ev[7]) != hipSuccess) ms = 0.f;
     ctx->st.launches += 1;
     ctx->st.kernel_ms += ms;
     ctx->st.samples += count;
-    ctx->st.arcs += host_ctr[2];
-    ctx->st.nodes += host_ctr[3];
-    ctx->st.hyperedge_nodes += host_used <= cap ? host_used : 0;
+    ctx->st.arcs += arcs;
+    ctx->st.nodes += nodes;
+    ctx->st.hyperedge_nodes += used <= cap ? entries : 0;
     ctx->st.lds_bitmap = plan.lds_bits ? 1 : 0;
     ctx->st.slots = grid;
-    if (host_used <= cap) {
-      *total = host_used;
-      ctx->staged_entries += host_used;
+    if (used <= cap) {
+      *total = entries;
+      ctx->staged_entries += used;
       ctx->staged_samples += count;
       return CENTRA_OK;
     }
-    cap = host_used + 1024;   // staging overflowed: the batch is redrawn identically
+    cap = used + slack + 1024;   // staging overflowed: the batch is redrawn identically
   }
   return fail(ctx, CENTRA_EHIP, "sample_paths: staging did not converge");
 }
@@ -515,7 +549,7 @@ int sample_reserve(centra_ctx* ctx, const centra_graph* g, uint32_t count, uint6
   if ((rc = ensure_slots(ctx, g->n, want ? want : 1, s, &fresh))) return rc;
   if ((rc = ensure(ctx, ctx->stage_pos, size_t(count) * 8, false, s))) return rc;
   if ((rc = ensure(ctx, ctx->stage_len, size_t(count) * 4 + 8 + 8 * (size_t(count) + 1), false, s))) return rc;
-  if ((rc = ensure(ctx, ctx->work_ctr, 64, false, s))) return rc;
+  if ((rc = ensure(ctx, ctx->work_ctr, kCtrBytes, false, s))) return rc;
   if ((rc = ensure(ctx, ctx->stage_nodes, (stage_entries ? stage_entries : 1) * 4, false, s))) return rc;
   return ensure(ctx, ctx->scan_tmp, scan_tile_words(count) * 8, false, s);
 }
