@@ -724,6 +724,145 @@ uint32_t greedy_hist_words() { return kGainBins; }
 
 uint32_t greedy_part_words() { return kArgGrid; }
 
+// ---------------------------------------------------------------------------
+// Greedy by one workgroup, gains and covered bits in LDS: a round needs no
+// global atomic, no other workgroup and no launch, so it takes 4.8
+// us (n = 2,000, m = 10,000, 45,000 entries, k = 10) where a round of kernels
+// takes 11.3 (two of them for one query, four for the engine's).  Per round: the largest key of the n gains; then each wave takes
+// 64 entries of the pick's rows at a time, marks the newly covered samples
+// and spreads the concatenation of their hyperedges over its lanes.
+constexpr int kSoloBlock = 1024;
+constexpr size_t kSoloLds = 144 << 10;      // of the 160 KB of a CU
+constexpr uint64_t kSoloEntries = 12288;    // hyperedge entries per round that one workgroup is given
+constexpr int kSoloUnroll = 4;              // hyperedge entries a lane has in flight
+
+struct SoloShared {
+  uint64_t seg_beg[kMaxSegments], seg_pre[kMaxSegments + 1];
+  uint64_t red[2 * Coll<kSoloBlock>::kHalf];
+  unsigned long long cov;   // samples covered so far
+};
+
+__device__ __forceinline__ void greedy_solo_run(const GreedyDesc& q, int32_t* gain, SoloShared& sh) {
+  Coll<kSoloBlock> co{sh.red, 0};
+  const uint32_t tid = threadIdx.x, n = q.n;
+  const int lane = lane_id();
+  uint32_t* covered = reinterpret_cast<uint32_t*>(gain + n);
+  for (uint32_t u = tid; u < n; u += kSoloBlock) gain[u] = static_cast<int32_t>(q.deg[u]);
+  for (uint64_t w = tid; w < (q.m + 31) / 32 + 1; w += kSoloBlock) covered[w] = 0;
+  if (tid == 0) sh.cov = 0;
+  __syncthreads();
+  uint32_t r = 0;
+  for (; r < q.k; ++r) {
+    int32_t top = 0;
+    uint32_t at = 0;
+    for (uint32_t u = tid; u < n; u += kSoloBlock) {
+      const int32_t g = gain[u];
+      at = g > top ? u : at;
+      top = g > top ? g : top;
+    }
+    const uint64_t key = co.max(gain_key(top, at));
+    if ((key >> 32) == 0) break;
+    const uint32_t pick = 0xFFFFFFFFu - static_cast<uint32_t>(key);
+    if (tid < kWave) {   // segment starts and the prefix of the row lengths (n_seg <= 64)
+      uint64_t rb = 0, len = 0;
+      if (tid < q.n_seg) {
+        const uint64_t* o = q.seg_off + size_t(tid) * (size_t(n) + 1);
+        rb = o[pick];
+        len = o[pick + 1] - rb;
+      }
+      const uint64_t incl = wave_incl_scan_u64(len);
+      if (tid < q.n_seg) {
+        sh.seg_beg[tid] = rb;
+        sh.seg_pre[tid + 1] = incl;
+      }
+      if (tid == 0) sh.seg_pre[0] = 0;
+    }
+    __syncthreads();
+    const uint64_t row = sh.seg_pre[q.n_seg];
+    uint32_t g = 0, cnt = 0;
+    for (uint64_t base = tid - lane; base < row; base += kSoloBlock) {   // uniform in the wave
+      const uint64_t x = base + lane;
+      uint64_t h0 = 0;
+      uint32_t len = 0;
+      bool fresh = false;
+      if (x < row) {
+        while (x >= sh.seg_pre[g + 1]) ++g;
+        const uint32_t s = q.inc[sh.seg_beg[g] + (x - sh.seg_pre[g])];
+        const uint32_t bit = 1u << (s & 31u);
+        fresh = !(atomicOr(&covered[s >> 5], bit) & bit);
+        if (fresh) {
+          h0 = q.he_off[s];
+          len = static_cast<uint32_t>(q.he_off[s + 1] - h0);
+        }
+      }
+      cnt += static_cast<uint32_t>(__popcll(__ballot(fresh)));
+      const uint32_t incl = wave_incl_scan_u32(len), off = incl - len;
+      const uint32_t total = lane_u32(incl, kWave - 1);
+      for (uint32_t e0 = 0; e0 < total; e0 += kWave * kSoloUnroll) {
+        uint32_t v[kSoloUnroll];
+#pragma unroll
+        for (int j = 0; j < kSoloUnroll; ++j) {
+          // the sample holding entry e: the last lane with off <= e (empty
+          // hyperedges repeat their successor's offset)
+          const uint32_t e = e0 + j * kWave + lane;
+          int lo = 0;
+#pragma unroll
+          for (int step = 32; step; step >>= 1)
+            if (static_cast<uint32_t>(__shfl(static_cast<int>(off), lo + step, kWave)) <= e) lo += step;
+          const uint64_t b = __shfl(h0, lo, kWave);
+          const uint32_t o = static_cast<uint32_t>(__shfl(static_cast<int>(off), lo, kWave));
+          v[j] = e < total ? q.he_nodes[b + (e - o)] : kUnseen;
+        }
+#pragma unroll
+        for (int j = 0; j < kSoloUnroll; ++j)
+          if (v[j] < n) atomicSub(&gain[v[j]], 1);
+      }
+    }
+    if (lane == 0 && cnt) atomicAdd(&sh.cov, static_cast<unsigned long long>(cnt));
+    __syncthreads();
+    if (tid == 0) {   // (sh.cov next changes after the next round's barriers)
+      q.picks[r] = pick;
+      q.cov_cum[r] = sh.cov;
+    }
+  }
+  if (tid == 0) *q.n_picked = r;
+}
+
+__global__ __launch_bounds__(kSoloBlock) void k_greedy_solo(GreedyDesc q) {
+  extern __shared__ int32_t solo_lds[];
+  __shared__ SoloShared sh;
+  greedy_solo_run(q, solo_lds, sh);
+}
+
+__global__ __launch_bounds__(kSoloBlock) void k_greedy_solo_multi(const GreedyDesc* d) {
+  extern __shared__ int32_t solo_lds[];
+  __shared__ SoloShared sh;
+  const GreedyDesc q = d[blockIdx.x];
+  if (q.k) greedy_solo_run(q, solo_lds, sh);
+}
+
+size_t greedy_solo_lds(uint32_t n, uint64_t m) { return size_t(n) * 4 + ((m + 31) / 32 + 1) * 4; }
+
+// One workgroup where the state fits its LDS and the hyperedges' nodes, of
+// which a round of kernels takes many at once, do not outweigh the rounds
+// (whole cover call, us, one workgroup against rounds; n = 2,000, m = 10,000:
+// 40,000 entries, k = 20: 291, 446; 300,000 entries, k = 50: 627, 760; k =
+// 20: 501, 487).
+bool greedy_solo(uint32_t n, uint64_t m, uint64_t entries, uint32_t k) {
+  return greedy_solo_lds(n, m) <= kSoloLds && entries <= uint64_t(k) * kSoloEntries;
+}
+
+template <typename F>
+static void allow_lds(F* f) {
+  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            static_cast<int>(kSoloLds));
+}
+
+void greedy_multi_solo(const GreedyDesc* d, uint32_t n_q, size_t lds, hipStream_t s) {
+  allow_lds(&k_greedy_solo_multi);
+  hipLaunchKernelGGL(k_greedy_solo_multi, dim3(n_q), dim3(kSoloBlock), lds, s, d);
+}
+
 __global__ void k_greedy_finish(const uint64_t* best, const uint64_t* newcov, uint32_t k, uint32_t* picks,
                                 uint64_t* cov_cum, uint32_t* n_picked) {
   if (threadIdx.x != 0 || blockIdx.x != 0) return;
@@ -740,13 +879,20 @@ __global__ void k_greedy_finish(const uint64_t* best, const uint64_t* newcov, ui
 }
 
 // Launches greedy's k rounds on an incidence of n_seg segments (offsets
-// seg_off, entries inc, degrees deg): gain u32[n], covered u32[m/32 + 1],
+// seg_off, entries inc (at most `entries`), degrees deg): gain u32[n], covered u32[m/32 + 1],
 // best u64[k + kArgGrid] and newcov u64[k] are the round state.  Launches
 // only.
 static void greedy_kernels(uint32_t n, uint64_t m, const uint64_t* he_off, const uint32_t* he_nodes, uint32_t k,
                            const uint32_t* deg, const uint64_t* seg_off, uint32_t n_seg, const uint32_t* inc,
                            int32_t* gain, uint32_t* cov, uint64_t* best, uint64_t* newcov, uint32_t* picks,
-                           uint64_t* cov_cum, uint32_t* n_picked, hipStream_t s) {
+                           uint64_t* cov_cum, uint32_t* n_picked, uint64_t entries, hipStream_t s) {
+  if (greedy_solo(n, m, entries, k)) {
+    const GreedyDesc q = {gain, cov, nullptr, best, newcov, deg, seg_off, inc, he_off, he_nodes, picks, cov_cum,
+                          n_picked, nullptr, nullptr, nullptr, m, n, n_seg, k, 0};
+    allow_lds(&k_greedy_solo);
+    hipLaunchKernelGGL(k_greedy_solo, dim3(1), dim3(kSoloBlock), greedy_solo_lds(n, m), s, q);
+    return;
+  }
   hipLaunchKernelGGL(k_gain_init, dim3(grid_for(n, 256)), dim3(256), 0, s, deg, n, gain);
   fill_u32(cov, 0, (m + 31) / 32 + 1, s);
   fill_u64(best, 0, k, s);
@@ -781,7 +927,7 @@ int greedy_on_incidence(centra_ctx* ctx, uint32_t n, uint64_t m, const uint64_t*
                  static_cast<const uint64_t*>(ctx->inc_off.ptr), ctx->inc_nseg,
                  static_cast<const uint32_t*>(ctx->inc.ptr), static_cast<int32_t*>(ctx->gain.ptr),
                  static_cast<uint32_t*>(ctx->covered.ptr), static_cast<uint64_t*>(ctx->best.ptr),
-                 static_cast<uint64_t*>(ctx->newcov.ptr), picks, cov_cum, n_picked, s);
+                 static_cast<uint64_t*>(ctx->newcov.ptr), picks, cov_cum, n_picked, ctx->inc_limit, s);
   CENTRA_HIP(ctx, hipGetLastError());
   return CENTRA_OK;
 }
@@ -872,7 +1018,7 @@ int greedy_cover_static(uint32_t n, uint64_t m, const uint64_t* he_off, const ui
   // here, and every other region is written before it is read
   fill_u32(flags, 0, 1, s);
   incidence_segment(n, 0, m, I, I, he_off, he_nodes, true, deg, sdeg, off, cur, inc, inc_node, tiles, flags, s);
-  greedy_kernels(n, m, he_off, he_nodes, k, deg, off, 1, inc, gain, cov, best, newcov, picks, cov_cum, n_picked, s);
+  greedy_kernels(n, m, he_off, he_nodes, k, deg, off, 1, inc, gain, cov, best, newcov, picks, cov_cum, n_picked, I, s);
   if ((e = hipGetLastError()) != hipSuccess) {
     *err = std::string("greedy_cover_noalloc: launch failed: ") + hipGetErrorString(e);
     return CENTRA_EHIP;

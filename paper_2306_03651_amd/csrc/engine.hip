@@ -455,16 +455,24 @@ static ResLayout res_layout(size_t at, uint32_t k, uint32_t t) {
   return L;
 }
 
-static int greedy_rounds(centra_engine* e, uint32_t cap_q, uint32_t max_n, uint32_t gc, uint32_t kmax, hipStream_t s) {
+// The tick's greedy runs; solo_lds > 0: all of them by one workgroup each.
+static int greedy_rounds(centra_engine* e, uint32_t cap_q, uint32_t max_n, uint32_t gc, uint32_t kmax, size_t solo_lds,
+                         hipStream_t s) {
   centra_ctx* ctx = e->ctx;
   GreedyDesc* d = static_cast<GreedyDesc*>(e->descs.ptr);
   uint32_t* rb = static_cast<uint32_t*>(e->round_base.ptr);
   fill_u32(rb, 0, 1, s);
-  const uint32_t chunks = (kmax + kRoundChunk - 1) / kRoundChunk;
+  const uint32_t chunks = solo_lds ? 1u : (kmax + kRoundChunk - 1) / kRoundChunk;
+  auto launch = [&](hipStream_t st) {
+    if (solo_lds)
+      greedy_multi_solo(d, cap_q, solo_lds, st);
+    else
+      greedy_multi_rounds(d, cap_q, max_n, gc, rb, kRoundChunk, st);
+  };
   if (e->flags & CENTRA_ENGINE_NO_GRAPHS) {
-    for (uint32_t c = 0; c < chunks; ++c) greedy_multi_rounds(d, cap_q, max_n, gc, rb, kRoundChunk, s);
+    for (uint32_t c = 0; c < chunks; ++c) launch(s);
     CENTRA_HIP(ctx, hipGetLastError());
-    e->st.greedy_launches += uint64_t(chunks) * (4 * kRoundChunk + 1);
+    e->st.greedy_launches += solo_lds ? 1 : uint64_t(chunks) * (4 * kRoundChunk + 1);
     return CENTRA_OK;
   }
   if (e->graphs_for != e->descs.ptr) {   // the descriptor buffer moved: drop graphs that read the old one
@@ -472,13 +480,13 @@ static int greedy_rounds(centra_engine* e, uint32_t cap_q, uint32_t max_n, uint3
     e->graphs.clear();
     e->graphs_for = e->descs.ptr;
   }
-  const auto gkey = std::make_tuple(cap_q, max_n, gc);
+  const auto gkey = std::make_tuple(cap_q, max_n, solo_lds ? static_cast<uint32_t>(solo_lds) : gc);
   auto it = e->graphs.find(gkey);
   if (it == e->graphs.end()) {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     CENTRA_HIP(ctx, hipStreamBeginCapture(e->cap_stream, hipStreamCaptureModeThreadLocal));
-    greedy_multi_rounds(d, cap_q, max_n, gc, rb, kRoundChunk, e->cap_stream);
+    launch(e->cap_stream);
     hipError_t err = hipStreamEndCapture(e->cap_stream, &graph);
     if (err != hipSuccess) return hip_fail(ctx, err, "engine: greedy capture");
     err = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
@@ -699,6 +707,12 @@ static int tick(centra_engine* e, double now, bool* progress, hipStream_t s) {
   size_t res_bytes = 0;
   uint32_t max_n = 0, kmax = 0, n_rows = 0, max_n_sel = 0;
   uint64_t max_m = 0;
+  // Every run is one that a workgroup does alone (they share the launch).  A
+  // tick of one run keeps the rounds, though it would gain too: serving
+  // queries that come 1.3 ms apart are expected to share ticks, and alone in
+  // a workgroup the earlier one is over by then.
+  bool solo = gg.size() > 1;
+  size_t solo_lds = 0;
   for (GGroup& G : gg) {
     G.lay = res_layout(res_bytes, G.k, 0);
     res_bytes = G.lay.end;
@@ -706,7 +720,14 @@ static int tick(centra_engine* e, double now, bool* progress, hipStream_t s) {
     max_n = std::max(max_n, p.g->n);
     kmax = std::max(kmax, G.k);
     max_m = std::max(max_m, p.level_m[G.level]);
+    solo_lds = std::max(solo_lds, greedy_solo_lds(p.g->n, p.level_m[G.level]));
   }
+  for (const GGroup& G : gg) {   // (every query's rounds take as long as the longest's)
+    const EnginePool& p = e->pools[G.pool];
+    solo = solo && greedy_solo(p.g->n, p.level_m[G.level], p.I_have, kmax);
+  }
+  // (in steps, for a few graph shapes only)
+  solo_lds = solo ? (solo_lds + 16383) / 16384 * 16384 : 0;
   for (SGroup& S : sg) {
     if (sel_prefix) {
       S.k = K_sel;
@@ -780,7 +801,7 @@ static int tick(centra_engine* e, double now, bool* progress, hipStream_t s) {
   hipEvent_t* ev = ctx->ev;
   CENTRA_HIP(ctx, hipEventRecord(ev[4], s));
   if (!gg.empty()) {
-    greedy_multi_init(dd, cap_q, max_n, s);
+    if (!solo_lds) greedy_multi_init(dd, cap_q, max_n, s);
     // cover parts per run: enough for the longest incidence row a run can
     // meet (at most its sample size) at 256 entries each, at most 256 (a
     // part then walks its share of the row in strides)
@@ -791,8 +812,8 @@ static int tick(centra_engine* e, double now, bool* progress, hipStream_t s) {
     // the captured graphs are keyed by the argmax shape: round max_n up
     uint32_t max_n_key = 4096;
     while (max_n_key < max_n) max_n_key <<= 1;
-    if ((rc = greedy_rounds(e, cap_q, max_n_key, gcp, kmax, s))) return rc;
-    greedy_multi_finish(dd, cap_q, s);
+    if ((rc = greedy_rounds(e, cap_q, max_n_key, gcp, kmax, solo_lds, s))) return rc;
+    if (!solo_lds) greedy_multi_finish(dd, cap_q, s);
   }
   CENTRA_HIP(ctx, hipEventRecord(ev[5], s));
   if (n_rows) {

@@ -257,6 +257,12 @@ struct GreedyDesc {
   uint64_t m;
   uint32_t n, n_seg, k, pad;
 };
+// Whether a run (entries: at most this many in its rows) is done by one
+// workgroup with its state in LDS, and the LDS bytes that takes.
+bool greedy_solo(uint32_t n, uint64_t m, uint64_t entries, uint32_t k);
+size_t greedy_solo_lds(uint32_t n, uint64_t m);
+// The whole runs of n_q such queries, a workgroup each (lds: the most any needs).
+void greedy_multi_solo(const GreedyDesc* d, uint32_t n_q, size_t lds, hipStream_t s);
 uint32_t greedy_part_words();
 uint32_t greedy_cand_words();
 uint32_t greedy_hist_words();
