@@ -707,11 +707,8 @@ static int tick(centra_engine* e, double now, bool* progress, hipStream_t s) {
   size_t res_bytes = 0;
   uint32_t max_n = 0, kmax = 0, n_rows = 0, max_n_sel = 0;
   uint64_t max_m = 0;
-  // Every run is one that a workgroup does alone (they share the launch).  A
-  // tick of one run keeps the rounds, though it would gain too: serving
-  // queries that come 1.3 ms apart are expected to share ticks, and alone in
-  // a workgroup the earlier one is over by then.
-  bool solo = gg.size() > 1;
+  // every run is one that a workgroup does alone (they share the launch)
+  bool solo = !gg.empty();
   size_t solo_lds = 0;
   for (GGroup& G : gg) {
     G.lay = res_layout(res_bytes, G.k, 0);
@@ -1077,6 +1074,14 @@ int centra_engine_submit(centra_engine* e, uint32_t pool_id, uint32_t k, uint32_
   return CENTRA_OK;
 }
 
+// In a realtime run, a tick that drew samples for one query alone lasts at
+// least this long: queries that arrive within a few ms of each other are meant
+// to share their ticks (one fused launch per level), and a lone one would
+// otherwise be through its levels before the next is there (a level takes 0.3
+// to 1.2 ms; it took 1.7 ms, so no query finishes later than it did).  Ticks
+// answered from cached levels are not held.
+constexpr double kLonePaceS = 1.5e-3;
+
 int centra_engine_run(centra_engine* e, int realtime, void* stream) {
   if (!e) return CENTRA_EINVAL;
   centra_ctx* ctx = e->ctx;
@@ -1092,7 +1097,15 @@ int centra_engine_run(centra_engine* e, int realtime, void* stream) {
     if (!pending) break;
     const double now = realtime ? now_s() - e->run_t0 : 1e300;
     bool progress = false;
+    const uint64_t drawn = e->st.samples;
+    const double begun = now_s();
     if ((rc = tick(e, now, &progress, s))) break;
+    if (realtime && e->st.samples != drawn) {
+      uint32_t active = 0;
+      for (const EngineQuery& q : e->queries) active += q.state == 1;
+      const double rest = begun + kLonePaceS - now_s();
+      if (active == 1 && rest > 0) std::this_thread::sleep_for(std::chrono::duration<double>(rest));
+    }
     if (!progress) {
       if (!realtime) {
         rc = fail(ctx, CENTRA_EHIP, "engine_run: no progress");
