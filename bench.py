@@ -649,7 +649,7 @@ def main():
     traffic = None if bidir else read_traffic(W["traffic"])
     roofline = {"bound": "hbm", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 5), "traffic": traffic,
-                "kernel": "k_tri_sample" if tri else "k_kpath + k_kpath_gather" if kp else
+                "kernel": "k_tri_pick" if tri else "k_kpath + k_kpath_gather" if kp else
                 "k_sample_bidir" if bidir else "k_sample_paths",
                 "launches": st.launches,
                 "avg_launch_ms": round(st.kernel_ms / launches, 3),

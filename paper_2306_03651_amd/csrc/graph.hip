@@ -267,6 +267,7 @@ void release_graph_buffers(centra_ctx* ctx, centra_graph* g) {
   release(ctx, g->tri_c);
   release(ctx, g->tri_cap);
   release(ctx, g->tri_dir);
+  release(ctx, g->tri_abc);
   g->tri_list_off = nullptr;
   g->tri_dir_w = 0;
 }
