@@ -359,7 +359,9 @@ CENTRA_API int centra_check(centra_ctx *ctx, void *stream);
  * immediately around each launch.
  * arcs counts every CSR entry the kernel scans (level expansions, the
  * checks around t, the backtrack is not included); nodes counts every node
- * given a level.  A re-launch after a staging overflow counts again.
+ * given a level (the bidirectional sampler gives none to those of a search's
+ * last level that it only has to look at).  A re-launch after a staging
+ * overflow counts again.
  * Wide samples: a BFS about to expand a level of more than 65,536 nodes,
  * or a level of at least 4,096 nodes or 65,536 arcs once it has scanned more
  * CSR entries than its launch's budget (4,096 for each work item of a

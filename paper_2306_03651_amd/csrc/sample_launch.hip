@@ -41,7 +41,7 @@ static size_t slot_bytes(uint32_t n) { return size_t(n) * (8 + 8 + 4) + start_wo
 // Slot state takes at most half of the device's memory (96 GiB if the size
 // cannot be queried; asked once per context); the context budget, when set,
 // limits it further.
-static size_t slot_mem_cap(centra_ctx* ctx) {
+size_t slot_mem_cap(centra_ctx* ctx) {
   if (ctx->slot_cap) return ctx->slot_cap;
   size_t free_b = 0, total_b = 0;
   if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || total_b == 0) {
