@@ -192,7 +192,7 @@ void centra_destroy(centra_ctx* ctx) {
                     &ctx->stage_len, &ctx->work_ctr, &ctx->scan_tmp, &ctx->deg, &ctx->inc_off,
                     &ctx->inc_cursor, &ctx->inc, &ctx->inc_node, &ctx->gain, &ctx->covered, &ctx->best,
                     &ctx->newcov, &ctx->words, &ctx->P, &ctx->Rtm, &ctx->topk_tmp, &ctx->misc,
-                    &ctx->store_off, &ctx->store_nodes, &ctx->kp_len, &ctx->kp_stage, &ctx->inc_ws, &ctx->seg_deg, &ctx->multi_tab, &ctx->sel_rows, &ctx->ext_bmax, &ctx->bi_rec_f, &ctx->bi_rec_b, &ctx->bi_q_f,
+                    &ctx->store_off, &ctx->store_nodes, &ctx->kp_len, &ctx->kp_stage, &ctx->inc_ws, &ctx->batch_ws, &ctx->seg_deg, &ctx->multi_tab, &ctx->sel_rows, &ctx->ext_bmax, &ctx->bi_rec_f, &ctx->bi_rec_b, &ctx->bi_q_f,
                     &ctx->bi_q_b};
   for (DevBuf* b : bufs) release(ctx, *b);
   if (ctx->d_flags) (void)hipFree(ctx->d_flags);
@@ -370,7 +370,7 @@ int centra_greedy_cover(centra_ctx* ctx, uint32_t n, uint64_t m, const uint64_t*
   if (rc) return rc;
   if ((rc = build_incidence(ctx, n, 0, m, he_off, he_nodes, s))) return rc;
   if ((rc = check_flags(ctx, s, "greedy_cover"))) return rc;
-  if ((rc = greedy_on_incidence(ctx, n, m, he_off, he_nodes, k, picks, cov_cum, n_picked, s))) return rc;
+  if ((rc = greedy_on_incidence(ctx, true, n, m, he_off, he_nodes, k, picks, cov_cum, n_picked, s))) return rc;
   CENTRA_HIP(ctx, hipStreamSynchronize(s));
   return CENTRA_OK;
 }
@@ -456,7 +456,7 @@ int centra_extend(centra_ctx* ctx, const centra_extend_args* a, void* stream) {
   ctx->ext_cap = a->he_cap;
   ctx->ext_n = n;
   if (a->picks &&
-      (rc = greedy_on_incidence(ctx, n, m, a->he_off, a->he_nodes, a->k, a->picks, a->cov_cum, a->n_picked, s)))
+      (rc = greedy_on_incidence(ctx, false, n, m, a->he_off, a->he_nodes, a->k, a->picks, a->cov_cum, a->n_picked, s)))
     return rc;
   if (a->t) {
     // the counts extend from mc_m only if it starts a segment (the entries
@@ -671,7 +671,7 @@ int progressive_run(centra_ctx* ctx, const centra_graph* g, const centra_params*
     uint32_t* store_nodes = static_cast<uint32_t*>(ctx->store_nodes.ptr);
     CENTRA_HIP(ctx, hipEventRecord(ev[1], s));
     if ((rc = build_incidence(ctx, n, m_prev, m_i, store_off, store_nodes, s))) return rc;
-    if ((rc = greedy_on_incidence(ctx, n, m_i, store_off, store_nodes, k, reinterpret_cast<uint32_t*>(misc),
+    if ((rc = greedy_on_incidence(ctx, true, n, m_i, store_off, store_nodes, k, reinterpret_cast<uint32_t*>(misc),
                                   reinterpret_cast<uint64_t*>(misc + o_cov), reinterpret_cast<uint32_t*>(misc + o_np),
                                   s)))
       return rc;

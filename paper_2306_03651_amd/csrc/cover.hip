@@ -461,6 +461,381 @@ __global__ __launch_bounds__(kCoverBlock) void k_cover(const uint64_t* part, uin
 }
 
 // ---------------------------------------------------------------------------
+// Greedy in batches of picks.  A round of two kernels is a chain of dependent
+// trips to memory, 21 us however few samples it covers (n = m = 10^6), and
+// greedy needs k of them in sequence.  But the picks that follow one another
+// mostly come from the few nodes of largest gain, and while one of those is
+// the best of all, the rounds depend on nothing but the samples that several
+// of them share.  So a batch
+//   1. finds up to 64 candidates, the nodes of largest gain, and tau, the
+//      largest key (gain << 32 | ~u) of any other node;
+//   2. sets, for every uncovered sample of their rows, the bits of the
+//      candidates it holds in a mask of the sample, and lists the masks of two
+//      bits or more;
+//   3. runs greedy rounds over the candidates in one workgroup: a candidate's
+//      gain only falls by the listed masks it shares with a pick.  Gains only
+//      fall, so as long as the best candidate's key exceeds tau, it is the
+//      largest of all nodes': the sequential greedy's pick;
+//   4. covers the picks' rows at once (the order of covering changes no gain).
+// The first round's pick always is a candidate, so a batch has at least one;
+// two batches make 50 picks on the hyperedge sets and path samples measured.
+// The host reads how far a batch came and starts another, or, where batches
+// yield little, goes on by rounds.  n = m = 10^6, 4M entries, k = 50: 1,040 us
+// by rounds, 270 in batches; BA n = 10^5, 400,000 path samples, k = 50: 650 by
+// rounds, 280 in batches.
+constexpr uint32_t kCands = 64;
+constexpr uint32_t kTopBlocks = 64, kTopBlock = 256, kTopCols = kTopBlocks * kTopBlock;
+constexpr uint32_t kBatchBlock = 1024;
+constexpr uint32_t kBatchSegs = 16;            // incidence segments at most
+constexpr uint32_t kBatchRows = kCands * kBatchSegs;
+constexpr uint32_t kBatchList = 1u << 18;      // masks listed at most
+constexpr uint32_t kBatchMinK = 12;            // rounds from which batches pay
+constexpr uint32_t kBatchMinPicks = 8;         // a batch with fewer is the last
+
+// Device state of a batch.  Row i = c * n_seg + g is candidate c's in segment
+// g; pre is the prefix of the rows' lengths.
+struct BatchState {
+  uint64_t tau;
+  uint32_t r;          // rounds done
+  uint32_t fail;       // a node twice in a hyperedge, or more masks than the list holds
+  uint32_t done;       // no positive gain is left
+  uint32_t n_cand, n_list, pad;
+  uint32_t node[kCands];
+  int32_t gain[kCands];
+  uint64_t chosen;     // bits of the candidates that were picked
+  uint64_t beg[kBatchRows], pre[kBatchRows + 1];
+};
+
+struct BatchArgs {
+  uint32_t n, n_seg, k;
+  const uint64_t* seg_off;
+  const uint32_t* inc;
+  const uint64_t* he_off;
+  const uint32_t* he_nodes;
+  int32_t* gain;
+  uint32_t* covered;
+  uint64_t* best;     // u64[k] keys
+  uint64_t* newcov;   // u64[k]
+  uint64_t* part;     // u64[kTopCols + kTopBlocks]
+  BatchState* st;
+  uint64_t* list;     // u64[kBatchList]
+  uint64_t* mask;     // u64[m]
+};
+
+// Bin of a positive gain: 8 bins per bit length, by the 3 bits below the
+// leading one (nondecreasing in g).  (The engine's lists use it too.)
+constexpr uint32_t kGainBins = 256;
+__device__ __forceinline__ uint32_t gain_bin(uint32_t g) {
+  const uint32_t bl = 32u - __clz(g);
+  const uint32_t sub = bl >= 4 ? (g >> (bl - 4)) & 7u : (g << (4 - bl)) & 7u;
+  return (bl - 1) * 8 + sub;
+}
+
+// The last row that starts at or before entry e.
+__device__ __forceinline__ uint32_t batch_row(const uint64_t* pre, uint64_t e) {
+  uint32_t i = 0;
+#pragma unroll
+  for (uint32_t step = kBatchRows / 2; step; step >>= 1)
+    if (pre[i + step] <= e) i += step;
+  return i;
+}
+
+// Calls f(sample, candidate) for every entry of the candidates' rows.
+template <typename F>
+__device__ __forceinline__ void batch_entries(const BatchArgs& a, uint64_t* pre, const F& f) {
+  for (uint32_t i = threadIdx.x; i <= kBatchRows; i += blockDim.x) pre[i] = a.st->pre[i];
+  __syncthreads();
+  const uint64_t total = pre[kBatchRows];
+  for (uint64_t e0 = uint64_t(blockIdx.x) * blockDim.x; e0 < total; e0 += uint64_t(gridDim.x) * blockDim.x) {
+    const uint64_t e = e0 + threadIdx.x;
+    if (e >= total) continue;
+    const uint32_t i = batch_row(pre, e);
+    f(a.inc[a.st->beg[i] + (e - pre[i])], i / a.n_seg);
+  }
+}
+
+// part[x] = the largest key of the nodes u = x mod kTopCols (nodes of large
+// gain often are neighbours by id: that spreads them), part[kTopCols + b] the
+// largest of the second keys of workgroup b's columns.
+// Masks that the batch before set are cleared.
+__global__ __launch_bounds__(kTopBlock) void k_batch_top(BatchArgs a, int first) {
+  __shared__ uint64_t red[kTopBlock / kWave];
+  __shared__ uint64_t pre[kBatchRows + 1];
+  if (!first) batch_entries(a, pre, [&](uint32_t s, uint32_t) { a.mask[s] = 0; });
+  constexpr int kLoads = 16;
+  const uint32_t x = blockIdx.x * kTopBlock + threadIdx.x;
+  uint64_t k1 = 0, k2 = 0;
+  for (uint64_t u0 = x; u0 < a.n; u0 += uint64_t(kLoads) * kTopCols) {
+    int32_t g[kLoads];
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j) {
+      const uint64_t u = u0 + uint64_t(j) * kTopCols;
+      g[j] = u < a.n ? a.gain[u] : 0;
+    }
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j) {
+      const uint64_t key = gain_key(g[j], static_cast<uint32_t>(u0) + j * kTopCols);
+      const uint64_t low = key < k1 ? key : k1;
+      k1 = key > k1 ? key : k1;
+      k2 = low > k2 ? low : k2;
+    }
+  }
+  a.part[x] = k1;
+  k2 = block_max_u64<kTopBlock>(k2, red);
+  if (threadIdx.x == 0) a.part[kTopCols + blockIdx.x] = k2;
+}
+
+// The candidates: the largest of the columns' keys, and of the others those
+// of the bins of gains that fit; tau; the candidates' rows.
+__global__ __launch_bounds__(kBatchBlock) void k_batch_cands(BatchArgs a) {
+  __shared__ uint64_t red[2 * Coll<kBatchBlock>::kHalf];
+  __shared__ uint32_t hist[kGainBins], cut, used;
+  __shared__ uint32_t node[kCands];
+  Coll<kBatchBlock> co{red, 0};
+  constexpr uint32_t kOwn = kTopCols / kBatchBlock;
+  const uint32_t tid = threadIdx.x;
+  uint64_t key[kOwn], mx = 0, tau = tid < kTopBlocks ? a.part[kTopCols + tid] : 0ull;
+#pragma unroll
+  for (uint32_t i = 0; i < kOwn; ++i) key[i] = a.part[i * kBatchBlock + tid];
+  if (tid < kGainBins) hist[tid] = 0;
+  if (tid < kCands) node[tid] = kUnseen;
+  if (tid == 0) used = 1;   // place 0 is the largest's
+  __syncthreads();
+#pragma unroll
+  for (uint32_t i = 0; i < kOwn; ++i) {
+    if (key[i]) atomicAdd(&hist[gain_bin(static_cast<uint32_t>(key[i] >> 32))], 1u);
+    mx = key[i] > mx ? key[i] : mx;
+  }
+  mx = co.max(mx);
+  if (tid < kWave) {
+    // the lowest bin that, with those above it, holds at most kCands keys
+    // (the top one in any case: what does not fit counts for tau)
+    uint32_t h[kGainBins / kWave], sum = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < kGainBins / kWave; ++j) {
+      h[j] = hist[kGainBins - 1 - (tid * (kGainBins / kWave) + j)];
+      sum += h[j];
+    }
+    uint32_t run = wave_incl_scan_u32(sum) - sum, fit = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < kGainBins / kWave; ++j) {
+      run += h[j];
+      fit += run <= kCands ? 1u : 0u;
+    }
+    fit = wave_sum_u32(fit);   // bins from the top that fit together
+    if (tid == 0) {
+      const uint32_t top = mx ? gain_bin(static_cast<uint32_t>(mx >> 32)) : 0u;
+      const uint32_t lowest = kGainBins - fit;
+      cut = lowest < top ? lowest : top;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (uint32_t i = 0; i < kOwn; ++i) {
+    if (!key[i]) continue;
+    uint32_t at = kCands;
+    if (key[i] == mx)
+      at = 0;
+    else if (gain_bin(static_cast<uint32_t>(key[i] >> 32)) >= cut)
+      at = atomicAdd(&used, 1u);
+    if (at < kCands) {
+      node[at] = 0xFFFFFFFFu - static_cast<uint32_t>(key[i]);
+      a.st->node[at] = node[at];
+      a.st->gain[at] = static_cast<int32_t>(key[i] >> 32);
+    } else {
+      tau = key[i] > tau ? key[i] : tau;
+    }
+  }
+  tau = co.max(tau);
+  const uint32_t n_cand = mx ? (used < kCands ? used : kCands) : 0u, rows = n_cand * a.n_seg;   // (rows <= kBatchBlock)
+  uint64_t rb = 0, len = 0, total;
+  if (tid < rows) {
+    const uint64_t* o = a.seg_off + size_t(tid % a.n_seg) * (size_t(a.n) + 1) + node[tid / a.n_seg];
+    rb = o[0];
+    len = o[1] - rb;
+  }
+  const uint64_t before = co.scan(len, &total);
+  a.st->beg[tid] = rb;
+  a.st->pre[tid] = before;
+  if (tid == 0) {
+    a.st->pre[kBatchRows] = total;
+    a.st->tau = tau;
+    a.st->n_cand = n_cand;
+    a.st->n_list = 0;
+    a.st->done = mx ? 0u : 1u;
+  }
+}
+
+__global__ __launch_bounds__(256) void k_batch_mask(BatchArgs a) {
+  __shared__ uint64_t pre[kBatchRows + 1];
+  batch_entries(a, pre, [&](uint32_t s, uint32_t c) {
+    if (a.covered[s >> 5] >> (s & 31u) & 1u) return;
+    const uint64_t old = atomicOr(reinterpret_cast<unsigned long long*>(&a.mask[s]), 1ull << c);
+    if (old >> c & 1ull) a.st->fail = 1;
+  });
+}
+
+// (One addition to the list's length per workgroup and step: one per wave took
+// 19 us for 130,000 entries, the additions to one word in a row.)
+__global__ __launch_bounds__(256) void k_batch_list(BatchArgs a) {
+  __shared__ uint64_t pre[kBatchRows + 1], red[2 * Coll<256>::kHalf];
+  __shared__ uint32_t base;
+  Coll<256> co{red, 0};
+  for (uint32_t i = threadIdx.x; i <= kBatchRows; i += 256) pre[i] = a.st->pre[i];
+  __syncthreads();
+  const uint64_t total = pre[kBatchRows];
+  for (uint64_t e0 = uint64_t(blockIdx.x) * 256; e0 < total; e0 += uint64_t(gridDim.x) * 256) {   // uniform
+    const uint64_t e = e0 + threadIdx.x;
+    uint64_t w = 0;
+    if (e < total) {
+      const uint32_t i = batch_row(pre, e);
+      w = a.mask[a.inc[a.st->beg[i] + (e - pre[i])]];
+      // two bits at least, and the lowest candidate's entry
+      if ((w & (w - 1)) == 0 || (w & (0ull - w)) != 1ull << (i / a.n_seg)) w = 0;
+    }
+    uint64_t found;
+    const uint32_t at = static_cast<uint32_t>(co.scan(w ? 1u : 0u, &found));
+    if (found && threadIdx.x == 0) base = atomicAdd(&a.st->n_list, static_cast<uint32_t>(found));
+    __syncthreads();
+    if (w) {
+      if (base + at < kBatchList)
+        a.list[base + at] = w;
+      else
+        a.st->fail = 1;
+    }
+    __syncthreads();
+  }
+}
+
+// The rounds over the candidates.  Thread t owns the masks t, t + 1024, ... of
+// the list and drops those that a pick covers.
+__global__ __launch_bounds__(kBatchBlock) void k_batch_solve(BatchArgs a) {
+  __shared__ int32_t gain[kCands];
+  __shared__ uint32_t node[kCands];
+  __shared__ uint32_t pick;
+  const uint32_t tid = threadIdx.x;
+  if (tid < kCands) {
+    const bool is = tid < a.st->n_cand;
+    gain[tid] = is ? a.st->gain[tid] : 0;
+    node[tid] = is ? a.st->node[tid] : 0u;
+  }
+  const uint32_t n_list = a.st->n_list;
+  uint32_t own = a.st->fail || tid >= n_list ? 0u : (n_list - tid + kBatchBlock - 1) / kBatchBlock;
+  uint32_t r = a.st->r;
+  uint64_t chosen = 0;
+  const uint64_t tau = a.st->tau;
+  const bool run = !a.st->fail;
+  __syncthreads();
+  while (run && r < a.k) {
+    if (tid < kWave) {
+      const uint64_t key = gain_key(gain[tid], node[tid]);
+      const uint64_t mx = wave_max_u64(key);
+      if (key == mx && mx > tau) {   // one lane: keys are distinct, mx > 0
+        pick = tid;
+        a.best[r] = key;
+        a.newcov[r] = key >> 32;
+        gain[tid] = 0;
+      }
+      if (mx <= tau) {
+        pick = kCands;
+        if (tau == 0 && tid == 0) a.st->done = 1;   // (mx is 0 too: no gain is left anywhere)
+      }
+    }
+    __syncthreads();
+    const uint32_t c = pick;
+    if (c == kCands) break;
+    uint32_t kept = 0;
+    constexpr uint32_t kLoads = 8;   // masks under way at once
+    for (uint32_t i = 0; i < own; i += kLoads) {
+      uint64_t x[kLoads];
+#pragma unroll
+      for (uint32_t j = 0; j < kLoads; ++j) x[j] = i + j < own ? a.list[size_t(i + j) * kBatchBlock + tid] : 0ull;
+#pragma unroll
+      for (uint32_t j = 0; j < kLoads; ++j) {
+        uint64_t m = x[j];
+        if (m >> c & 1ull) {
+          for (m &= ~(1ull << c); m; m &= m - 1)
+            atomicSub(&gain[__ffsll(static_cast<unsigned long long>(m)) - 1], 1);
+        } else if (m) {
+          if (kept != i + j) a.list[size_t(kept) * kBatchBlock + tid] = m;   // (at or below the places read)
+          ++kept;
+        }
+      }
+    }
+    own = kept;
+    ++r;
+    chosen |= 1ull << c;
+    __syncthreads();
+  }
+  if (tid == 0) {
+    a.st->r = r;
+    a.st->chosen = chosen;
+  }
+}
+
+// Covers the picks' rows.  A sample is covered by the entry of its first pick
+// (its mask says which), so no thread needs the answer of an atomic.  A
+// hyperedge of up to kShort nodes is walked by that entry's thread; longer
+// ones (paths of thousands of nodes) by the workgroup, the concatenation of
+// the step's split evenly over the threads.
+__global__ __launch_bounds__(kCoverBlock) void k_batch_cover(BatchArgs a) {
+  constexpr uint32_t kShort = 8;
+  __shared__ AggTable tab;
+  __shared__ uint64_t pre[kBatchRows + 1], hbeg[kCoverBlock];
+  __shared__ uint32_t hoff[kCoverBlock], scan[kCoverBlock / kWave + 1];
+  for (uint32_t i = threadIdx.x; i <= kBatchRows; i += kCoverBlock) pre[i] = a.st->pre[i];
+  agg_init(tab);
+  const uint64_t chosen = a.st->chosen;
+  __syncthreads();
+  const uint64_t total_e = chosen ? pre[kBatchRows] : 0ull;
+  const uint64_t stride = uint64_t(gridDim.x) * kCoverBlock;
+  for (uint64_t e0 = uint64_t(blockIdx.x) * kCoverBlock; e0 < total_e; e0 += stride) {   // uniform trip count
+    const uint64_t e = e0 + threadIdx.x;
+    uint32_t len = 0;
+    uint64_t h0 = 0;
+    const uint32_t i = e < total_e ? batch_row(pre, e) : 0u;
+    if (e < total_e && chosen >> (i / a.n_seg) & 1ull) {
+      const uint32_t s = a.inc[a.st->beg[i] + (e - pre[i])];
+      const uint64_t w = a.mask[s] & chosen;
+      if ((w & (0ull - w)) == 1ull << (i / a.n_seg)) {
+        h0 = a.he_off[s];
+        len = static_cast<uint32_t>(a.he_off[s + 1] - h0);
+        atomicOr(&a.covered[s >> 5], 1u << (s & 31u));
+        if (len <= kShort) {
+          uint32_t v[kShort];
+#pragma unroll
+          for (uint32_t j = 0; j < kShort; ++j) v[j] = j < len ? a.he_nodes[h0 + j] : kUnseen;
+#pragma unroll
+          for (uint32_t j = 0; j < kShort; ++j)
+            if (v[j] < a.n && !agg_add(tab, v[j])) atomicSub(&a.gain[v[j]], 1);
+          len = 0;
+        }
+      }
+    }
+    if (!__syncthreads_or(len != 0)) continue;
+    uint32_t total;
+    const uint32_t off = block_excl_scan_u32<kCoverBlock>(len, &total, scan);
+    hbeg[threadIdx.x] = h0;
+    hoff[threadIdx.x] = off;
+    __syncthreads();
+    for (uint32_t x = threadIdx.x; x < total; x += kCoverBlock) {
+      // the sample holding entry x: the last i with hoff[i] <= x (the others,
+      // without nodes to walk, repeat their successor's offset)
+      uint32_t l = 0;
+#pragma unroll
+      for (uint32_t step = kCoverBlock / 2; step; step >>= 1)
+        if (hoff[l + step] <= x) l += step;
+      const uint32_t v = a.he_nodes[hbeg[l] + (x - hoff[l])];
+      if (v < a.n && !agg_add(tab, v)) atomicSub(&a.gain[v], 1);
+    }
+    __syncthreads();
+  }
+  __syncthreads();
+  for (uint32_t i = threadIdx.x; i < kAggSize; i += kCoverBlock)
+    if (tab.key[i] != kUnseen) atomicSub(&a.gain[tab.key[i]], static_cast<int32_t>(tab.cnt[i]));
+}
+
+// ---------------------------------------------------------------------------
 // Greedy of many queries at once (the engine's fused rounds): blockIdx.y
 // selects the query's descriptor; a query whose k is reached, or that is
 // inactive (k = 0), leaves its workgroups at once.  The round number comes
@@ -482,16 +857,7 @@ __global__ __launch_bounds__(kCoverBlock) void k_cover(const uint64_t* part, uin
 //   list     one workgroup scans the list.
 // The round after a list's largest gain falls below tau is full again.
 constexpr uint32_t kCandMax = 8192;
-constexpr uint32_t kGainBins = 256;
 constexpr uint32_t kModeFull = 0, kModeCompact = 1, kModeList = 2;
-
-// Bin of a positive gain: 8 bins per bit length, by the 3 bits below the
-// leading one (nondecreasing in g).
-__device__ __forceinline__ uint32_t gain_bin(uint32_t g) {
-  const uint32_t bl = 32u - __clz(g);
-  const uint32_t sub = bl >= 4 ? (g >> (bl - 4)) & 7u : (g << (4 - bl)) & 7u;
-  return (bl - 1) * 8 + sub;
-}
 
 // Smallest gain of bin b (or of the next nonempty bin above it).
 __device__ __forceinline__ uint32_t bin_min(uint32_t b) {
@@ -863,25 +1229,55 @@ void greedy_multi_solo(const GreedyDesc* d, uint32_t n_q, size_t lds, hipStream_
   hipLaunchKernelGGL(k_greedy_solo_multi, dim3(n_q), dim3(kSoloBlock), lds, s, d);
 }
 
-__global__ void k_greedy_finish(const uint64_t* best, const uint64_t* newcov, uint32_t k, uint32_t* picks,
-                                uint64_t* cov_cum, uint32_t* n_picked) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// The rounds' results, up to the first without a gain, by one wave.
+__global__ __launch_bounds__(kWave) void k_greedy_finish(const uint64_t* best, const uint64_t* newcov, uint32_t k,
+                                                         uint32_t* picks, uint64_t* cov_cum, uint32_t* n_picked) {
   uint64_t cov = 0;
-  uint32_t r = 0;
-  for (; r < k; ++r) {
-    const uint64_t key = best[r];
-    if ((key >> 32) == 0) break;
-    cov += newcov[r];
-    picks[r] = 0xFFFFFFFFu - static_cast<uint32_t>(key);
-    cov_cum[r] = cov;
+  uint32_t r0 = 0, n = 0;
+  for (; r0 < k; r0 += kWave) {
+    const uint32_t r = r0 + threadIdx.x;
+    const uint64_t key = r < k ? best[r] : 0ull;
+    const uint64_t end = __ballot((key >> 32) == 0);
+    const uint32_t here = end ? __ffsll(static_cast<unsigned long long>(end)) - 1 : kWave;
+    const uint64_t incl = wave_incl_scan_u64(threadIdx.x < here ? newcov[r] : 0ull);
+    if (threadIdx.x < here) {
+      picks[r] = 0xFFFFFFFFu - static_cast<uint32_t>(key);
+      cov_cum[r] = cov + incl;
+    }
+    n += here;
+    cov += lane_u64(incl, kWave - 1);
+    if (end) break;
   }
-  *n_picked = r;
+  if (threadIdx.x == 0) *n_picked = n;
+}
+
+// The round state's start: gain, covered and the rounds' keys and counts.
+static void greedy_start(uint32_t n, uint64_t m, uint32_t k, const uint32_t* deg, int32_t* gain, uint32_t* cov,
+                         uint64_t* best, uint64_t* newcov, hipStream_t s) {
+  hipLaunchKernelGGL(k_gain_init, dim3(grid_for(n, 256)), dim3(256), 0, s, deg, n, gain);
+  fill_u32(cov, 0, (m + 31) / 32 + 1, s);
+  fill_u64(best, 0, k, s);
+  fill_u64(newcov, 0, k, s);
+}
+
+// Rounds r0 .. k - 1, each by an argmax and a covering kernel.
+static void greedy_rounds(uint32_t r0, uint32_t n, const uint64_t* he_off, const uint32_t* he_nodes, uint32_t k,
+                          const uint64_t* seg_off, uint32_t n_seg, const uint32_t* inc, int32_t* gain, uint32_t* cov,
+                          uint64_t* best, uint64_t* newcov, hipStream_t s) {
+  const unsigned ga = grid_for(n, kArgBlock, kArgGrid);
+  uint64_t* part = best + k;
+  const unsigned gc = 1024;
+  for (uint32_t r = r0; r < k; ++r) {
+    hipLaunchKernelGGL(k_argmax, dim3(ga), dim3(kArgBlock), 0, s, gain, n, part);
+    hipLaunchKernelGGL(k_cover, dim3(gc), dim3(kCoverBlock), 0, s, part, ga, best + r, seg_off, n_seg, inc, he_off,
+                       he_nodes, n, cov, gain, newcov + r);
+  }
 }
 
 // Launches greedy's k rounds on an incidence of n_seg segments (offsets
-// seg_off, entries inc (at most `entries`), degrees deg): gain u32[n], covered u32[m/32 + 1],
-// best u64[k + kArgGrid] and newcov u64[k] are the round state.  Launches
-// only.
+// seg_off, entries inc (at most `entries`), degrees deg): gain u32[n],
+// covered u32[m/32 + 1], best u64[k + kArgGrid] and newcov u64[k] are the
+// round state.  Launches only.
 static void greedy_kernels(uint32_t n, uint64_t m, const uint64_t* he_off, const uint32_t* he_nodes, uint32_t k,
                            const uint32_t* deg, const uint64_t* seg_off, uint32_t n_seg, const uint32_t* inc,
                            int32_t* gain, uint32_t* cov, uint64_t* best, uint64_t* newcov, uint32_t* picks,
@@ -893,19 +1289,52 @@ static void greedy_kernels(uint32_t n, uint64_t m, const uint64_t* he_off, const
     hipLaunchKernelGGL(k_greedy_solo, dim3(1), dim3(kSoloBlock), greedy_solo_lds(n, m), s, q);
     return;
   }
-  hipLaunchKernelGGL(k_gain_init, dim3(grid_for(n, 256)), dim3(256), 0, s, deg, n, gain);
-  fill_u32(cov, 0, (m + 31) / 32 + 1, s);
-  fill_u64(best, 0, k, s);
-  fill_u64(newcov, 0, k, s);
-  const unsigned ga = grid_for(n, kArgBlock, kArgGrid);
-  uint64_t* part = best + k;
-  const unsigned gc = 1024;
-  for (uint32_t r = 0; r < k; ++r) {
-    hipLaunchKernelGGL(k_argmax, dim3(ga), dim3(kArgBlock), 0, s, gain, n, part);
-    hipLaunchKernelGGL(k_cover, dim3(gc), dim3(kCoverBlock), 0, s, part, ga, best + r, seg_off, n_seg, inc, he_off,
-                       he_nodes, n, cov, gain, newcov + r);
+  greedy_start(n, m, k, deg, gain, cov, best, newcov, s);
+  greedy_rounds(0, n, he_off, he_nodes, k, seg_off, n_seg, inc, gain, cov, best, newcov, s);
+  hipLaunchKernelGGL(k_greedy_finish, dim3(1), dim3(kWave), 0, s, best, newcov, k, picks, cov_cum, n_picked);
+}
+
+// The same in batches, waiting for each; *ran is false if there is no room.
+static int greedy_batches(centra_ctx* ctx, BatchArgs a, uint64_t m, const uint32_t* deg, uint32_t* picks,
+                          uint64_t* cov_cum, uint32_t* n_picked, bool* ran, hipStream_t s) {
+  const size_t part_b = size_t(kTopCols + kTopBlocks) * 8, st_b = (sizeof(BatchState) + 255) & ~size_t(255);
+  *ran = false;
+  if (ensure(ctx, ctx->batch_ws, part_b + st_b + size_t(kBatchList) * 8 + m * 8, false, s)) {
+    ctx->err.clear();
+    return CENTRA_OK;
   }
-  hipLaunchKernelGGL(k_greedy_finish, dim3(1), dim3(64), 0, s, best, newcov, k, picks, cov_cum, n_picked);
+  *ran = true;
+  char* ws = static_cast<char*>(ctx->batch_ws.ptr);
+  a.part = reinterpret_cast<uint64_t*>(ws);
+  a.st = reinterpret_cast<BatchState*>(ws + part_b);
+  a.list = reinterpret_cast<uint64_t*>(ws + part_b + st_b);
+  a.mask = a.list + kBatchList;
+  greedy_start(a.n, m, a.k, deg, a.gain, a.covered, a.best, a.newcov, s);
+  fill_u32(reinterpret_cast<uint32_t*>(a.st), 0, 16, s);   // r and fail among them
+  fill_u64(a.mask, 0, m, s);
+  uint32_t r = 0;
+  while (r < a.k) {
+    hipLaunchKernelGGL(k_batch_top, dim3(kTopBlocks), dim3(kTopBlock), 0, s, a, r == 0 ? 1 : 0);
+    hipLaunchKernelGGL(k_batch_cands, dim3(1), dim3(kBatchBlock), 0, s, a);
+    hipLaunchKernelGGL(k_batch_mask, dim3(512), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_batch_list, dim3(512), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_batch_solve, dim3(1), dim3(kBatchBlock), 0, s, a);
+    hipLaunchKernelGGL(k_batch_cover, dim3(1024), dim3(kCoverBlock), 0, s, a);
+    uint32_t h[3];   // r, fail, done
+    CENTRA_HIP(ctx, hipMemcpyAsync(h, &a.st->r, sizeof(h), hipMemcpyDeviceToHost, s));
+    CENTRA_HIP(ctx, hipStreamSynchronize(s));
+    const bool little = h[0] - r < kBatchMinPicks;
+    r = h[0];
+    if (h[2]) break;   // no positive gain is left
+    if (h[1] || little) {
+      greedy_rounds(r, a.n, a.he_off, a.he_nodes, a.k, a.seg_off, a.n_seg, a.inc, a.gain, a.covered, a.best, a.newcov,
+                    s);
+      break;
+    }
+  }
+  hipLaunchKernelGGL(k_greedy_finish, dim3(1), dim3(kWave), 0, s, a.best, a.newcov, a.k, picks, cov_cum, n_picked);
+  CENTRA_HIP(ctx, hipGetLastError());
+  return CENTRA_OK;
 }
 
 int greedy_reserve(centra_ctx* ctx, uint32_t n, uint64_t m, uint32_t k, hipStream_t s) {
@@ -916,13 +1345,34 @@ int greedy_reserve(centra_ctx* ctx, uint32_t n, uint64_t m, uint32_t k, hipStrea
   return ensure(ctx, ctx->newcov, size_t(k) * 8, false, s);
 }
 
-int greedy_on_incidence(centra_ctx* ctx, uint32_t n, uint64_t m, const uint64_t* he_off, const uint32_t* he_nodes,
+int greedy_on_incidence(centra_ctx* ctx, bool waits, uint32_t n, uint64_t m, const uint64_t* he_off, const uint32_t* he_nodes,
                         uint32_t k, uint32_t* picks, uint64_t* cov_cum, uint32_t* n_picked, hipStream_t s) {
   int rc;
   if ((rc = ensure(ctx, ctx->gain, size_t(n) * 4, false, s))) return rc;
   if ((rc = ensure(ctx, ctx->covered, ((m + 31) / 32 + 1) * 4, false, s))) return rc;
   if ((rc = ensure(ctx, ctx->best, (size_t(k) + kArgGrid) * 8, false, s))) return rc;
   if ((rc = ensure(ctx, ctx->newcov, size_t(k) * 8, false, s))) return rc;
+  // In batches where the call may wait for them; not under a budget, whose
+  // memory other steps may need.
+  if (waits && !ctx->budget && k >= kBatchMinK && ctx->inc_nseg <= kBatchSegs &&
+      !greedy_solo(n, m, ctx->inc_limit, k)) {
+    BatchArgs a{};
+    a.n = n;
+    a.n_seg = ctx->inc_nseg;
+    a.k = k;
+    a.seg_off = static_cast<const uint64_t*>(ctx->inc_off.ptr);
+    a.inc = static_cast<const uint32_t*>(ctx->inc.ptr);
+    a.he_off = he_off;
+    a.he_nodes = he_nodes;
+    a.gain = static_cast<int32_t*>(ctx->gain.ptr);
+    a.covered = static_cast<uint32_t*>(ctx->covered.ptr);
+    a.best = static_cast<uint64_t*>(ctx->best.ptr);
+    a.newcov = static_cast<uint64_t*>(ctx->newcov.ptr);
+    bool ran;
+    if ((rc = greedy_batches(ctx, a, m, static_cast<const uint32_t*>(ctx->deg.ptr), picks, cov_cum, n_picked, &ran, s)))
+      return rc;
+    if (ran) return CENTRA_OK;
+  }
   greedy_kernels(n, m, he_off, he_nodes, k, static_cast<const uint32_t*>(ctx->deg.ptr),
                  static_cast<const uint64_t*>(ctx->inc_off.ptr), ctx->inc_nseg,
                  static_cast<const uint32_t*>(ctx->inc.ptr), static_cast<int32_t*>(ctx->gain.ptr),

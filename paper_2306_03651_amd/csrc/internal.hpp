@@ -51,6 +51,7 @@ struct centra_ctx {
   centra::DevBuf scan_tmp;
   // incidence (node -> samples) and greedy / AMCERA workspaces
   centra::DevBuf deg, inc_off, inc_cursor, inc, inc_node, gain, covered, best, newcov, seg_deg;
+  centra::DevBuf batch_ws;            // greedy in batches: candidates, masks
   centra::DevBuf inc_ws;              // workspace of the bucketed incidence build
   uint32_t inc_nseg = 0;              // incidence segments held in inc_off / inc / inc_node
   uint64_t inc_m0 = 0;                // first sample of the newest segment (0: it holds every sample)
@@ -225,7 +226,8 @@ constexpr uint32_t kMaxSegments = 64;
 // ~0 reads the exact size.
 int build_incidence(centra_ctx* ctx, uint32_t n, uint64_t m0, uint64_t m1, const uint64_t* he_off,
                     const uint32_t* he_nodes, hipStream_t s, uint64_t entry_cap = ~0ull);
-int greedy_on_incidence(centra_ctx* ctx, uint32_t n, uint64_t m, const uint64_t* he_off,
+// waits: the caller waits for the stream anyway, so this may do so too.
+int greedy_on_incidence(centra_ctx* ctx, bool waits, uint32_t n, uint64_t m, const uint64_t* he_off,
                         const uint32_t* he_nodes, uint32_t k, uint32_t* picks, uint64_t* cov_cum,
                         uint32_t* n_picked, hipStream_t s);
 
