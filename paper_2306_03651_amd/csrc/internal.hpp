@@ -79,7 +79,7 @@ struct centra_ctx {
   const centra_graph* prog_g = nullptr;
   uint64_t prog_ghash = 0, prog_phash = 0, prog_m = 0, prog_entries = 0, prog_inc_gen = 0, prog_words_gen = 0;
   uint32_t prog_i = 0;
-  centra::DevBuf words, P, Rtm, topk_tmp, misc, sel_rows;
+  centra::DevBuf words, P, topk_tmp, misc;
   // sample store of centra_progressive
   centra::DevBuf store_off, store_nodes;
   centra::DevBuf kp_len;     // kappa-path walk lengths

@@ -10,7 +10,9 @@
 // samples of u's incidence row whose bit j is set.  A wave walks a span of
 // the incidence (grouped by node), lane j counting trial j (k_rade_count).
 //
-// Top-k.  For every trial row (plus one row of degrees) the k-th largest
+// Top-k.  The t columns of R and the column of degrees are selected over the
+// node-major P itself (columns_topk), or, for the engine, which keeps R by
+// trial, over rows (select_topk_rows): for every row the k-th largest
 // positive value is found by MSD radix selection: a histogram over the bit
 // length, then 10-bit digit histograms below the leading bit, each with
 // per-bin counts and sums; the answer is the sum of every value above the
@@ -144,20 +146,24 @@ __global__ __launch_bounds__(kCountBlock) void k_rade_count(const uint32_t* inc,
   if (live && acc) atomicAdd(&P[uint64_t(cur) * t + jt], static_cast<int32_t>(acc));
 }
 
-// R[j][u] = 2 P[u][j] - deg[u] (trial-major for the selection) and, if
-// requested, R_out[u][j] (node-major).  64 x 64 tiles through LDS.
+// R[u][j] = 2 P[u][j] - deg[u].
+__global__ void k_rade_rows(const int32_t* P, const uint32_t* deg, uint32_t n, uint32_t t, int32_t* R) {
+  const uint64_t total = uint64_t(n) * t;
+  for (uint64_t i = blockIdx.x * uint64_t(blockDim.x) + threadIdx.x; i < total; i += uint64_t(gridDim.x) * blockDim.x)
+    R[i] = 2 * P[i] - static_cast<int32_t>(deg[i / t]);
+}
+
+// R[j][u] = 2 P[u][j] - deg[u] (trial-major, for the selection over rows).
+// 64 x 64 tiles through LDS.
 __global__ __launch_bounds__(256) void k_rade_finish(const int32_t* P, const uint32_t* deg, uint32_t n, uint32_t t,
-                                                     int32_t* Rtm, int32_t* R_out) {
+                                                     int32_t* Rtm) {
   __shared__ int32_t tile[64][65];
   const uint32_t u0 = blockIdx.x * 64, j0 = blockIdx.y * 64;
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;   // 64 x 4
   for (int r = ty; r < 64; r += 4) {
     const uint32_t u = u0 + r, j = j0 + tx;
     int32_t v = 0;
-    if (u < n && j < t) {
-      v = 2 * P[uint64_t(u) * t + j] - static_cast<int32_t>(deg[u]);
-      if (R_out) R_out[uint64_t(u) * t + j] = v;
-    }
+    if (u < n && j < t) v = 2 * P[uint64_t(u) * t + j] - static_cast<int32_t>(deg[u]);
     tile[r][tx] = v;
   }
   __syncthreads();
@@ -486,8 +492,7 @@ void rade_count_launch(const uint32_t* inc, const uint32_t* inc_node, const uint
 }
 
 void rade_finish_launch(const int32_t* P, const uint32_t* deg, uint32_t n, uint32_t t, int32_t* Rtm, hipStream_t s) {
-  hipLaunchKernelGGL(k_rade_finish, dim3((n + 63) / 64, (t + 63) / 64), dim3(256), 0, s, P, deg, n, t, Rtm,
-                     static_cast<int32_t*>(nullptr));
+  hipLaunchKernelGGL(k_rade_finish, dim3((n + 63) / 64, (t + 63) / 64), dim3(256), 0, s, P, deg, n, t, Rtm);
 }
 
 void bmax_launch(const uint64_t* he_off, uint64_t m0, uint64_t m1, uint32_t* b_max, hipStream_t s) {
@@ -496,24 +501,353 @@ void bmax_launch(const uint64_t* he_off, uint64_t m0, uint64_t m1, uint32_t* b_m
                        b_max);
 }
 
+// ---------------------------------------------------------------------------
+// Sums of the k largest positive values of the t columns of R = 2 P - deg and
+// of the column of degrees, without R: a lane reads its trial's column of the
+// node-major P.  The k-th largest value of a column is narrowed down to a
+// range [lo, lo + 2^w): first by bins of 8 to the octave (values below 16 have
+// bins of their own), then by 256 bins of the range a pass, then the values
+// above it are summed.  R[u][j] <= deg[u], so a pass reads only the rows of
+// nodes whose degree reaches some open range of its 64 trials: mostly the
+// first pass is the only one over all of P, and it is bound by reading it.
+// Each workgroup has its own counts in LDS and writes them out; a workgroup
+// per column adds them up.  n = 10^6, t = 64 (k = 50): 377 us with R written by
+// trial and selected by rows, 215 so.
+constexpr int kColBlock = 1024;
+constexpr uint32_t kColParts = 256;   // workgroups of a pass over 64 trials
+constexpr uint32_t kColBins = 256;
+constexpr uint64_t kColFloors = 32u << 20;      // values (of P) from which floors pay
+constexpr uint32_t kColSmall = 36u << 10;   // nodes whose column one workgroup holds in LDS
+constexpr uint32_t kColPad = kWave + 1;   // LDS words from one bin to the next
+constexpr size_t kColLds = size_t(kColBins) * (kColPad + 1) * 4;
+
+struct ColState {
+  uint32_t lo, w, need, done;   // done: the sum takes the values above lo and `need` copies of lo
+};
+
+struct ColArgs {
+  const int32_t* P;
+  const uint32_t* deg;
+  uint32_t n, t, k, parts;
+  ColState* st;      // [t + 1], the degrees last
+  uint32_t* cnt;     // [t + 1][parts][kColBins]
+  uint64_t* sum;     // [t + 1][parts]
+  int64_t* topk_sum;
+  int64_t* deg_topk;
+};
+
+// 8 bins per octave (as the greedy's gain_bin), and the values of a bin:
+// [lo, lo + 2^w).
+__device__ __forceinline__ uint32_t col_bin(uint32_t x) {
+  const uint32_t bl = 32u - __clz(x);
+  return (bl - 1) * 8 + (bl >= 4 ? (x >> (bl - 4)) & 7u : (x << (4 - bl)) & 7u);
+}
+__device__ __forceinline__ void col_range(uint32_t bin, uint32_t* lo, uint32_t* w) {
+  const uint32_t bl = bin / 8 + 1, sub = bin % 8;
+  *w = bl >= 4 ? bl - 4 : 0u;
+  *lo = bl >= 4 ? (8u + sub) << (bl - 4) : (8u + sub) >> (4 - bl);
+}
+
+// Calls row(u, deg[u]) for the nodes of the wave's share with degree above
+// `above` (kRows rows under way at once), deg(d) with every lane's degrees.
+template <typename Deg, typename Row>
+__device__ __forceinline__ void col_nodes(const ColArgs& a, uint32_t above, const Deg& deg, const Row& row) {
+  const uint64_t stride = uint64_t(gridDim.x) * kColBlock;
+  for (uint64_t u0 = uint64_t(blockIdx.x) * kColBlock + (threadIdx.x & ~63u); u0 < a.n; u0 += stride) {
+    const uint64_t u = u0 + lane_id();
+    const uint32_t d = u < a.n ? a.deg[u] : 0u;
+    deg(d);
+    constexpr int kRows = 8;
+    for (uint64_t m = __ballot(d > above); m;) {
+      uint32_t at[kRows];
+      int cnt = 0;
+#pragma unroll
+      for (int i = 0; i < kRows; ++i) {
+        at[i] = m ? static_cast<uint32_t>(__ffsll(static_cast<unsigned long long>(m)) - 1) : 0u;
+        cnt += m ? 1 : 0;
+        m &= m - 1;
+      }
+      int32_t p[kRows];
+#pragma unroll
+      for (int i = 0; i < kRows; ++i) p[i] = i < cnt ? row.load(u0 + at[i]) : 0;
+#pragma unroll
+      for (int i = 0; i < kRows; ++i)
+        if (i < cnt) row.use(2 * p[i] - static_cast<int32_t>(lane_u32(d, static_cast<int>(at[i]))));
+    }
+  }
+}
+
+// A lane's column of P and what becomes of its values.
+template <typename F>
+struct ColRow {
+  const int32_t* P;
+  uint32_t t, j;
+  const F& f;
+  __device__ __forceinline__ int32_t load(uint64_t u) const { return j < t ? P[u * t + j] : 0; }
+  __device__ __forceinline__ void use(int32_t x) const {
+    if (j < t && x > 0) f(static_cast<uint32_t>(x));
+  }
+};
+
+// One counting pass for the trials 64 g .. 64 g + 63 of group g = blockIdx.y
+// (and, in group 0, the degrees).
+// pass 0: all values above the columns' floors; < 0: those of nodes of at least
+// `some` entries, for the floors; > 0: those in the open ranges.
+__global__ __launch_bounds__(kColBlock) void k_col_count(ColArgs a, int pass, uint32_t some) {
+  extern __shared__ uint32_t col_lds[];
+  uint32_t* hist = col_lds;                        // [bin][kColPad]
+  uint32_t* dhist = col_lds + kColBins * kColPad;  // [bin]
+  const uint32_t g = blockIdx.y, j = 64 * g + lane_id();
+  const bool live = j < a.t, degs = g == 0;
+  const ColState s = live ? a.st[j] : ColState{0, 0, 0, 1}, sd = degs ? a.st[a.t] : ColState{0, 0, 0, 1};
+  if (__ballot(!s.done) == 0 && sd.done) return;   // uniform: every wave holds the same columns
+  for (uint32_t i = threadIdx.x; i < kColBins * (kColPad + 1); i += kColBlock) col_lds[i] = 0;
+  // a node below every open range is of no use
+  const bool first = pass <= 0;
+  uint32_t above = s.done ? 0xFFFFFFFFu : s.lo ? s.lo - 1 : 0u;
+  if (pass < 0) above = some - 1;
+  for (int o = 32; o; o >>= 1) above = min(above, static_cast<uint32_t>(__shfl_xor(static_cast<int>(above), o, kWave)));
+  __syncthreads();
+  const uint32_t lane = lane_id();
+  const uint32_t shift = s.w > 8 ? s.w - 8 : 0u, dshift = sd.w > 8 ? sd.w - 8 : 0u;
+  const auto count = [&](uint32_t x) {
+    if (first)
+      atomicAdd(&hist[col_bin(x) * kColPad + lane], 1u);
+    else if (!s.done && x >= s.lo && (x - s.lo) >> s.w == 0)
+      atomicAdd(&hist[((x - s.lo) >> shift) * kColPad + lane], 1u);
+  };
+  col_nodes(
+      a, above,
+      [&](uint32_t d) {
+        if (!degs || d == 0) return;
+        if (pass < 0 && d < some) return;
+        if (first)
+          atomicAdd(&dhist[col_bin(d)], 1u);
+        else if (!sd.done && d >= sd.lo && (d - sd.lo) >> sd.w == 0)
+          atomicAdd(&dhist[(d - sd.lo) >> dshift], 1u);
+      },
+      ColRow<decltype(count)>{a.P, a.t, j, count});
+  __syncthreads();
+  const uint32_t cols = a.t - 64 * g < 64 ? a.t - 64 * g : 64u;
+  for (uint32_t i = threadIdx.x; i < cols * kColBins; i += kColBlock)
+    a.cnt[(size_t(64 * g + i / kColBins) * a.parts + blockIdx.x) * kColBins + i % kColBins] =
+        hist[(i % kColBins) * kColPad + i / kColBins];
+  if (degs && threadIdx.x < kColBins)
+    a.cnt[(size_t(a.t) * a.parts + blockIdx.x) * kColBins + threadIdx.x] = dhist[threadIdx.x];
+}
+
+// Narrows s by a pass's counts (one wave; cnt(bin) in any lane).  floor_only:
+// the counts are of some of the column's values only, so the bin found bounds
+// the k-th largest from below.
+template <typename Cnt>
+__device__ __forceinline__ void col_narrow(ColState& s, bool first, bool floor_only, const Cnt& cnt) {
+  // lane l takes the bins 255 - 4 l, ..., 252 - 4 l: from the top
+  constexpr uint32_t kOwn = kColBins / kWave;
+  const uint32_t lane = lane_id();
+  uint32_t h[kOwn], mine = 0;
+#pragma unroll
+  for (uint32_t i = 0; i < kOwn; ++i) {
+    h[i] = cnt(kColBins - 1 - (lane * kOwn + i));
+    mine += h[i];
+  }
+  uint32_t run = wave_incl_scan_u32(mine) - mine;
+  const uint64_t hit = __ballot(run < s.need && s.need <= run + mine);
+  if (!hit) {   // (the first pass) fewer than k positive values: all of them count
+    if (!floor_only) s = ColState{0, 0, 0, 1};
+    return;
+  }
+  uint32_t i = 0;
+  while (i + 1 < kOwn && run + h[i] < s.need) run += h[i++];
+  const int at = __ffsll(static_cast<unsigned long long>(hit)) - 1;
+  const uint32_t b = lane_u32(kColBins - 1 - (lane * kOwn + i), at);
+  run = lane_u32(run, at);
+  if (floor_only) {
+    uint32_t w;
+    col_range(b, &s.lo, &w);
+    return;
+  }
+  s.need -= run;
+  if (first) {
+    col_range(b, &s.lo, &s.w);
+  } else {
+    const uint32_t shift = s.w > 8 ? s.w - 8 : 0u;
+    s.lo += b << shift;
+    s.w = shift;
+  }
+  s.done = s.w == 0 ? 1u : 0u;
+}
+
+// Narrows column blockIdx.x's range by the pass's counts.
+__global__ __launch_bounds__(kColBlock) void k_col_decide(ColArgs a, int pass) {
+  __shared__ uint32_t part[kColBlock / kColBins][kColBins];
+  const uint32_t c = blockIdx.x, bin = threadIdx.x % kColBins, q = threadIdx.x / kColBins;
+  ColState s = a.st[c];
+  if (s.done) return;
+  uint32_t sum = 0;
+  for (uint32_t p = q; p < a.parts; p += kColBlock / kColBins) sum += a.cnt[(size_t(c) * a.parts + p) * kColBins + bin];
+  part[q][bin] = sum;
+  __syncthreads();
+  if (threadIdx.x >= kWave) return;
+  col_narrow(s, pass == 0, pass < 0, [&](uint32_t b) {
+    uint32_t x = 0;
+    for (uint32_t i = 0; i < kColBlock / kColBins; ++i) x += part[i][b];
+    return x;
+  });
+  if (threadIdx.x == 0) a.st[c] = s;
+}
+
+// The same for a column that fits in LDS: one workgroup per column reads it
+// once.  (n = 2,000, t = 10: 57 us with R written by trial and selected by
+// rows, ten launches, 4.5 so; n = 20,011, t = 32: 60, 27.)
+__global__ __launch_bounds__(kColBlock) void k_col_small(ColArgs a) {
+  extern __shared__ uint32_t col_lds[];   // the column's positive values, 0 for the others
+  __shared__ uint32_t hist[kColBins];
+  __shared__ uint64_t red[kColBlock / kWave];
+  __shared__ ColState shared;
+  const uint32_t c = blockIdx.x;
+  ColState s{0, 0, a.k, 0};
+  if (threadIdx.x < kColBins) hist[threadIdx.x] = 0;
+  __syncthreads();
+  for (uint32_t u = threadIdx.x; u < a.n; u += kColBlock) {
+    const int32_t d = static_cast<int32_t>(a.deg[u]);
+    const int32_t x = c < a.t ? 2 * a.P[uint64_t(u) * a.t + c] - d : d;
+    col_lds[u] = x > 0 ? static_cast<uint32_t>(x) : 0u;
+    if (x > 0) atomicAdd(&hist[col_bin(static_cast<uint32_t>(x))], 1u);
+  }
+  for (bool first = true;; first = false) {
+    __syncthreads();
+    if (threadIdx.x < kWave) {
+      col_narrow(s, first, false, [&](uint32_t b) { return hist[b]; });
+      if (threadIdx.x == 0) shared = s;
+    }
+    __syncthreads();
+    s = shared;
+    if (s.done) break;
+    if (threadIdx.x < kColBins) hist[threadIdx.x] = 0;
+    __syncthreads();
+    const uint32_t shift = s.w > 8 ? s.w - 8 : 0u;
+    for (uint32_t u = threadIdx.x; u < a.n; u += kColBlock) {
+      const uint32_t x = col_lds[u];
+      if (x >= s.lo && (x - s.lo) >> s.w == 0) atomicAdd(&hist[(x - s.lo) >> shift], 1u);   // (s.lo >= 16)
+    }
+  }
+  uint64_t sum = 0;
+  for (uint32_t u = threadIdx.x; u < a.n; u += kColBlock) sum += col_lds[u] > s.lo ? col_lds[u] : 0u;
+  sum = block_sum_u64<kColBlock>(sum, red);
+  if (threadIdx.x) return;
+  const int64_t r = static_cast<int64_t>(sum + uint64_t(s.need) * s.lo);
+  if (c < a.t)
+    a.topk_sum[c] = r;
+  else
+    *a.deg_topk = r;
+}
+
+// Sums of the values above lo.
+__global__ __launch_bounds__(kColBlock) void k_col_sum(ColArgs a) {
+  __shared__ unsigned long long sum[kWave], dsum;
+  const uint32_t g = blockIdx.y, j = 64 * g + lane_id();
+  const bool live = j < a.t, degs = g == 0;
+  const uint32_t lo = live ? a.st[j].lo : 0xFFFFFFFFu, dlo = degs ? a.st[a.t].lo : 0xFFFFFFFFu;
+  uint32_t above = lo;
+  for (int o = 32; o; o >>= 1) above = min(above, static_cast<uint32_t>(__shfl_xor(static_cast<int>(above), o, kWave)));
+  if (threadIdx.x < kWave) sum[threadIdx.x] = 0;
+  if (threadIdx.x == 0) dsum = 0;
+  __syncthreads();
+  uint64_t acc = 0, dacc = 0;
+  const auto add = [&](uint32_t x) { acc += x > lo ? x : 0u; };
+  col_nodes(a, above, [&](uint32_t d) { dacc += d > dlo ? d : 0u; }, ColRow<decltype(add)>{a.P, a.t, j, add});
+  if (acc) atomicAdd(&sum[lane_id()], static_cast<unsigned long long>(acc));
+  if (dacc) atomicAdd(&dsum, static_cast<unsigned long long>(dacc));
+  __syncthreads();
+  if (threadIdx.x < kWave && live) a.sum[size_t(j) * a.parts + blockIdx.x] = sum[threadIdx.x];
+  if (threadIdx.x == 0 && degs) a.sum[size_t(a.t) * a.parts + blockIdx.x] = dsum;
+}
+
+__global__ __launch_bounds__(kWave) void k_col_out(ColArgs a) {
+  const uint32_t c = blockIdx.x;
+  uint64_t sum = 0;
+  for (uint32_t p = threadIdx.x; p < a.parts; p += kWave) sum += a.sum[size_t(c) * a.parts + p];
+  sum = wave_sum_u64(sum);
+  if (threadIdx.x) return;
+  const ColState s = a.st[c];
+  const int64_t r = static_cast<int64_t>(sum + uint64_t(s.need) * s.lo);
+  if (c < a.t)
+    a.topk_sum[c] = r;
+  else
+    *a.deg_topk = r;
+}
+
+__global__ void k_col_init(ColArgs a) {
+  const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
+  if (c <= a.t) a.st[c] = ColState{0, 0, a.k, 0};
+}
+
+static uint32_t col_parts(uint32_t n, uint32_t t) {
+  const uint32_t groups = (t + 63) / 64, most = kColParts / groups ? kColParts / groups : 1u;
+  const uint32_t want = (n + kColBlock - 1) / kColBlock;
+  return want < most ? want : most;
+}
+
+static size_t col_ws_bytes(uint32_t n, uint32_t t) {
+  return size_t(t + 1) * (sizeof(ColState) + size_t(col_parts(n, t)) * (kColBins * 4 + 8));
+}
+
+// max_value: a bound on the degrees.
+static void columns_topk(const int32_t* P, const uint32_t* deg, uint32_t n, uint32_t t, uint32_t k, uint64_t max_value,
+                         void* ws, int64_t* topk_sum, int64_t* deg_topk, hipStream_t s) {
+  ColArgs a{};
+  a.P = P;
+  a.deg = deg;
+  a.n = n;
+  a.t = t;
+  a.k = k;
+  a.parts = col_parts(n, t);
+  a.sum = static_cast<uint64_t*>(ws);
+  a.st = reinterpret_cast<ColState*>(a.sum + size_t(t + 1) * a.parts);
+  a.cnt = reinterpret_cast<uint32_t*>(a.st + (t + 1));
+  a.topk_sum = topk_sum;
+  a.deg_topk = deg_topk;
+  const dim3 grid(a.parts, (t + 63) / 64), block(kColBlock);
+  if (n <= kColSmall) {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_col_small), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              static_cast<int>(kColSmall * 4));
+    hipLaunchKernelGGL(k_col_small, dim3(t + 1), block, size_t(n) * 4, s, a);
+    return;
+  }
+  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_col_count), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            static_cast<int>(kColLds));
+  hipLaunchKernelGGL(k_col_init, dim3((t + 256) / 256), dim3(256), 0, s, a);
+  // Floors for the columns' k-th values from the nodes of several times the
+  // mean degree, which on skewed samples rule most rows out of the first pass.
+  // They cost a pass over the degrees and two launches, 25 us, and spare up to
+  // the reading of P (n = 10^6, t = 64: 735 us for the whole call without, 677
+  // with; n = 10^5: 5 us more).
+  if (uint64_t(n) * t >= kColFloors) {
+    const uint64_t mean = max_value / n;
+    const uint32_t some = mean < (1u << 26) ? static_cast<uint32_t>(4 * mean + 8) : 1u << 28;
+    hipLaunchKernelGGL(k_col_count, grid, block, kColLds, s, a, -1, some);
+    hipLaunchKernelGGL(k_col_decide, dim3(t + 1), block, 0, s, a, -1);
+  }
+  // the first pass leaves ranges of at most 2^(bits - 4) values, each further
+  // one 2^8 times less
+  int bits = 0;
+  while (bits < 31 && max_value >> bits) ++bits;
+  for (int left = bits > 4 ? bits - 4 : 0, pass = 0; pass == 0 || left > 0; ++pass) {
+    hipLaunchKernelGGL(k_col_count, grid, block, kColLds, s, a, pass, 0u);
+    hipLaunchKernelGGL(k_col_decide, dim3(t + 1), block, 0, s, a, pass);
+    if (pass) left -= 8;
+  }
+  hipLaunchKernelGGL(k_col_sum, grid, block, 0, s, a);
+  hipLaunchKernelGGL(k_col_out, dim3(t + 1), dim3(kWave), 0, s, a);
+}
+
 int mcera_reserve(centra_ctx* ctx, uint32_t n, uint64_t m, uint32_t t, hipStream_t s) {
   const uint32_t Wt = (t + 63) / 64;
   int rc;
   if ((rc = ensure(ctx, ctx->words, size_t(m) * Wt * 8, true, s))) return rc;
   if ((rc = ensure(ctx, ctx->P, size_t(n) * t * 4, true, s))) return rc;
-  if ((rc = ensure(ctx, ctx->Rtm, size_t(n) * t * 4, false, s))) return rc;
-  if ((rc = ensure(ctx, ctx->topk_tmp, select_ws_bytes(t + 1), false, s))) return rc;
-  if ((rc = ensure(ctx, ctx->sel_rows, size_t(t + 1) * sizeof(SelRow), false, s))) return rc;
+  if ((rc = ensure(ctx, ctx->topk_tmp, col_ws_bytes(n, t), false, s))) return rc;
   return ensure(ctx, ctx->ext_bmax, 256, true, s);
-}
-
-// The selection rows of the AMCERA: trial j's row of Rtm, then the degree
-// row (built on the device, so that no host buffer has to outlive the call).
-__global__ void k_mcera_rows(SelRow* rows, const int32_t* Rtm, const int32_t* deg, uint32_t n, uint32_t t, uint32_t k,
-                             int64_t* topk_sum, int64_t* deg_topk) {
-  const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j > t) return;
-  rows[j] = j < t ? SelRow{Rtm + size_t(j) * n, n, k, topk_sum + j} : SelRow{deg, n, k, deg_topk};
 }
 
 int mcera_on_incidence(centra_ctx* ctx, uint32_t n, uint64_t m, uint64_t m0, const uint64_t* he_off, uint32_t t,
@@ -524,22 +858,15 @@ int mcera_on_incidence(centra_ctx* ctx, uint32_t n, uint64_t m, uint64_t m0, con
   const uint64_t span_cap = m0 == ctx->inc_m0 ? ctx->inc_span_cap : ctx->inc_limit;
   int rc;
   if ((rc = ensure(ctx, ctx->P, size_t(n) * t * 4, m0 > 0, s))) return rc;
-  if ((rc = ensure(ctx, ctx->Rtm, size_t(n) * t * 4, false, s))) return rc;
-  const uint32_t rows = t + 1;
-  if ((rc = ensure(ctx, ctx->topk_tmp, select_ws_bytes(rows), false, s))) return rc;
-  if ((rc = ensure(ctx, ctx->sel_rows, size_t(rows) * sizeof(SelRow), false, s))) return rc;
+  if ((rc = ensure(ctx, ctx->topk_tmp, col_ws_bytes(n, t), false, s))) return rc;
   int32_t* P = static_cast<int32_t*>(ctx->P.ptr);
-  int32_t* Rtm = static_cast<int32_t*>(ctx->Rtm.ptr);
+  const uint32_t* deg = static_cast<const uint32_t*>(ctx->deg.ptr);
   if (m0 == 0) fill_u32(reinterpret_cast<uint32_t*>(P), 0, size_t(n) * t, s);
   rade_count_launch(static_cast<const uint32_t*>(ctx->inc.ptr), static_cast<const uint32_t*>(ctx->inc_node.ptr), he_off,
                     m0, m, span_cap, ctx->inc_limit, static_cast<const uint64_t*>(ctx->words.ptr), t, P, s);
-  hipLaunchKernelGGL(k_rade_finish, dim3((n + 63) / 64, (t + 63) / 64), dim3(256), 0, s, P,
-                     static_cast<const uint32_t*>(ctx->deg.ptr), n, t, Rtm, R_out);
-  // selection over the t trial rows and the degree row
-  SelRow* drows = static_cast<SelRow*>(ctx->sel_rows.ptr);
-  hipLaunchKernelGGL(k_mcera_rows, dim3((rows + 255) / 256), dim3(256), 0, s, drows, Rtm,
-                     static_cast<const int32_t*>(ctx->deg.ptr), n, t, k, topk_sum, reinterpret_cast<int64_t*>(deg_topk));
-  select_topk_rows(drows, rows, n, ctx->topk_tmp.ptr, s);
+  if (R_out)
+    hipLaunchKernelGGL(k_rade_rows, dim3(grid_for(uint64_t(n) * t, 256)), dim3(256), 0, s, P, deg, n, t, R_out);
+  columns_topk(P, deg, n, t, k, ctx->inc_limit, ctx->topk_tmp.ptr, topk_sum, reinterpret_cast<int64_t*>(deg_topk), s);
   if (m0 == 0) fill_u32(b_max, 0, 1, s);
   if (m > m0)
     hipLaunchKernelGGL(k_bmax, dim3(grid_for(m - m0, kBmaxBlock, 512)), dim3(kBmaxBlock), 0, s, he_off + m0, m - m0,
