@@ -11,7 +11,7 @@
 //      place in a bucket-ordered scratch array;
 //   2. the same workgroups visit the same samples in the same order and
 //      write each entry, (node, sample) in 8 bytes, to its bucket's run;
-//   3. buckets are cut into items of at most kItem entries; per item, the
+//   3. buckets are cut into items of some 1,000 to 16,000 entries; per item, the
 //      nodes' counts in LDS (a node's slot is its id within the bucket);
 //      one global add per node present adds them to the segment degrees
 //      (a bucket of one item has one add per node); a scan of the degrees
@@ -36,6 +36,8 @@ constexpr uint32_t kPartBlock = 256;
 constexpr uint32_t kPartGrid = 512;        // workgroups of passes 1 and 2
 constexpr uint32_t kItemBlock = 256;
 constexpr uint32_t kItem = 16384;          // entries per item (at most)
+constexpr uint32_t kItemLeast = 1024;
+constexpr uint32_t kItemsWanted = 192;     // items to spread over the device
 constexpr uint32_t kItemGrid = 2048;
 
 unsigned grid_of(uint64_t n, unsigned block, unsigned cap = 65535) {
@@ -118,17 +120,17 @@ __global__ __launch_bounds__(kPartBlock) void k_inc_partition(const uint64_t* he
   }
 }
 
-// Items of each bucket: nitems[b] = ceil(entries of bucket b / kItem).
-__global__ void k_inc_items(const uint64_t* pos, uint32_t n_buckets, uint32_t* nitems) {
+// Items of each bucket: nitems[b] = ceil(entries of bucket b / item).
+__global__ void k_inc_items(const uint64_t* pos, uint32_t n_buckets, uint32_t item, uint32_t* nitems) {
   const uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b >= n_buckets) return;
   const uint64_t sz = pos[size_t(b + 1) * kPartGrid] - pos[size_t(b) * kPartGrid];
-  nitems[b] = static_cast<uint32_t>((sz + kItem - 1) / kItem);
+  nitems[b] = static_cast<uint32_t>((sz + item - 1) / item);
 }
 
 // Item q: its bucket (the last b with item_off[b] <= q) and entry range.
 __device__ __forceinline__ void item_range(const uint64_t* item_off, uint32_t n_buckets, const uint64_t* pos,
-                                           uint64_t q, uint32_t* bucket, uint64_t* e0, uint64_t* e1) {
+                                           uint32_t item, uint64_t q, uint32_t* bucket, uint64_t* e0, uint64_t* e1) {
   uint32_t lo = 0, hi = n_buckets - 1;
   while (lo < hi) {
     const uint32_t mid = (lo + hi + 1) >> 1;
@@ -139,8 +141,8 @@ __device__ __forceinline__ void item_range(const uint64_t* item_off, uint32_t n_
   }
   const uint64_t bs = pos[size_t(lo) * kPartGrid], be = pos[size_t(lo + 1) * kPartGrid];
   *bucket = lo;
-  *e0 = bs + (q - item_off[lo]) * kItem;
-  *e1 = *e0 + kItem < be ? *e0 + kItem : be;
+  *e0 = bs + (q - item_off[lo]) * item;
+  *e1 = *e0 + item < be ? *e0 + item : be;
 }
 
 // Passes 3 (PLACE = false) and 4 (PLACE = true) over the items, grid
@@ -152,7 +154,7 @@ __device__ __forceinline__ void item_range(const uint64_t* item_off, uint32_t n_
 template <bool PLACE>
 __global__ __launch_bounds__(kItemBlock) void k_inc_items_pass(const uint64_t* tmp, const uint64_t* pos,
                                                                const uint64_t* item_off, uint32_t n_buckets,
-                                                               uint32_t* sdeg, uint64_t* cur, uint32_t* inc,
+                                                               uint32_t item, uint32_t* sdeg, uint64_t* cur, uint32_t* inc,
                                                                uint32_t* inc_node, uint64_t limit, uint32_t* flags) {
   __shared__ uint32_t cnt[kBucketNodes];
   __shared__ unsigned long long base[PLACE ? kBucketNodes : 1];
@@ -160,7 +162,7 @@ __global__ __launch_bounds__(kItemBlock) void k_inc_items_pass(const uint64_t* t
   for (uint64_t q = blockIdx.x; q < items; q += gridDim.x) {
     uint32_t bucket;
     uint64_t e0, e1;
-    item_range(item_off, n_buckets, pos, q, &bucket, &e0, &e1);
+    item_range(item_off, n_buckets, pos, item, q, &bucket, &e0, &e1);
     const uint32_t node0 = bucket << kBucketLog;
     for (uint32_t i = threadIdx.x; i < kBucketNodes; i += kItemBlock) cnt[i] = 0;
     __syncthreads();
@@ -269,6 +271,12 @@ void incidence_segment_bucketed(uint32_t n, uint64_t m0, uint64_t m1, uint64_t s
   if (first_segment) fill_u32(deg, 0, n, s);
   fill_u32(sdeg, 0, n, s);
   const bool any = m1 > m0 && span_cap;
+  // items small enough for the device to have some hundreds (with 16,384
+  // entries each, the 45,000 of 10,000 samples were three workgroups' work: 56
+  // us for passes 3 and 4, 12 with 1,024; 4M entries: 90 us with 16,384, 125 with
+  // 8,192, whose nodes are reserved for twice as often)
+  uint32_t item = kItem;
+  while (item > kItemLeast && span_cap / item < kItemsWanted) item >>= 1;
   if (any) {
     hipLaunchKernelGGL(k_inc_bucket_count, dim3(kPartGrid), dim3(kPartBlock), size_t(B) * 4, s, he_off, he_nodes, m0,
                        m1, n, limit, span_cap, B, w.cnt, flags);
@@ -276,11 +284,11 @@ void incidence_segment_bucketed(uint32_t n, uint64_t m0, uint64_t m1, uint64_t s
     hipLaunchKernelGGL(k_inc_partition, dim3(kPartGrid), dim3(kPartBlock), size_t(B) * 8, s, he_off, he_nodes, m0, m1,
                        n, limit, span_cap, B, static_cast<const uint64_t*>(w.pos), w.tmp, span_cap, flags);
     hipLaunchKernelGGL(k_inc_items, dim3(grid_of(B, 256)), dim3(256), 0, s, static_cast<const uint64_t*>(w.pos), B,
-                       w.nitems);
+                       item, w.nitems);
     excl_scan_u32_to_u64_ws(w.nitems, w.item_off, B, w.tiles, s);
     hipLaunchKernelGGL(k_inc_items_pass<false>, dim3(kItemGrid), dim3(kItemBlock), 0, s,
                        static_cast<const uint64_t*>(w.tmp), static_cast<const uint64_t*>(w.pos),
-                       static_cast<const uint64_t*>(w.item_off), B, sdeg, static_cast<uint64_t*>(nullptr),
+                       static_cast<const uint64_t*>(w.item_off), B, item, sdeg, static_cast<uint64_t*>(nullptr),
                        static_cast<uint32_t*>(nullptr), static_cast<uint32_t*>(nullptr), limit, flags);
   }
   excl_scan_u32_to_u64_ws(sdeg, off, n, w.tiles, s);
@@ -292,7 +300,7 @@ void incidence_segment_bucketed(uint32_t n, uint64_t m0, uint64_t m1, uint64_t s
   if (any)
     hipLaunchKernelGGL(k_inc_items_pass<true>, dim3(kItemGrid), dim3(kItemBlock), 0, s,
                        static_cast<const uint64_t*>(w.tmp), static_cast<const uint64_t*>(w.pos),
-                       static_cast<const uint64_t*>(w.item_off), B, static_cast<uint32_t*>(nullptr), cur, inc,
+                       static_cast<const uint64_t*>(w.item_off), B, item, static_cast<uint32_t*>(nullptr), cur, inc,
                        inc_node, limit, flags);
   hipLaunchKernelGGL(k_inc_add, dim3(grid_of(n, 256)), dim3(256), 0, s, static_cast<const uint32_t*>(sdeg), n, deg);
 }
