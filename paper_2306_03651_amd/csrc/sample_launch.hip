@@ -54,14 +54,18 @@ size_t slot_mem_cap(centra_ctx* ctx) {
 // Variant choice.  Default: one wave per BFS (most BFSs are short chains of
 // dependent steps; a wave needs no barrier, and 4,096 of them hide each
 // other's trips to memory: BA n = 10^6, 400,000 samples, 15.1 ms, against
-// 19.4 ms with 128 threads).  Where the memory cap or the budget leaves fewer
-// slots than fill the device, more threads per BFS do: 128 below 3,072 slots,
-// 256 below 2,048 (directed R-MAT scale 22, 1,524 slots, 2.7M samples a
+// 19.4 ms with 128 threads).  Where there are few BFSs, more threads each end
+// the longest of them sooner: 256 below 2,048 samples (BA n = 10^6, 2,000: 0.99
+// ms with 64, 0.65 with 128, 0.48 with 256), 128 below 16,384 (10,000: 1.57,
+// 1.19, 1.02; BA n = 2,000: 0.26, 0.20, 0.23; 4-neighbour grid 128 x 128, the
+// exception: 15.3, 19.3, 24.2).  So also where the memory cap or the budget
+// leaves fewer slots than fill the device: 128 below 3,072 slots, 256 below
+// 2,048 (directed R-MAT scale 22, 1,524 slots, 2.7M samples a
 // launch: 405 ms with 64 threads, 321 with 128, 298 with 256).
 // CENTRA_SAMPLER_VARIANT selects another: "lds" (exact LDS bitmap, 1024
 // threads, when the bitmap fits), "hbm512", "hbm256", "hbm128", "hbm64" (LDS
 // filter, that many threads).
-static SamplePlan plan_for(centra_ctx* ctx, uint32_t n, int block_override = 0) {
+static SamplePlan plan_for(centra_ctx* ctx, uint32_t n, uint32_t count, int block_override = 0) {
   SamplePlan p{};
   p.bit_words = (n + 31) / 32;
   int max_lds = 0, cus = 0;
@@ -74,7 +78,7 @@ static SamplePlan plan_for(centra_ctx* ctx, uint32_t n, int block_override = 0) 
   const size_t cap = slot_mem_cap(ctx);
   const size_t most = (ctx->budget && ctx->budget < cap ? ctx->budget : cap) / slot_bytes(n);
   const char* v = env ? env : "";
-  p.block = most < 2048 ? 256 : most < 3072 ? 128 : 64;
+  p.block = most < 2048 || count < 2048 ? 256 : most < 3072 || count < 16384 ? 128 : 64;
   if (!strcmp(v, "hbm64")) p.block = 64;
   if (!strcmp(v, "hbm512")) p.block = 512;
   if (!strcmp(v, "hbm256")) p.block = 256;
@@ -341,11 +345,12 @@ static int launch_sampler(centra_ctx* ctx, SampleArgs a, uint32_t count, uint32_
                           uint64_t* total, hipStream_t s, uint64_t async_cap = 0) {
   int rc;
   *total = 0;
-  const SamplePlan plan = plan_for(ctx, max_n, multi ? block : 0);
+  const SamplePlan plan = plan_for(ctx, max_n, count, multi ? block : 0);
   uint32_t want = count < plan.resident ? count : plan.resident;
   bool fresh = false;
   if ((rc = ensure_slots(ctx, max_n, want, s, &fresh))) return rc;
-  const uint32_t grid = count < ctx->slots ? count : ctx->slots;
+  // (slots may be left from a launch of more and smaller workgroups)
+  const uint32_t grid = want < ctx->slots ? want : ctx->slots;
   if ((rc = ensure(ctx, ctx->stage_pos, size_t(count) * 8, false, s))) return rc;
   if ((rc = ensure(ctx, ctx->stage_len, size_t(count) * 4 + 8 + 8 * (size_t(count) + 1), false, s))) return rc;
   if ((rc = ensure(ctx, ctx->work_ctr, kCtrBytes, false, s))) return rc;
@@ -542,7 +547,7 @@ __global__ void k_stage_append(uint32_t count, const uint64_t* stage_pos, const 
 }
 
 int sample_reserve(centra_ctx* ctx, const centra_graph* g, uint32_t count, uint64_t stage_entries, hipStream_t s) {
-  const SamplePlan plan = plan_for(ctx, g->n);
+  const SamplePlan plan = plan_for(ctx, g->n, count);
   const uint32_t want = count < plan.resident ? count : plan.resident;
   int rc;
   bool fresh = false;   // no placement search here: there is no launch to time
