@@ -488,8 +488,13 @@ constexpr uint32_t kTopBlocks = 64, kTopBlock = 256, kTopCols = kTopBlocks * kTo
 constexpr uint32_t kBatchBlock = 1024;
 constexpr uint32_t kBatchSegs = 16;            // incidence segments at most
 constexpr uint32_t kBatchRows = kCands * kBatchSegs;
-constexpr uint32_t kBatchList = 1u << 18;      // masks listed at most
+constexpr uint32_t kBatchList = 1u << 19;      // masks listed at most
 constexpr uint32_t kBatchMinK = 12;            // rounds from which batches pay
+// Samples up to which they do: one workgroup goes through the listed masks for
+// every pick, and their number grows with m (a whole run on BA n = 10^5 up to
+// 400,000 samples: 9.4 ms in batches, 10.8 by rounds; build and greedy of 4M
+// samples of BA n = 10^6: 3.7 in batches, 2.3 by rounds).
+constexpr uint64_t kBatchMaxM = 2u << 20;
 constexpr uint32_t kBatchMinPicks = 8;         // a batch with fewer is the last
 
 // Device state of a batch.  Row i = c * n_seg + g is candidate c's in segment
@@ -1354,7 +1359,7 @@ int greedy_on_incidence(centra_ctx* ctx, bool waits, uint32_t n, uint64_t m, con
   if ((rc = ensure(ctx, ctx->newcov, size_t(k) * 8, false, s))) return rc;
   // In batches where the call may wait for them; not under a budget, whose
   // memory other steps may need.
-  if (waits && !ctx->budget && k >= kBatchMinK && ctx->inc_nseg <= kBatchSegs &&
+  if (waits && !ctx->budget && k >= kBatchMinK && m <= kBatchMaxM && ctx->inc_nseg <= kBatchSegs &&
       !greedy_solo(n, m, ctx->inc_limit, k)) {
     BatchArgs a{};
     a.n = n;

@@ -29,7 +29,7 @@ SETS = {
     "hubs": lambda rng: (45_000, hubs(45_000, 60_000, 200, rng)),
     "columns": lambda rng: (70_000, [np.unique(np.concatenate([16384 * rng.integers(0, 4, 2) + rng.integers(0, 3, 2),
                                                                rng.integers(0, 70_000, 1)])) for _ in range(40_000)]),
-    "shared": lambda rng: (40_000, [np.arange(60)[rng.random(60) < 0.2] for _ in range(300_000)]),   # past the list
+    "shared": lambda rng: (40_000, [np.arange(60)[rng.random(60) < 0.2] for _ in range(560_000)]),   # past the list
 }
 
 
