@@ -198,21 +198,19 @@ __global__ __launch_bounds__(kItemBlock) void k_inc_items_pass(const uint64_t* t
   }
 }
 
-// a[i] += *add (the addend read on the device)
-__global__ void k_inc_offset(uint64_t* a, uint64_t n, const uint64_t* add) {
-  const uint64_t x = *add;
-  if (x == 0) return;
-  for (uint64_t i = blockIdx.x * uint64_t(blockDim.x) + threadIdx.x; i < n; i += uint64_t(gridDim.x) * blockDim.x)
-    a[i] += x;
-}
-
-__global__ void k_inc_copy(const uint64_t* src, uint64_t* dst, uint64_t n) {
-  for (uint64_t i = blockIdx.x * uint64_t(blockDim.x) + threadIdx.x; i < n; i += uint64_t(gridDim.x) * blockDim.x)
-    dst[i] = src[i];
-}
-
-__global__ void k_inc_add(const uint32_t* a, uint32_t n, uint32_t* acc) {
-  for (uint32_t u = blockIdx.x * blockDim.x + threadIdx.x; u < n; u += gridDim.x * blockDim.x) acc[u] += a[u];
+// Between passes 3 and 4, per node: the row's offset in the incidence (past
+// the *add entries of the samples before, if there are any), its cursor, and the degree over
+// the segments.
+__global__ void k_inc_rows(uint64_t* off, uint64_t* cur, const uint64_t* add, const uint32_t* sdeg, uint32_t* deg,
+                           uint32_t n, int first) {
+  const uint64_t x = add ? *add : 0ull;
+  for (uint64_t u = blockIdx.x * uint64_t(blockDim.x) + threadIdx.x; u <= n; u += uint64_t(gridDim.x) * blockDim.x) {
+    const uint64_t o = off[u] + x;
+    if (x) off[u] = o;
+    if (u == n) break;
+    cur[u] = o;
+    deg[u] = (first ? 0u : deg[u]) + sdeg[u];
+  }
 }
 
 uint32_t buckets_of(uint32_t n) { return (n + kBucketNodes - 1) / kBucketNodes; }
@@ -268,7 +266,6 @@ void incidence_segment_bucketed(uint32_t n, uint64_t m0, uint64_t m1, uint64_t s
   size_t total = 0;
   const IncWs w = carve(ws, n, span_cap, &total);
   const uint32_t B = buckets_of(n);
-  if (first_segment) fill_u32(deg, 0, n, s);
   fill_u32(sdeg, 0, n, s);
   const bool any = m1 > m0 && span_cap;
   // items small enough for the device to have some hundreds (with 16,384
@@ -292,17 +289,13 @@ void incidence_segment_bucketed(uint32_t n, uint64_t m0, uint64_t m1, uint64_t s
                        static_cast<uint32_t*>(nullptr), static_cast<uint32_t*>(nullptr), limit, flags);
   }
   excl_scan_u32_to_u64_ws(sdeg, off, n, w.tiles, s);
-  if (m0)
-    hipLaunchKernelGGL(k_inc_offset, dim3(grid_of(uint64_t(n) + 1, 256)), dim3(256), 0, s, off, uint64_t(n) + 1,
-                       he_off + m0);
-  hipLaunchKernelGGL(k_inc_copy, dim3(grid_of(n, 256)), dim3(256), 0, s, static_cast<const uint64_t*>(off), cur,
-                     uint64_t(n));
+  hipLaunchKernelGGL(k_inc_rows, dim3(grid_of(uint64_t(n) + 1, 256)), dim3(256), 0, s, off, cur,
+                     m0 ? he_off + m0 : nullptr, static_cast<const uint32_t*>(sdeg), deg, n, first_segment ? 1 : 0);
   if (any)
     hipLaunchKernelGGL(k_inc_items_pass<true>, dim3(kItemGrid), dim3(kItemBlock), 0, s,
                        static_cast<const uint64_t*>(w.tmp), static_cast<const uint64_t*>(w.pos),
                        static_cast<const uint64_t*>(w.item_off), B, item, static_cast<uint32_t*>(nullptr), cur, inc,
                        inc_node, limit, flags);
-  hipLaunchKernelGGL(k_inc_add, dim3(grid_of(n, 256)), dim3(256), 0, s, static_cast<const uint32_t*>(sdeg), n, deg);
 }
 
 }  // namespace centra

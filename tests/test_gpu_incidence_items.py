@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("entries", [1, 1023, 1024, 1025, 196_608, 393_215, 393_216, 3_145_728])
-@pytest.mark.parametrize("n", [2047, 2049])
+@pytest.mark.parametrize("n", [2047, 2049, 12_287, 12_288, 12_289])
 def test_every_entry_once(n, entries):
     rng = np.random.default_rng(entries)
     nodes = np.minimum((n * rng.random(entries) ** 4).astype(np.uint32), n - 1)
