@@ -57,15 +57,16 @@ size_t slot_mem_cap(centra_ctx* ctx) {
 // 19.4 ms with 128 threads).  Where there are few BFSs, more threads each end
 // the longest of them sooner: 256 below 2,048 samples (BA n = 10^6, 2,000: 0.99
 // ms with 64, 0.65 with 128, 0.48 with 256), 128 below 16,384 (10,000: 1.57,
-// 1.19, 1.02; BA n = 2,000: 0.26, 0.20, 0.23; 4-neighbour grid 128 x 128, the
-// exception: 15.3, 19.3, 24.2).  So also where the memory cap or the budget
+// 1.19, 1.02; BA n = 2,000: 0.26, 0.20, 0.23).  Where no row is longer than a
+// wave the levels are narrow and one wave each does from 2,048 on (4-neighbour
+// grid 128 x 128, 10,000 samples: 15.3, 19.3, 24.2).  So also where the memory cap or the budget
 // leaves fewer slots than fill the device: 128 below 3,072 slots, 256 below
 // 2,048 (directed R-MAT scale 22, 1,524 slots, 2.7M samples a
 // launch: 405 ms with 64 threads, 321 with 128, 298 with 256).
 // CENTRA_SAMPLER_VARIANT selects another: "lds" (exact LDS bitmap, 1024
 // threads, when the bitmap fits), "hbm512", "hbm256", "hbm128", "hbm64" (LDS
 // filter, that many threads).
-static SamplePlan plan_for(centra_ctx* ctx, uint32_t n, uint32_t count, int block_override = 0) {
+static SamplePlan plan_for(centra_ctx* ctx, uint32_t n, uint32_t count, uint32_t max_degree, int block_override = 0) {
   SamplePlan p{};
   p.bit_words = (n + 31) / 32;
   int max_lds = 0, cus = 0;
@@ -78,7 +79,8 @@ static SamplePlan plan_for(centra_ctx* ctx, uint32_t n, uint32_t count, int bloc
   const size_t cap = slot_mem_cap(ctx);
   const size_t most = (ctx->budget && ctx->budget < cap ? ctx->budget : cap) / slot_bytes(n);
   const char* v = env ? env : "";
-  p.block = most < 2048 || count < 2048 ? 256 : most < 3072 || count < 16384 ? 128 : 64;
+  const uint32_t many = max_degree <= kWave ? 2048 : 16384;   // samples from which one wave each is enough
+  p.block = most < 2048 || count < 2048 ? 256 : most < 3072 || count < many ? 128 : 64;
   if (!strcmp(v, "hbm64")) p.block = 64;
   if (!strcmp(v, "hbm512")) p.block = 512;
   if (!strcmp(v, "hbm256")) p.block = 256;
@@ -345,7 +347,7 @@ static int launch_sampler(centra_ctx* ctx, SampleArgs a, uint32_t count, uint32_
                           uint64_t* total, hipStream_t s, uint64_t async_cap = 0) {
   int rc;
   *total = 0;
-  const SamplePlan plan = plan_for(ctx, max_n, count, multi ? block : 0);
+  const SamplePlan plan = plan_for(ctx, max_n, count, a.max_out_deg, multi ? block : 0);
   uint32_t want = count < plan.resident ? count : plan.resident;
   bool fresh = false;
   if ((rc = ensure_slots(ctx, max_n, want, s, &fresh))) return rc;
@@ -547,7 +549,7 @@ __global__ void k_stage_append(uint32_t count, const uint64_t* stage_pos, const 
 }
 
 int sample_reserve(centra_ctx* ctx, const centra_graph* g, uint32_t count, uint64_t stage_entries, hipStream_t s) {
-  const SamplePlan plan = plan_for(ctx, g->n, count);
+  const SamplePlan plan = plan_for(ctx, g->n, count, g->max_out_degree);
   const uint32_t want = count < plan.resident ? count : plan.resident;
   int rc;
   bool fresh = false;   // no placement search here: there is no launch to time
