@@ -352,7 +352,7 @@ static int build_level(centra_engine* e, EnginePool& p, uint32_t j, hipStream_t 
   int32_t* P = static_cast<int32_t*>(p.P.ptr);
   if (j == 0) fill_u32(reinterpret_cast<uint32_t*>(P), 0, size_t(n) * t, s);
   rade_count_launch(static_cast<const uint32_t*>(p.inc.ptr), static_cast<const uint32_t*>(p.inc_node.ptr), off, m0, m1,
-                    I1 - I0, I1, words, t, P, s);
+                    I1 - I0, I1, words, t, j == 0, P, s);
   rade_finish_launch(P, degj, n, t, static_cast<int32_t*>(p.R[j].ptr), s);
   uint32_t* bm = static_cast<uint32_t*>(p.bmax.ptr);
   if (j == 0)

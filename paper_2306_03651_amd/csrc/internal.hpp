@@ -307,11 +307,13 @@ constexpr uint32_t kSelPrefixMax = 2048;
 size_t select_prefix_ws_bytes(uint32_t n_rows, uint32_t K);
 void select_prefix_rows(const SelRow* rows, uint32_t n_rows, uint32_t max_n, uint32_t K, void* ws, int64_t* out,
                         hipStream_t s);
-// Launch-only AMCERA steps (mcera.hip).
+// Launch-only AMCERA steps (mcera.hip).  whole: P is zero and samples
+// [m0, m1) are one segment of the incidence, so each node has one row there.
 void rade_words_launch(uint64_t seed, uint32_t instance, uint64_t s0, uint64_t s1, uint32_t t, uint64_t* words,
                        hipStream_t s);
 void rade_count_launch(const uint32_t* inc, const uint32_t* inc_node, const uint64_t* he_off, uint64_t m0, uint64_t m1,
-                       uint64_t span_cap, uint64_t limit, const uint64_t* words, uint32_t t, int32_t* P, hipStream_t s);
+                       uint64_t span_cap, uint64_t limit, const uint64_t* words, uint32_t t, bool whole, int32_t* P,
+                       hipStream_t s);
 void rade_finish_launch(const int32_t* P, const uint32_t* deg, uint32_t n, uint32_t t, int32_t* Rtm, hipStream_t s);
 void bmax_launch(const uint64_t* he_off, uint64_t m0, uint64_t m1, uint32_t* b_max, hipStream_t s);
 

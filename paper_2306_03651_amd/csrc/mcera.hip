@@ -85,9 +85,9 @@ constexpr uint32_t kCountWaves = 16384;   // two fills of the device
 // trials, where this takes 7.6.
 //
 // A run of entries that both starts and ends inside the span is the node's
-// whole row of the segment: with `whole` (the first segment; P is zero) its
-// counts are stored, the others are added atomically (spans may split a
-// row).  (Atomics execute in memory on this card: n = 10^6, 4.5M entries, 64
+// whole row of its segment: with `whole` (the range is one segment and P is
+// zero, so a node has no other run) its counts are stored, the others are
+// added atomically (spans may split a row).  (Atomics execute in memory on this card: n = 10^6, 4.5M entries, 64
 // trials, 191 us with atomics alone, 114 with stores.)
 __global__ __launch_bounds__(kCountBlock) void k_rade_count(const uint32_t* inc, const uint32_t* inc_node,
                                                             const uint64_t* he_off, uint64_t m0, uint64_t m1,
@@ -480,14 +480,15 @@ void rade_words_launch(uint64_t seed, uint32_t instance, uint64_t s0, uint64_t s
 }
 
 void rade_count_launch(const uint32_t* inc, const uint32_t* inc_node, const uint64_t* he_off, uint64_t m0, uint64_t m1,
-                       uint64_t span_cap, uint64_t limit, const uint64_t* words, uint32_t t, int32_t* P, hipStream_t s) {
+                       uint64_t span_cap, uint64_t limit, const uint64_t* words, uint32_t t, bool whole, int32_t* P,
+                       hipStream_t s) {
   const uint32_t Wt = (t + 63) / 64;
   if (m1 > m0 && span_cap) {
     uint64_t waves = (span_cap + kWave - 1) / kWave;
     if (waves > kCountWaves) waves = kCountWaves;
     const uint64_t blocks = (waves * kWave + kCountBlock - 1) / kCountBlock;
     hipLaunchKernelGGL(k_rade_count, dim3(static_cast<unsigned>(blocks), Wt), dim3(kCountBlock), 0, s, inc, inc_node,
-                       he_off, m0, m1, limit, words, Wt, t, m0 == 0 ? 1 : 0, P);
+                       he_off, m0, m1, limit, words, Wt, t, whole ? 1 : 0, P);
   }
 }
 
@@ -863,7 +864,8 @@ int mcera_on_incidence(centra_ctx* ctx, uint32_t n, uint64_t m, uint64_t m0, con
   const uint32_t* deg = static_cast<const uint32_t*>(ctx->deg.ptr);
   if (m0 == 0) fill_u32(reinterpret_cast<uint32_t*>(P), 0, size_t(n) * t, s);
   rade_count_launch(static_cast<const uint32_t*>(ctx->inc.ptr), static_cast<const uint32_t*>(ctx->inc_node.ptr), he_off,
-                    m0, m, span_cap, ctx->inc_limit, static_cast<const uint64_t*>(ctx->words.ptr), t, P, s);
+                    m0, m, span_cap, ctx->inc_limit, static_cast<const uint64_t*>(ctx->words.ptr), t,
+                    m0 == 0 && ctx->inc_nseg == 1, P, s);
   if (R_out)
     hipLaunchKernelGGL(k_rade_rows, dim3(grid_for(uint64_t(n) * t, 256)), dim3(256), 0, s, P, deg, n, t, R_out);
   columns_topk(P, deg, n, t, k, ctx->inc_limit, ctx->topk_tmp.ptr, topk_sum, reinterpret_cast<int64_t*>(deg_topk), s);
