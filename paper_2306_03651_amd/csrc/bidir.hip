@@ -741,34 +741,33 @@ constexpr uint32_t kBiFewSlots = 1024;
 // Slot arrays of the bidirectional sampler: forward and backward records
 // and queues, 40 bytes per node per slot, at most half of the device's
 // memory (the context budget can lower that).
+constexpr uint32_t kBiLeanSlots = 1792;   // slots beyond which memory is only taken if much is left
+
 static size_t most_bidir_slots(centra_ctx* ctx, uint32_t n) {
   const size_t most = slot_mem_cap(ctx) / (size_t(n) * 40);
   return most ? most : 1;
 }
 
 static int ensure_bidir_slots(centra_ctx* ctx, uint32_t n, uint32_t want, hipStream_t s) {
-  const size_t most = most_bidir_slots(ctx, n);
-  if (want > most) want = static_cast<uint32_t>(most);
   if (ctx->bi_slots >= want && ctx->bi_n >= n) return CENTRA_OK;
-  uint32_t slots = want;   // sized for this launch alone (see ensure_slots)
-  const uint32_t nn = n;
-  for (;;) {
-    const size_t need = size_t(slots) * nn * 40;
-    const size_t have = ctx->bi_rec_f.bytes + ctx->bi_rec_b.bytes + ctx->bi_q_f.bytes + ctx->bi_q_b.bytes;
-    if (!ctx->budget || ctx->allocated - have + need <= ctx->budget || slots <= 1) break;
+  const uint32_t nn = n;   // sized for this launch alone (see ensure_slots)
+  DevBuf* bufs[] = {&ctx->bi_rec_f, &ctx->bi_rec_b, &ctx->bi_q_f, &ctx->bi_q_b};
+  size_t have = 0;
+  for (DevBuf* b : bufs) have += b->bytes;
+  uint32_t slots = slots_that_fit(ctx, size_t(nn) * 40, want, kBiLeanSlots, have);
+  int rc;
+  for (;;) {   // halve the slot count while the device cannot hold the state
+    for (DevBuf* b : bufs) release(ctx, *b);
+    ctx->bi_slots = 0;
+    ctx->bi_n = 0;
+    rc = ensure(ctx, ctx->bi_rec_f, size_t(slots) * nn * 16, false, s);
+    if (!rc) rc = ensure(ctx, ctx->bi_rec_b, size_t(slots) * nn * 16, false, s);
+    if (!rc) rc = ensure(ctx, ctx->bi_q_f, size_t(slots) * nn * 4, false, s);
+    if (!rc) rc = ensure(ctx, ctx->bi_q_b, size_t(slots) * nn * 4, false, s);
+    if (rc != CENTRA_ENOMEM || slots <= 64) break;
     slots /= 2;
   }
-  release(ctx, ctx->bi_rec_f);
-  release(ctx, ctx->bi_rec_b);
-  release(ctx, ctx->bi_q_f);
-  release(ctx, ctx->bi_q_b);
-  ctx->bi_slots = 0;
-  ctx->bi_n = 0;
-  int rc;
-  if ((rc = ensure(ctx, ctx->bi_rec_f, size_t(slots) * nn * 16, false, s))) return rc;
-  if ((rc = ensure(ctx, ctx->bi_rec_b, size_t(slots) * nn * 16, false, s))) return rc;
-  if ((rc = ensure(ctx, ctx->bi_q_f, size_t(slots) * nn * 4, false, s))) return rc;
-  if ((rc = ensure(ctx, ctx->bi_q_b, size_t(slots) * nn * 4, false, s))) return rc;
+  if (rc) return rc;
   fill_u64(static_cast<uint64_t*>(ctx->bi_rec_f.ptr), 0, size_t(slots) * nn * 2, s);   // stamp 0: never claimed
   fill_u64(static_cast<uint64_t*>(ctx->bi_rec_b.ptr), 0, size_t(slots) * nn * 2, s);
   CENTRA_HIP(ctx, hipGetLastError());

@@ -20,6 +20,7 @@ namespace centra {
 // CU (the bitmap takes most of the LDS); the other variants (a 2 KB visited
 // filter in LDS) run several workgroups of 64 to 512 threads per CU.
 constexpr uint32_t kMaxSlots = 8192;
+constexpr uint32_t kLeanSlots = 3072;   // slots beyond which memory is only taken if much is left
 
 // Byte offsets of a launch's counters in work_ctr: the two words that every
 // workgroup adds to on lines of their own; then arcs, nodes, entries, and
@@ -100,41 +101,55 @@ static SamplePlan plan_for(centra_ctx* ctx, uint32_t n, uint32_t count, uint32_t
   return p;
 }
 
+// Slots for a launch that has a use for `want`, where the state held now
+// takes `have` bytes.  Up to `lean` of them may take half of the device.
+// More hide more latency but leave less memory to whatever is allocated
+// next, so they are only taken without a budget, and while the state stays
+// within three eighths of the device and three eighths remain free.  (A
+// context that draws from both samplers on n = 2 10^6 would otherwise ask for
+// the whole device.)
+uint32_t slots_that_fit(centra_ctx* ctx, size_t per_slot, uint32_t want, uint32_t lean, size_t have) {
+  const size_t most = slot_mem_cap(ctx) / per_slot;
+  if (want > most) want = most ? static_cast<uint32_t>(most) : 1u;
+  if (ctx->budget) {
+    const size_t others = ctx->allocated - have;
+    auto fits = [&](uint32_t slots) { return others + size_t(slots) * per_slot <= ctx->budget; };
+    uint32_t slots = want < lean ? want : lean;
+    if (!fits(slots))
+      for (slots = lean; slots > 1 && !fits(slots);) slots /= 2;
+    return slots < want ? slots : want;
+  }
+  if (want > lean) {
+    const size_t share = slot_mem_cap(ctx) / 4 * 3;
+    size_t free_b = 0, total_b = 0;
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
+      (void)hipGetLastError();
+      return lean;
+    }
+    const size_t room = free_b + have > share ? std::min(share, free_b + have - share) : 0;
+    want = std::max<uint32_t>(lean, std::min<size_t>(want, room / per_slot));
+  }
+  return want;
+}
+
 static int ensure_slots(centra_ctx* ctx, uint32_t gn, uint32_t want, hipStream_t s, bool* fresh) {
   *fresh = false;
-  const size_t cap_bytes = slot_mem_cap(ctx);
-  {
-    // never ask for more slots than the cap holds
-    const size_t most = cap_bytes / slot_bytes(gn);
-    if (want > most) want = most ? static_cast<uint32_t>(most) : 1u;
-  }
   if (ctx->slots >= want && ctx->slot_n >= gn) return CENTRA_OK;
   // a new allocation is sized for this launch alone: keeping the largest n
   // ever seen with the largest slot count ever asked for would grow the
   // state (and its zero fill) to the memory cap after one large graph
-  uint32_t slots = want;
   const uint32_t n = gn;
-  const size_t per_slot = slot_bytes(n);
   DevBuf* bufs[] = {&ctx->slot_map, &ctx->slot_sig, &ctx->slot_q, &ctx->slot_starts, &ctx->slot_pinfo};
-  // at most the cap of slot state (or the budget, if smaller)
-  if (size_t(slots) * per_slot > cap_bytes) slots = static_cast<uint32_t>(cap_bytes / per_slot);
-  if (slots == 0) slots = 1;
-  // shrink the slot count if the budget cannot hold all of them
   size_t have = 0;
   for (DevBuf* b : bufs) have += b->bytes;
-  for (;;) {
-    const size_t need = size_t(slots) * per_slot;
-    if (!ctx->budget || ctx->allocated - have + need <= ctx->budget || slots <= 1) break;
-    slots /= 2;
-  }
+  uint32_t slots = slots_that_fit(ctx, slot_bytes(n), want, kLeanSlots, have);
   int rc;
   for (;;) {   // halve the slot count while the device cannot hold the state
     for (DevBuf* b : bufs) release(ctx, *b);
     ctx->slots = 0;
     ctx->slot_n = 0;
     rc = ensure(ctx, ctx->slot_map, size_t(slots) * n * 8, false, s);
-    // (two slots' counts at least: one sample's records of the device-wide BFS)
-    if (!rc) rc = ensure(ctx, ctx->slot_sig, size_t(slots < 2 ? 2 : slots) * n * 8, false, s);
+    if (!rc) rc = ensure(ctx, ctx->slot_sig, size_t(slots) * n * 8, false, s);
     if (!rc) rc = ensure(ctx, ctx->slot_pinfo, size_t(slots) * kPairMax * 12, false, s);
     if (!rc) rc = ensure(ctx, ctx->slot_q, size_t(slots) * n * 4, false, s);
     if (!rc) rc = ensure(ctx, ctx->slot_starts, size_t(slots) * start_words(n) * 8, false, s);
@@ -272,7 +287,7 @@ static int probe_slots(centra_ctx* ctx, SampleArgs a, const SamplePlan& plan, bo
     // left out, as the timed launches leave it to the device-wide BFS
     int rc;
     const uint32_t grid = count < ctx->slots ? count : ctx->slots;
-    if (!multi && !plan.lds_bits && wide_enabled() && (rc = defer_args(ctx, a, grid, s))) return rc;
+    if (!multi && !plan.lds_bits && wide_enabled() && ctx->slots >= 2 && (rc = defer_args(ctx, a, grid, s))) return rc;
     CENTRA_HIP(ctx, hipEventRecord(ctx->ev[6], s));
     sample_kernel_launch(a, plan.block, plan.lds_bits, multi, grid, plan.dyn_lds, s);
     CENTRA_HIP(ctx, hipGetLastError());
@@ -391,7 +406,8 @@ static int launch_sampler(centra_ctx* ctx, SampleArgs a, uint32_t count, uint32_
     fill_u64(static_cast<uint64_t*>(ctx->work_ctr.ptr), 0, kCtrBytes / 8, s);
     reserve_stamps(ctx, count, s);
     launch_args(ctx, a, plan, count, cap, chunk);
-    const bool wide = !async_cap && !multi && !plan.lds_bits && wide_enabled();
+    // (a sample's records of the device-wide BFS take two slots' counts)
+    const bool wide = !async_cap && !multi && !plan.lds_bits && wide_enabled() && ctx->slots >= 2;
     if (wide && (rc = defer_args(ctx, a, grid, s))) return rc;
     CENTRA_HIP(ctx, hipEventRecord(ctx->ev[6], s));
     sample_kernel_launch(a, plan.block, plan.lds_bits, multi, grid, plan.dyn_lds, s);
