@@ -749,16 +749,18 @@ static size_t most_bidir_slots(centra_ctx* ctx, uint32_t n) {
 }
 
 static int ensure_bidir_slots(centra_ctx* ctx, uint32_t n, uint32_t want, hipStream_t s) {
-  if (ctx->bi_slots >= want && ctx->bi_n >= n) return CENTRA_OK;
+  // enough of them, or all that this many were cut down to
+  if ((ctx->bi_slots >= want && ctx->bi_n >= n) || (ctx->bi_want >= want && ctx->bi_n == n)) return CENTRA_OK;
   const uint32_t nn = n;   // sized for this launch alone (see ensure_slots)
   DevBuf* bufs[] = {&ctx->bi_rec_f, &ctx->bi_rec_b, &ctx->bi_q_f, &ctx->bi_q_b};
   size_t have = 0;
   for (DevBuf* b : bufs) have += b->bytes;
   uint32_t slots = slots_that_fit(ctx, size_t(nn) * 40, want, kBiLeanSlots, have);
+  if (ctx->bi_slots >= slots && ctx->bi_n >= nn) return CENTRA_OK;
   int rc;
   for (;;) {   // halve the slot count while the device cannot hold the state
     for (DevBuf* b : bufs) release(ctx, *b);
-    ctx->bi_slots = 0;
+    ctx->bi_slots = ctx->bi_want = 0;
     ctx->bi_n = 0;
     rc = ensure(ctx, ctx->bi_rec_f, size_t(slots) * nn * 16, false, s);
     if (!rc) rc = ensure(ctx, ctx->bi_rec_b, size_t(slots) * nn * 16, false, s);
@@ -772,6 +774,7 @@ static int ensure_bidir_slots(centra_ctx* ctx, uint32_t n, uint32_t want, hipStr
   fill_u64(static_cast<uint64_t*>(ctx->bi_rec_b.ptr), 0, size_t(slots) * nn * 2, s);
   CENTRA_HIP(ctx, hipGetLastError());
   ctx->bi_slots = slots;
+  ctx->bi_want = want;
   ctx->bi_n = nn;
   return CENTRA_OK;
 }

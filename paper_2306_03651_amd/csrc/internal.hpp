@@ -35,12 +35,14 @@ struct centra_ctx {
   std::string log;   // one-time choices of the context (slot placement), one line each
   bool placed = false;   // the slot records' placement was searched
   uint32_t slots = 0;
+  uint32_t slot_want = 0;   // the slots last asked for, of which memory left `slots`
   uint32_t slot_n = 0;
   uint32_t stamp_next = 1;   // BFS stamp of the next sample (records start at stamp 0)
   // slot arrays of the bidirectional sampler (forward and backward records
   // and queues); stamps are shared with the single-source sampler
   centra::DevBuf bi_rec_f, bi_rec_b, bi_q_f, bi_q_b;
   uint32_t bi_slots = 0;
+  uint32_t bi_want = 0;
   uint32_t bi_n = 0;
   // sampling staging area
   centra::DevBuf stage_nodes, stage_pos, stage_len, work_ctr, multi_tab;

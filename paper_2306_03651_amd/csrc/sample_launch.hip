@@ -134,7 +134,8 @@ uint32_t slots_that_fit(centra_ctx* ctx, size_t per_slot, uint32_t want, uint32_
 
 static int ensure_slots(centra_ctx* ctx, uint32_t gn, uint32_t want, hipStream_t s, bool* fresh) {
   *fresh = false;
-  if (ctx->slots >= want && ctx->slot_n >= gn) return CENTRA_OK;
+  // enough of them, or all that this many were cut down to
+  if ((ctx->slots >= want && ctx->slot_n >= gn) || (ctx->slot_want >= want && ctx->slot_n == gn)) return CENTRA_OK;
   // a new allocation is sized for this launch alone: keeping the largest n
   // ever seen with the largest slot count ever asked for would grow the
   // state (and its zero fill) to the memory cap after one large graph
@@ -143,10 +144,11 @@ static int ensure_slots(centra_ctx* ctx, uint32_t gn, uint32_t want, hipStream_t
   size_t have = 0;
   for (DevBuf* b : bufs) have += b->bytes;
   uint32_t slots = slots_that_fit(ctx, slot_bytes(n), want, kLeanSlots, have);
+  if (ctx->slots >= slots && ctx->slot_n >= n) return CENTRA_OK;
   int rc;
   for (;;) {   // halve the slot count while the device cannot hold the state
     for (DevBuf* b : bufs) release(ctx, *b);
-    ctx->slots = 0;
+    ctx->slots = ctx->slot_want = 0;
     ctx->slot_n = 0;
     rc = ensure(ctx, ctx->slot_map, size_t(slots) * n * 8, false, s);
     if (!rc) rc = ensure(ctx, ctx->slot_sig, size_t(slots) * n * 8, false, s);
@@ -161,6 +163,7 @@ static int ensure_slots(centra_ctx* ctx, uint32_t gn, uint32_t want, hipStream_t
   CENTRA_HIP(ctx, hipGetLastError());
   ctx->slots = slots;
   ctx->slot_n = n;
+  ctx->slot_want = want;
   *fresh = true;
   return CENTRA_OK;
 }

@@ -1,5 +1,6 @@
 """The per-BFS state of both path samplers where memory does not hold as much
-of it as a launch has a use for."""
+of it as a launch has a use for: a budget or a filled device gives fewer
+slots, and a later call of the same kind keeps them."""
 import numpy as np
 import pytest
 import torch
@@ -18,6 +19,38 @@ def draw(call, ctx, dg, count, per=64):
     call(ctx, dg.handle, 7, 1, 0, count, off, nodes, None, None, None)
     torch.cuda.synchronize()
     return off_np(off), nodes_np(nodes), binding.centra_sampler_stats_get(ctx)
+
+
+@pytest.mark.parametrize("bidir", [False, True])
+@pytest.mark.parametrize("share", [1.1, 0.9, 0.4, 0.001])
+def test_slots_cut_by_the_budget_are_kept(bidir, share):
+    # shares of the state of as many slots as half of the device may hold; the
+    # smallest leaves room for one or two
+    n, count = (1_000_000, 20_000) if share > 0.01 else (3000, 400)
+    g = inputs.ba_graph(n, 3, 5)
+    state = 1792 * 40 * n if bidir else 3072 * (20.125 * n + 12 * 65536)
+    call = binding.centra_sample_paths_bidir if bidir else binding.centra_sample_paths
+    ctx = binding.centra_create(0, int(share * state) + (64 << 20 if n > 3000 else 1 << 20))
+    try:
+        dg = binding.DeviceGraph(ctx, g)
+        try:
+            say(f"bidir {bidir}, budget for {share} of the slots: {count} samples three times")
+            got = [draw(call, ctx, dg, count) for _ in range(3)]
+            say("  slots", [x[2].slots for x in got])
+            for off, nodes, st in got[1:]:
+                assert st.slots == got[0][2].slots >= 1
+                assert np.array_equal(off, got[0][0]) and np.array_equal(nodes, got[0][1])
+            if n > 3000:   # halves of the most that may take half of the device, or what the threads per BFS use
+                assert got[0][2].slots == ({1.1: 1792, 0.9: 896, 0.4: 448} if bidir else
+                                           {1.1: 3072, 0.9: 2048, 0.4: 1024})[share]
+            if not bidir:
+                want = oracle_paths(g, 7, 1, range(0, 40), dg.info()[1])
+                off, nodes = got[0][:2]
+                assert all(np.array_equal(nodes[int(off[i]):int(off[i + 1])], w[0]) for i, w in enumerate(want))
+        finally:
+            dg.release()
+    finally:
+        binding.centra_destroy(ctx)
 
 
 def test_both_samplers_on_one_context():
