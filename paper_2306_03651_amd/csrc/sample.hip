@@ -103,6 +103,9 @@ template <int BLOCK>
 struct Round {
   static constexpr int kPer = BLOCK <= 128 ? 4 : BLOCK <= 512 ? 2 : 1;
   static constexpr uint32_t kArcs = BLOCK * kPer;
+  // slots of the duplicate table: twice a round's arcs where LDS allows it
+  // without a workgroup less per CU
+  static constexpr uint32_t kSlots = BLOCK == 128 ? kArcs + kArcs / 2 : BLOCK == 256 || BLOCK == 512 ? 2 * kArcs : kArcs;
   static constexpr int kMasks = kArcs / kWave;   // <= 64: one per lane
 };
 
@@ -110,13 +113,13 @@ template <int BLOCK>
 struct SampleShared {
   uint64_t sg[BLOCK];                    // per source of a chunk: its count, its ring index, or the sum of its arcs
   uint64_t ring[Ring<BLOCK>::kCache];    // per in-neighbour w of t: its count on the level the last test gave it
-  uint64_t dsum[Round<BLOCK>::kArcs];    // duplicate table: sums (zero when empty); in the tests the waves' hit lists
+  uint64_t dsum[Round<BLOCK>::kSlots];   // duplicate table: sums (zero when empty); in the tests the waves' hit lists
   uint64_t mask[3][Round<BLOCK>::kMasks];   // arcs of a round that start a source's run
   uint64_t red[2 * Coll<BLOCK>::kHalf];
   uint64_t hub_pairs;
   uint64_t pk_weight;                    // the entry a pick chose: its weight,
   uint32_t pk[4];                        // index, node and in-row bounds
-  uint32_t dkey[Round<BLOCK>::kArcs];    // duplicate table: nodes, kUnseen when empty
+  uint32_t dkey[Round<BLOCK>::kSlots];   // duplicate table: nodes, kUnseen when empty
   uint32_t rs[BLOCK];                    // per source of a chunk: row start less the arcs before it
   uint32_t fr[BLOCK];                    // the first nodes of the newest level
   uint32_t poff[Ring<BLOCK>::kCache];    // pair offsets of t's in-neighbours
@@ -507,9 +510,6 @@ __device__ __forceinline__ int ring_of(const uint32_t* poff, uint32_t dt, uint32
   return lo;
 }
 
-// log2 of a duplicate table's size
-__host__ __device__ constexpr int dup_log(uint32_t r) { return r <= 1 ? 0 : 1 + dup_log(r / 2); }
-
 // Appends the wave's newly claimed nodes to the queue: their places follow
 // one LDS atomic per wave (none in a workgroup of one wave, whose queue
 // length qn is a register).  Returns the thread's place.
@@ -541,37 +541,49 @@ __device__ __forceinline__ uint32_t append(bool has, uint32_t v, uint32_t le, co
 // node of a completed level (dropped), a node of the level being produced
 // (its contribution is added), or an unvisited node whose bit another node
 // set (claimed now).  Their contributions are summed per node in an LDS hash
-// table, and a flush looks every node of the table up, all loads in flight
+// table, and a look-up takes every node of the table, all loads in flight
 // together: one thread per node then adds the sum or claims the node, so no
 // global atomic is needed, and the two trips to memory of a look-up are paid
 // per table, not per round.  A workgroup of one wave fills the table over
-// several rounds; with more waves it is flushed after every round, whose
-// arcs it holds at most.
+// several rounds; with more waves it is looked up after every round, by the
+// threads that entered the nodes.
+//
+// In a flood nearly every arc is such a one, so the table must not fill up:
+// of a table with no more slots than a round has arcs the last entries take
+// hundreds of probes each, and those were most of a flooding BFS's time
+// (directed, n = 10^5, 8 out-arcs each, long in-rows, 20,000 samples, all on
+// their workgroups: 64 threads 33.7 ms -> 17, 128 22.3 -> 11, 256 19.6 -> 7,
+// 512 12.1 -> 5.2).
 template <int BLOCK>
 struct Dups {
-  static constexpr uint32_t kSlots = Round<BLOCK>::kArcs;
-  static constexpr int kPer = kSlots / BLOCK;
+  static constexpr uint32_t kSlots = Round<BLOCK>::kSlots;
+  static constexpr int PER = Round<BLOCK>::kPer;
   SampleShared<BLOCK>& sh;
   const Visited& vis;
   uint32_t n;   // nodes in the table (workgroups of one wave)
 
-  __device__ __forceinline__ void flush(uint32_t le, uint32_t* q, uint32_t& qn, uint64_t& mx, uint64_t& added) {
-    __syncthreads();   // the table's entries and the new nodes are in place
-    uint32_t v[kPer], p[kPer];
-    uint64_t x[kPer], old[kPer];
+  // Looks up the nodes v[k] in slots i[k] (kUnseen: none; every entry of the
+  // table is some thread's).
+  template <int N>
+  __device__ __forceinline__ void look_up(const uint32_t (&v)[N], const uint32_t (&i)[N], uint32_t le, uint32_t* q,
+                                          uint32_t& qn, uint64_t& mx, uint64_t& added) {
+    uint32_t p[N];
+    uint64_t x[N], old[N];
 #pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-      const uint32_t i = k * BLOCK + threadIdx.x;
-      v[k] = sh.dkey[i];
-      x[k] = sh.dsum[i];
-      sh.dkey[i] = kUnseen;
-      sh.dsum[i] = 0;
-      p[k] = v[k] != kUnseen ? vis.place(v[k]) : 0u;
+    for (int k = 0; k < N; ++k) {
+      p[k] = 0;
+      x[k] = 0;
+      if (i[k] != kUnseen) {
+        x[k] = sh.dsum[i[k]];
+        sh.dkey[i[k]] = kUnseen;
+        sh.dsum[i[k]] = 0;
+        p[k] = vis.place(v[k]);
+      }
     }
 #pragma unroll
-    for (int k = 0; k < kPer; ++k) old[k] = p[k] >= le && p[k] != kUnseen ? wg_ld_u64(&vis.sig[p[k]]) : 0ull;
+    for (int k = 0; k < N; ++k) old[k] = p[k] >= le && p[k] != kUnseen ? wg_ld_u64(&vis.sig[p[k]]) : 0ull;
 #pragma unroll
-    for (int k = 0; k < kPer; ++k) {
+    for (int k = 0; k < N; ++k) {
       const bool claims = p[k] == kUnseen;
       const uint32_t at = append<BLOCK>(claims, v[k], le, vis, q, sh, qn);
       if (p[k] >= le) {   // (completed levels and empty slots lie below)
@@ -581,21 +593,77 @@ struct Dups {
         mx = c > mx ? c : mx;
       }
     }
-    n = 0;
     __syncthreads();   // the table is empty, the counts are in place
   }
-  // adds c for node v (every slot taken at most once per round's arc, so a
-  // free one is found)
-  __device__ __forceinline__ bool put(uint32_t v, uint64_t c) {
-    uint32_t h = (v * 0x9E3779B1u) >> (32 - dup_log(kSlots));
+  // Adds c for node v; returns its slot if it was not in the table, else
+  // kUnseen.  (A round enters at most as many nodes as the table has slots,
+  // so a free one is found.)
+  __device__ __forceinline__ uint32_t put(uint32_t v, uint64_t c) {
+    uint32_t h = __umulhi(v * 0x9E3779B1u, kSlots);
     uint32_t was;
     for (;;) {
       was = atomicCAS(&sh.dkey[h], kUnseen, v);
       if (was == kUnseen || was == v) break;
-      h = (h + 1) & (kSlots - 1);
+      h = h + 1 == kSlots ? 0u : h + 1;
     }
     atomicAdd(reinterpret_cast<unsigned long long*>(&sh.dsum[h]), static_cast<unsigned long long>(c));
-    return was == kUnseen;
+    return was == kUnseen ? h : kUnseen;
+  }
+  // A round's arcs: bit k of dup set, node v[k] with contribution c[k] (all
+  // clear for no round); last: no round follows in the level.  Uniform.
+  __device__ __forceinline__ void round(uint32_t dup, const uint32_t (&v)[PER], const uint64_t (&c)[PER], bool last,
+                                        uint32_t le, uint32_t* q, uint32_t& qn, uint64_t& mx, uint64_t& added) {
+    if constexpr (BLOCK == kWave) {
+      // the table is looked up before more than three quarters of it would be
+      // taken, and at the level's end
+      constexpr uint32_t kMost = kSlots - kSlots / 4;
+      constexpr int kOwn = kSlots / BLOCK;
+      uint32_t d = dup, cnt = 0;
+#pragma unroll
+      for (int k = 0; k < PER; ++k) cnt += static_cast<uint32_t>(__popcll(__ballot((dup >> k) & 1u)));
+      // a round that alone would fill more than that goes in two halves
+      uint32_t later = 0, cnt_later = 0;
+      if (cnt > kMost) {
+        later = dup >> (PER / 2) << (PER / 2);
+        d = dup ^ later;
+#pragma unroll
+        for (int k = PER / 2; k < PER; ++k) cnt_later += static_cast<uint32_t>(__popcll(__ballot((dup >> k) & 1u)));
+        cnt -= cnt_later;
+      }
+      for (bool end = false;;) {   // (one place to look up and one to enter: code size)
+        if (n && (end || n + cnt > kMost)) {
+          __syncthreads();   // the entries and the new nodes are in place
+          uint32_t w[kOwn], i[kOwn];
+#pragma unroll
+          for (int k = 0; k < kOwn; ++k) {
+            i[k] = k * BLOCK + threadIdx.x;
+            w[k] = sh.dkey[i[k]];
+            if (w[k] == kUnseen) i[k] = kUnseen;
+          }
+          look_up(w, i, le, q, qn, mx, added);
+          n = 0;
+        }
+        if (end) break;
+        if (cnt) {
+          bool entered[PER];
+#pragma unroll
+          for (int k = 0; k < PER; ++k) entered[k] = ((d >> k) & 1u) && put(v[k], c[k]) != kUnseen;
+#pragma unroll
+          for (int k = 0; k < PER; ++k) n += static_cast<uint32_t>(__popcll(__ballot(entered[k])));
+        }
+        end = !cnt_later;
+        if (end && !last) break;
+        d = later;
+        cnt = cnt_later;
+        cnt_later = 0;
+      }
+    } else {
+      uint32_t i[PER];
+#pragma unroll
+      for (int k = 0; k < PER; ++k) i[k] = (dup >> k) & 1u ? put(v[k], c[k]) : kUnseen;
+      __syncthreads();   // the entries and the new nodes are in place
+      look_up(v, i, le, q, qn, mx, added);
+    }
   }
 };
 
@@ -632,7 +700,7 @@ using ConstInst = const SampleInst __attribute__((address_space(4)))*;
 template <int BLOCK, bool LDS_BITS, bool MULTI = false>
 __global__ __launch_bounds__(BLOCK, BLOCK <= 512 ? 4 : 1) void k_sample_paths(SampleArgs a) {
   constexpr int PER = Round<BLOCK>::kPer;
-  constexpr uint32_t R = Round<BLOCK>::kArcs;   // arcs of an expansion round, slots of the duplicate table
+  constexpr uint32_t R = Round<BLOCK>::kArcs;   // arcs of an expansion round
   __shared__ SampleShared<BLOCK> sh;
   extern __shared__ uint32_t dyn_bits[];
   const uint32_t tid = threadIdx.x;
@@ -652,7 +720,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK <= 512 ? 4 : 1) void k_sample_paths(Sa
   Coll<BLOCK> co{sh.red, 0};
   ArcSpread<BLOCK> sp{sh, 0, 0};
   sp.init();
-  for (uint32_t i = tid; i < R; i += BLOCK) {
+  for (uint32_t i = tid; i < Round<BLOCK>::kSlots; i += BLOCK) {
     sh.dkey[i] = kUnseen;
     sh.dsum[i] = 0;
   }
@@ -1068,7 +1136,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK <= 512 ? 4 : 1) void k_sample_paths(Sa
           }
           base += R;
         }
-        uint32_t dup = 0, n_dup = 0;   // bit k: arc k's target had its bit set
+        uint32_t dup = 0;   // bit k: arc k's target had its bit set
         if (!first) {
 #pragma unroll
           for (int k = 0; k < PER; ++k) {
@@ -1081,28 +1149,10 @@ __global__ __launch_bounds__(BLOCK, BLOCK <= 512 ? 4 : 1) void k_sample_paths(Sa
               mx = add[k] > mx ? add[k] : mx;
               added = sat_add(added, add[k]);
             }
-            const bool again = arc && !fresh;
-            if (again) dup |= 1u << k;
-            if (BLOCK == kWave) n_dup += static_cast<uint32_t>(__popcll(__ballot(again)));
+            if (arc && !fresh) dup |= 1u << k;
           }
         }
-        // the table is looked up when a round may not fit (an eighth stays
-        // free unless a round alone fills it, so that probing ends soon), at
-        // the level's end, and with more than one wave after every round
-        for (bool flush = BLOCK == kWave && dups.n && dups.n + n_dup > dups.kSlots - dups.kSlots / 8;;) {
-          if (flush) dups.flush(le, q, qn, mx, added);
-          bool entered[PER];
-#pragma unroll
-          for (int k = 0; k < PER; ++k) entered[k] = ((dup >> k) & 1u) && dups.put(v[k], add[k]);
-          if (BLOCK == kWave) {
-#pragma unroll
-            for (int k = 0; k < PER; ++k) dups.n += static_cast<uint32_t>(__popcll(__ballot(entered[k])));
-          }
-          dup = 0;
-          const bool again = BLOCK > kWave ? !flush && !first : !more && dups.n;
-          if (!again) break;
-          flush = true;
-        }
+        if (BLOCK == kWave || !first) dups.round(dup, v, add, !more, le, q, qn, mx, added);
         if (!more) break;
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
