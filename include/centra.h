@@ -362,19 +362,22 @@ CENTRA_API int centra_check(centra_ctx *ctx, void *stream);
  * given a level (the bidirectional sampler gives none to those of a search's
  * last level that it only has to look at).  A re-launch after a staging
  * overflow counts again.
- * Wide samples: a BFS about to expand a level of more than 65,536 nodes,
- * or a level of at least 4,096 nodes or 65,536 arcs once it has scanned more
- * CSR entries than its launch's budget (4,096 for each work item of a
- * workgroup's share, at least 2^17 and at most 2^21; a flood of a skewed
- * graph's reachable set; long narrow searches such as grids stay), is handed
- * from its workgroup to a device-wide BFS that redraws the sample level by
- * level with the whole GPU (same hyperedge).  kernel_ms, arcs and nodes stay
- * those of the workgroup kernel (a handed-over BFS's partial work
- * included); `wide` counts such samples, wide_ms is the wall time of their
- * device-wide BFSs (launches and the per-level synchronisation) and
- * wide_arcs the CSR entries those scanned (full levels).  Only the
- * synchronous single-graph launches do this (CENTRA_WIDE=0 turns it off;
- * tests only: CENTRA_WIDE_NODES lowers the level size that triggers it). */
+ * Deferred samples: a BFS about to expand a level of more than 65,536
+ * nodes, or a level of at least 4,096 nodes or 65,536 arcs once it has
+ * scanned more CSR entries than its launch's budget (4,096 for each work item
+ * of a workgroup's share, at least 2^17 and 1/128 of the graph's arcs, at
+ * most 2^21; a flood of a skewed graph's reachable set; long narrow searches
+ * such as grids stay), is left by its workgroup and redrawn after the launch
+ * (same hyperedge): up to 8 such samples by a device-wide BFS each, level by
+ * level with the whole GPU, more of them by a second launch with 512 threads
+ * each, from which those past a budget of 2^21 entries or with wider levels
+ * go to the device-wide BFS.  kernel_ms, arcs and nodes are those of the
+ * workgroup kernel (both launches, the partial work of BFSs that were left
+ * included); `wide` counts the device-wide BFSs, wide_ms is their wall time
+ * (launches and the per-level synchronisation) and wide_arcs the CSR entries
+ * they scanned (full levels).  Only the synchronous single-graph launches do
+ * this (CENTRA_WIDE=0 turns it off; tests only: CENTRA_WIDE_NODES lowers the
+ * level size that triggers it). */
 typedef struct {
     uint64_t launches;
     double kernel_ms;

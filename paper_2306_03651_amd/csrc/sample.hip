@@ -417,8 +417,8 @@ __device__ __forceinline__ uint32_t caller_id(const SampleArgs& a, uint32_t v) {
 constexpr uint32_t kWideMinWidth = 4096;
 constexpr uint64_t kWideMinArcs = 65536;
 
-// Appends work item idx to the deferred list (workgroup uniform); true if
-// it fit, the sample then being left to the device-wide BFS.
+// Appends sample idx to the deferred list (workgroup uniform); true if
+// it fit, the sample then being left for after the launch.
 template <int BLOCK>
 __device__ __forceinline__ bool defer_sample(const SampleArgs& a, uint32_t idx, SampleShared<BLOCK>& sh) {
   if (threadIdx.x == 0) {
@@ -775,7 +775,12 @@ __global__ __launch_bounds__(BLOCK, BLOCK <= 512 ? 4 : 1) void k_sample_paths(Sa
                     a.in_idx, a.new_of, a.orig_of, a.seed, a.first};
     }
     const uint64_t cap = g.c_bits >= 64 ? ~0ull : (1ull << g.c_bits);
-    const uint64_t sample = g.first + idx;
+    // the sample's place in the batch (a second launch draws listed ones)
+    uint32_t out = idx;
+    if constexpr (!LDS_BITS && !MULTI) {
+      if (a.items) out = uniform_u32(a.items[idx]);
+    }
+    const uint64_t sample = g.first + out;
     vis.base = uint64_t(a.stamp0 + idx) << 32;
     vis.exact = LDS_BITS || g.n <= (1u << kBitLog);
 
@@ -1058,12 +1063,12 @@ __global__ __launch_bounds__(BLOCK, BLOCK <= 512 ? 4 : 1) void k_sample_paths(Sa
       }
       if (shortcut || ended) break;
       if constexpr (!LDS_BITS && !MULTI) {
-        // a level too wide for one workgroup, or a wide level of a BFS that
-        // has already scanned millions of entries: the sample goes to the
-        // device-wide BFS (if the list has room), which redraws it in full
+        // a level too wide for one workgroup, or a wide level of a BFS past
+        // the scan budget: the sample is deferred (if the list has room) and
+        // redrawn in full after the launch
         if (a.defer_nodes &&
             (le - lb > a.defer_nodes || (n_arcs - arcs0 > a.defer_arcs && le - lb >= kWideMinWidth)) &&
-            defer_sample<BLOCK>(a, idx, sh)) {
+            defer_sample<BLOCK>(a, out, sh)) {
           deferred = true;
           break;
         }
@@ -1107,11 +1112,11 @@ __global__ __launch_bounds__(BLOCK, BLOCK <= 512 ? 4 : 1) void k_sample_paths(Sa
           more = true;   // (a round of no arcs if the chunk has none)
           if constexpr (!LDS_BITS && !MULTI) {
             // a level whose arcs run past the scan budget (hub frontiers): the
-            // device-wide BFS redraws the sample (uniform; the partial level
-            // is abandoned with the BFS's stamp)
+            // sample is deferred (uniform; the partial level is abandoned with
+            // the BFS's stamp)
             lvl_arcs += total;
             if (a.defer_nodes && n_arcs - arcs0 > a.defer_arcs &&
-                (le - lb >= kWideMinWidth || lvl_arcs >= kWideMinArcs) && defer_sample<BLOCK>(a, idx, sh)) {
+                (le - lb >= kWideMinWidth || lvl_arcs >= kWideMinArcs) && defer_sample<BLOCK>(a, out, sh)) {
               deferred = true;
               more = false;
             }
@@ -1358,13 +1363,13 @@ __global__ __launch_bounds__(BLOCK, BLOCK <= 512 ? 4 : 1) void k_sample_paths(Sa
       }
       if (tid == 0) {
         if (!ok) atomicOr(a.flags, kErrBacktrack);
-        a.stage_pos[idx] = hbase;
-        a.he_len[idx] = len;
+        a.stage_pos[out] = hbase;
+        a.he_len[out] = len;
         if (a.st_out) {
-          a.st_out[2 * size_t(idx)] = s0;
-          a.st_out[2 * size_t(idx) + 1] = t0;
+          a.st_out[2 * size_t(out)] = s0;
+          a.st_out[2 * size_t(out) + 1] = t0;
         }
-        if (a.dist_out) a.dist_out[idx] = d;
+        if (a.dist_out) a.dist_out[out] = d;
       }
     }
     // the map keeps this BFS's stamp (older than any later one); only the

@@ -72,14 +72,15 @@ struct SampleArgs {
   uint32_t n_inst;
   // deferral (single-graph launches only; defer_nodes = 0: none): a BFS
   // about to expand a level of more than defer_nodes nodes, or after
-  // scanning more than defer_arcs CSR entries, appends its work item to
+  // scanning more than defer_arcs CSR entries, appends its sample to
   // defer_list (at most defer_cap, counted in *defer_count) and leaves it
-  // to the device-wide BFS (wide_sample)
+  // to what follows the launch
   uint32_t defer_nodes;
   uint64_t defer_arcs;
   uint32_t defer_cap;
   uint32_t* defer_list;
   uint32_t* defer_count;
+  const uint32_t* items;   // the work items' samples, as offsets from `first` (null: 0 .. count - 1)
 };
 
 hipError_t sample_kernel_occupancy(int block, bool lds_bits, bool multi, size_t dyn_lds, int* per_cu);

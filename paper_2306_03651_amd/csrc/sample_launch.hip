@@ -168,18 +168,31 @@ static int ensure_slots(centra_ctx* ctx, uint32_t gn, uint32_t want, hipStream_t
   return CENTRA_OK;
 }
 
-// Wide samples: a BFS about to expand a level of more than kWideNodes
-// nodes, or past the launch's scan budget, is left to the device-wide BFS
-// (wide_samples in sample.hip); at most kWideCap per launch (the rest finish
-// on their workgroups).  The budget is what a workgroup may expect to scan in
-// the whole launch (kWideArcsPerItem entries per item of its share): a longer
-// BFS would hold the launch after the others have ended, while a shorter one
-// costs less on its workgroup than the whole GPU's time.  (Directed R-MAT
-// scale 20, 200,000 samples: one BFS of 2.3 million entries, 105 ms on its
-// wave, held a launch whose other samples took 6 ms.)
+// Deferred samples: a BFS about to expand a level of more than kWideNodes
+// nodes, or past the launch's scan budget, is left for after the launch; at
+// most kWideCap per launch (the rest finish on their workgroups).  The budget
+// is what a workgroup may expect to scan in the whole launch
+// (kWideArcsPerItem entries per item of its share): a longer BFS would hold
+// the launch after the others have ended.  (Directed R-MAT scale 20, 200,000
+// samples, three BFSs of some 2 million entries each: 28.6 ms with the
+// largest budget, 14.0 with this one.)
+//
+// Up to kWideFew of them go through the device-wide BFS (wide_samples in
+// sample.hip), which takes the whole GPU for each, 0.3 ms (n = 10^5) to 2.4
+// (n = 4 10^6), so the budget is also at least a share of the graph's arcs
+// (R-MAT scale 22, 20,000 samples: 9.2 ms without, 4.0 with; an eighth less of
+// it is as good, twice as much costs scale 20 a ninth).  More of them, of
+// graphs where many BFSs are long, are drawn by a second launch with
+// kSecondBlock threads each, from which only those past the largest budget go
+// to the device-wide BFS.  (BA n = 10^6 of 2 edges per node, 100,000 samples,
+// 1,240 deferred: 1,080 ms all device-wide, 47 with the second launch, 56 with
+// the largest budget; 256 threads in the second launch 49.)
 constexpr uint32_t kWideNodes = 65536;
 constexpr uint64_t kWideArcsPerItem = 4096;
 constexpr uint64_t kWideArcsMin = uint64_t(1) << 17, kWideArcsMax = uint64_t(1) << 21;
+constexpr uint64_t kWideArcsShare = 128;   // of the graph's arcs
+constexpr uint32_t kWideFew = 8;
+constexpr int kSecondBlock = 512;
 constexpr uint32_t kWideCap = 4096;
 constexpr uint32_t kWideGroup = 64;   // deferred samples advanced together
 
@@ -188,13 +201,15 @@ static bool wide_enabled() {
   return !(e && !strcmp(e, "0"));
 }
 
-// Turns deferral on in `a` (its list in ctx->wide_ws, its counter the
-// word after the statistics in work_ctr, cleared with them).
+// Turns deferral on in `a` (its list, with as much room for the second
+// launch's, in ctx->wide_ws, its counter the word after the statistics in
+// work_ctr, cleared with them).
 static int defer_args(centra_ctx* ctx, SampleArgs& a, uint32_t grid, hipStream_t s) {
   int rc;
-  if ((rc = ensure(ctx, ctx->wide_ws, size_t(kWideGroup) * 64 + size_t(kWideCap) * 4, false, s))) return rc;
+  if ((rc = ensure(ctx, ctx->wide_ws, size_t(kWideGroup) * 64 + size_t(kWideCap) * 8, false, s))) return rc;
   a.defer_nodes = kWideNodes;
-  a.defer_arcs = std::min(kWideArcsMax, std::max(kWideArcsMin, a.count / grid * kWideArcsPerItem));
+  a.defer_arcs = std::max({kWideArcsMin, a.n_arcs / kWideArcsShare, a.count / grid * kWideArcsPerItem});
+  a.defer_arcs = std::min(kWideArcsMax, a.defer_arcs);
   if (const char* e = getenv("CENTRA_WIDE_NODES")) {   // tests: a lower threshold
     const long v = atol(e);
     if (v >= 1 && v <= 0x7FFFFFFFl) a.defer_nodes = static_cast<uint32_t>(v);
@@ -261,6 +276,7 @@ static void launch_args(centra_ctx* ctx, SampleArgs& a, const SamplePlan& plan, 
   a.defer_cap = 0;
   a.defer_list = nullptr;
   a.defer_count = nullptr;
+  a.items = nullptr;
 }
 
 // Stamps: a launch numbers its work items stamp_next, stamp_next + 1, ...;
@@ -354,6 +370,33 @@ static int place_slots(centra_ctx* ctx, const SampleArgs& a, const SamplePlan& p
   return CENTRA_OK;
 }
 
+// Draws a launch's n deferred samples (in a.defer_list) by a launch of their
+// own; what this one defers is in a.defer_list on return (the other half of
+// the list).
+static int second_launch(centra_ctx* ctx, SampleArgs& a, uint32_t n, hipStream_t s) {
+  int per_cu = 0, cus = 0;
+  if (sample_kernel_occupancy(kSecondBlock, false, false, 0, &per_cu) != hipSuccess || per_cu <= 0) per_cu = 1;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess || cus <= 0)
+    cus = 256;
+  (void)hipGetLastError();
+  const uint32_t grid = std::min(std::min(n, ctx->slots), static_cast<uint32_t>(cus * per_cu));
+  reserve_stamps(ctx, n, s);
+  a.stamp0 = ctx->stamp_next;
+  ctx->stamp_next += n;
+  a.count = n;
+  a.items = a.defer_list;
+  a.defer_list += kWideCap;
+  a.defer_arcs = kWideArcsMax;
+  a.stage_chunk = 0;
+  fill_u64(a.work, 0, 1, s);
+  fill_u32(a.defer_count, 0, 1, s);
+  CENTRA_HIP(ctx, hipEventRecord(ctx->ev[6], s));
+  sample_kernel_launch(a, kSecondBlock, false, false, grid, 0, s);
+  CENTRA_HIP(ctx, hipGetLastError());
+  CENTRA_HIP(ctx, hipEventRecord(ctx->ev[7], s));
+  return CENTRA_OK;
+}
+
 // Runs one sampling launch of `count` work items into the staging area
 // (redrawn with a larger area if it overflows); `a` holds the graph part of
 // the arguments (or the instance table of a fused launch), `max_n` the
@@ -422,8 +465,19 @@ static int launch_sampler(centra_ctx* ctx, SampleArgs a, uint32_t count, uint32_
     CENTRA_HIP(ctx, hipMemcpyAsync(ctr, ctx->work_ctr.ptr, kCtrBytes, hipMemcpyDeviceToHost, s));
     CENTRA_HIP(ctx, hipStreamSynchronize(s));
     if ((rc = check_flags(ctx, s, "sample_paths"))) return rc;
+    float ms = 0.f, ms2 = 0.f;
+    if (hipEventElapsedTime(&ms, ctx->ev[6], ctx->ev[7]) != hipSuccess) ms = 0.f;
+    auto deferred = [&]() { return static_cast<uint32_t>(std::min<uint64_t>(stats[3] & 0xFFFFFFFFull, kWideCap)); };
+    uint32_t n_wide = wide ? deferred() : 0u;
+    if (n_wide > kWideFew) {
+      if ((rc = second_launch(ctx, a, n_wide, s))) return rc;
+      CENTRA_HIP(ctx, hipMemcpyAsync(ctr, ctx->work_ctr.ptr, kCtrBytes, hipMemcpyDeviceToHost, s));
+      CENTRA_HIP(ctx, hipStreamSynchronize(s));
+      if ((rc = check_flags(ctx, s, "sample_paths (second launch)"))) return rc;
+      if (hipEventElapsedTime(&ms2, ctx->ev[6], ctx->ev[7]) != hipSuccess) ms2 = 0.f;
+      n_wide = deferred();
+    }
     const uint64_t arcs = stats[0], nodes = stats[1];
-    const uint32_t n_wide = wide ? static_cast<uint32_t>(std::min<uint64_t>(stats[3] & 0xFFFFFFFFull, kWideCap)) : 0u;
     if (n_wide) {
       // the deferred samples, one device-wide BFS each, on the slots' queues
       // and (two slots' counts per sample) records
@@ -448,10 +502,8 @@ static int launch_sampler(centra_ctx* ctx, SampleArgs a, uint32_t count, uint32_
       ctx->st.wide += n_wide;
     }
     const uint64_t used = ctr[kCtrUsed / 8], entries = stats[2];
-    float ms = 0.f;
-    if (hipEventElapsedTime(&ms, ctx->ev[6], ctx->ev[7]) != hipSuccess) ms = 0.f;
     ctx->st.launches += 1;
-    ctx->st.kernel_ms += ms;
+    ctx->st.kernel_ms += ms + ms2;
     ctx->st.samples += count;
     ctx->st.arcs += arcs;
     ctx->st.nodes += nodes;
