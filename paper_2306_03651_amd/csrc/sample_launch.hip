@@ -52,22 +52,49 @@ size_t slot_mem_cap(centra_ctx* ctx) {
   return ctx->slot_cap = total_b / 2;
 }
 
-// Variant choice.  Default: one wave per BFS (most BFSs are short chains of
-// dependent steps; a wave needs no barrier, and 4,096 of them hide each
-// other's trips to memory: BA n = 10^6, 400,000 samples, 15.1 ms, against
-// 19.4 ms with 128 threads).  Where there are few BFSs, more threads each end
-// the longest of them sooner: 256 below 2,048 samples (BA n = 10^6, 2,000: 0.99
-// ms with 64, 0.65 with 128, 0.48 with 256), 128 below 16,384 (10,000: 1.57,
-// 1.19, 1.02; BA n = 2,000: 0.26, 0.20, 0.23).  Where no row is longer than a
-// wave the levels are narrow and one wave each does from 2,048 on (4-neighbour
-// grid 128 x 128, 10,000 samples: 15.3, 19.3, 24.2).  So also where the memory cap or the budget
-// leaves fewer slots than fill the device: 128 below 3,072 slots, 256 below
-// 2,048 (directed R-MAT scale 22, 1,524 slots, 2.7M samples a
-// launch: 405 ms with 64 threads, 321 with 128, 298 with 256).
+// Slots that a launch may have by the rules of memory alone, whatever else is
+// allocated.  Up to `lean` of them may take half of the device, or the whole
+// budget.  More hide more latency but leave less memory to whatever is
+// allocated next, so they may take three eighths of the device, or an eighth
+// of the budget.
+static size_t slots_allowed(centra_ctx* ctx, size_t per_slot, uint32_t lean) {
+  const size_t cap = slot_mem_cap(ctx), most = ctx->budget && ctx->budget < cap ? ctx->budget : cap;
+  const size_t room = ctx->budget ? std::min(cap / 4 * 3, ctx->budget / 8) : cap / 4 * 3;
+  return std::max(std::min<size_t>(lean, most / per_slot), room / per_slot);
+}
+
+// Variant choice.  Default: one wave per BFS where there are many (most BFSs
+// are short chains of dependent steps; a wave needs no barrier, and 4,096 of
+// them hide each other's trips to memory).  Where there are few, more threads
+// each end the longest of them sooner: 256 below 2,048 samples, 128 below
+// 32,768.  Where memory holds fewer slots, more threads each use them better:
+// 128 below 4,096 slots, 256 below 2,048.  Measured, ms with 64 / 128 / 256
+// threads:
+//   BA n = 10^6, 1,024 samples: 0.49 / 0.34 / 0.28; 16,384: 1.48 / 1.25 /
+//   1.28; 32,768: 2.26 / 2.07 / 2.39; 131,072: 6.2 / 6.9 / 8.7
+//   BA n = 10^5, 16,384: 0.52 / 0.54 / 0.71; 65,536: 1.19 / 1.61 / 2.41
+//   directed R-MAT scale 20, 16,384: 3.5 / 1.9 / 1.5; 32,768: 4.5 / 2.7 / 2.2
+//   BA of more nodes, 200,000 samples, 3,072 slots (64 threads; 128 have
+//   2,048, 256 1,024): 18.0 / 16.1 / 19.0; 1,902 slots: 31.6 / 22.3 / 23.3;
+//   1,272: 52 / 35 / 29; 955: 74 / 50 / 35
+//   directed R-MAT scale 22, 1,814 slots, 500,000 samples: 83 / 53 / 45.
+// On small graphs of short rows a level has at most some hundred nodes, and
+// one wave each does from 4,096 samples on (kNarrowNodes, kNarrowRow): grid 128
+// x 128, 2,048 samples: 3.5 / 3.1 / 3.4, 4,096: 4.2 / 4.7 / 5.6, 16,384: 11.5
+// / 13.9 / 17.8; random 4-regular, n = 4,000, 8,192: 0.38 / 0.40 / 0.55.  Not
+// on larger graphs (grid 256 x 256, 8,192: 29 / 24 / 28; 4-regular, n = 10^5:
+// 4.1 / 3.2 / 2.7) nor with longer rows (16-regular, n = 16,000, 8,192: 0.34 /
+// 0.29 / 0.33), be they in-rows alone (8 out-arcs, in-rows of up to 4,484, n =
+// 16,000: 2.3 / 1.2 / 0.7).
 // CENTRA_SAMPLER_VARIANT selects another: "lds" (exact LDS bitmap, 1024
 // threads, when the bitmap fits), "hbm512", "hbm256", "hbm128", "hbm64" (LDS
 // filter, that many threads).
-static SamplePlan plan_for(centra_ctx* ctx, uint32_t n, uint32_t count, uint32_t max_degree, int block_override = 0) {
+constexpr uint32_t kFewSamples = 2048, kManySamples = 32768, kManyNarrow = 4096;
+constexpr uint32_t kNarrowNodes = 32768, kNarrowRow = 8;
+constexpr size_t kFewSlots = 2048, kManySlots = 4096;
+
+// max_row: the longest row of the graph in either direction.
+static SamplePlan plan_for(centra_ctx* ctx, uint32_t n, uint32_t count, uint32_t max_row, int block_override = 0) {
   SamplePlan p{};
   p.bit_words = (n + 31) / 32;
   int max_lds = 0, cus = 0;
@@ -77,11 +104,10 @@ static SamplePlan plan_for(centra_ctx* ctx, uint32_t n, uint32_t count, uint32_t
     cus = 256;
   const size_t dyn = size_t(p.bit_words) * 4;
   const char* env = getenv("CENTRA_SAMPLER_VARIANT");
-  const size_t cap = slot_mem_cap(ctx);
-  const size_t most = (ctx->budget && ctx->budget < cap ? ctx->budget : cap) / slot_bytes(n);
+  const size_t slots = slots_allowed(ctx, slot_bytes(n), kLeanSlots);
   const char* v = env ? env : "";
-  const uint32_t many = max_degree <= kWave ? 2048 : 16384;   // samples from which one wave each is enough
-  p.block = most < 2048 || count < 2048 ? 256 : most < 3072 || count < many ? 128 : 64;
+  const uint32_t many = n <= kNarrowNodes && max_row <= kNarrowRow ? kManyNarrow : kManySamples;
+  p.block = slots < kFewSlots || count < kFewSamples ? 256 : slots < kManySlots || count < many ? 128 : 64;
   if (!strcmp(v, "hbm64")) p.block = 64;
   if (!strcmp(v, "hbm512")) p.block = 512;
   if (!strcmp(v, "hbm256")) p.block = 256;
@@ -102,31 +128,29 @@ static SamplePlan plan_for(centra_ctx* ctx, uint32_t n, uint32_t count, uint32_t
 }
 
 // Slots for a launch that has a use for `want`, where the state held now
-// takes `have` bytes.  Up to `lean` of them may take half of the device.
-// More hide more latency but leave less memory to whatever is allocated
-// next, so they are only taken without a budget, and while the state stays
-// within three eighths of the device and three eighths remain free.  (A
-// context that draws from both samplers on n = 2 10^6 would otherwise ask for
-// the whole device.)
+// takes `have` bytes: as many as the rules allow, more than `lean` of them
+// only while three eighths of the device remain free (a context that draws
+// from both samplers on n = 2 10^6 would otherwise ask for the whole device),
+// and no more than the budget holds.
 uint32_t slots_that_fit(centra_ctx* ctx, size_t per_slot, uint32_t want, uint32_t lean, size_t have) {
-  const size_t most = slot_mem_cap(ctx) / per_slot;
-  if (want > most) want = most ? static_cast<uint32_t>(most) : 1u;
+  const size_t most = std::max<size_t>(1, slots_allowed(ctx, per_slot, lean));
+  if (want > most) want = static_cast<uint32_t>(most);
   if (ctx->budget) {
     const size_t others = ctx->allocated - have;
     auto fits = [&](uint32_t slots) { return others + size_t(slots) * per_slot <= ctx->budget; };
-    uint32_t slots = want < lean ? want : lean;
+    uint32_t slots = want;
     if (!fits(slots))
       for (slots = lean; slots > 1 && !fits(slots);) slots /= 2;
     return slots < want ? slots : want;
   }
   if (want > lean) {
-    const size_t share = slot_mem_cap(ctx) / 4 * 3;
     size_t free_b = 0, total_b = 0;
     if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
       (void)hipGetLastError();
       return lean;
     }
-    const size_t room = free_b + have > share ? std::min(share, free_b + have - share) : 0;
+    const size_t keep = slot_mem_cap(ctx) / 4 * 3;
+    const size_t room = free_b + have > keep ? free_b + have - keep : 0;
     want = std::max<uint32_t>(lean, std::min<size_t>(want, room / per_slot));
   }
   return want;
@@ -400,15 +424,16 @@ static int second_launch(centra_ctx* ctx, SampleArgs& a, uint32_t n, hipStream_t
 // Runs one sampling launch of `count` work items into the staging area
 // (redrawn with a larger area if it overflows); `a` holds the graph part of
 // the arguments (or the instance table of a fused launch), `max_n` the
-// largest n of its graphs.  *total receives the staged node count.
+// largest n of its graphs, `max_row` their longest row in either direction.
+// *total receives the staged node count.
 // async_cap != 0: stream-ordered form; the staging area holds async_cap
 // entries, the launch is not redrawn, nothing is read back (the caller
 // learns the size from the device).
-static int launch_sampler(centra_ctx* ctx, SampleArgs a, uint32_t count, uint32_t max_n, bool multi, int block,
-                          uint64_t* total, hipStream_t s, uint64_t async_cap = 0) {
+static int launch_sampler(centra_ctx* ctx, SampleArgs a, uint32_t count, uint32_t max_n, uint32_t max_row, bool multi,
+                          int block, uint64_t* total, hipStream_t s, uint64_t async_cap = 0) {
   int rc;
   *total = 0;
-  const SamplePlan plan = plan_for(ctx, max_n, count, a.max_out_deg, multi ? block : 0);
+  const SamplePlan plan = plan_for(ctx, max_n, count, max_row, multi ? block : 0);
   uint32_t want = count < plan.resident ? count : plan.resident;
   bool fresh = false;
   if ((rc = ensure_slots(ctx, max_n, want, s, &fresh))) return rc;
@@ -521,6 +546,8 @@ static int launch_sampler(centra_ctx* ctx, SampleArgs a, uint32_t count, uint32_
   return fail(ctx, CENTRA_EHIP, "sample_paths: staging did not converge");
 }
 
+static uint32_t longest_row(const centra_graph* g) { return std::max(g->max_in_degree, g->max_out_degree); }
+
 int sample_to_stage(centra_ctx* ctx, const centra_graph* g, uint64_t seed, uint32_t instance, uint64_t first,
                     uint32_t count, uint32_t* st_out, uint32_t* dist_out, uint64_t* total, hipStream_t s) {
   *total = 0;
@@ -541,7 +568,7 @@ int sample_to_stage(centra_ctx* ctx, const centra_graph* g, uint64_t seed, uint3
   a.first = first;
   a.st_out = st_out;
   a.dist_out = dist_out;
-  return launch_sampler(ctx, a, count, g->n, false, 0, total, s);
+  return launch_sampler(ctx, a, count, g->n, longest_row(g), false, 0, total, s);
 }
 
 int sample_multi_to_stage(centra_ctx* ctx, const MultiSampleItem* items, uint32_t n_items, int block,
@@ -550,7 +577,7 @@ int sample_multi_to_stage(centra_ctx* ctx, const MultiSampleItem* items, uint32_
   std::vector<SampleInst> tab;
   std::vector<uint32_t> off;
   uint64_t count = 0;
-  uint32_t max_n = 0;
+  uint32_t max_n = 0, max_row = 0;
   for (uint32_t i = 0; i < n_items; ++i) {
     const MultiSampleItem& it = items[i];
     if (it.count == 0) continue;
@@ -571,7 +598,8 @@ int sample_multi_to_stage(centra_ctx* ctx, const MultiSampleItem* items, uint32_
     tab.push_back(x);
     off.push_back(static_cast<uint32_t>(count));
     count += it.count;
-    if (g->n > max_n) max_n = g->n;
+    max_n = std::max(max_n, g->n);
+    max_row = std::max(max_row, longest_row(g));
   }
   if (count == 0) return CENTRA_OK;
   if (count >= (1ull << 32)) return fail(ctx, CENTRA_ENOTSUP, "sample_multi: 2^32 work items or more");
@@ -587,7 +615,7 @@ int sample_multi_to_stage(centra_ctx* ctx, const MultiSampleItem* items, uint32_
   a.inst = reinterpret_cast<const SampleInst*>(dtab);
   a.item_off = reinterpret_cast<const uint32_t*>(dtab + off_at);
   a.n_inst = static_cast<uint32_t>(tab.size());
-  rc = launch_sampler(ctx, a, static_cast<uint32_t>(count), max_n, true, block, total, s);
+  rc = launch_sampler(ctx, a, static_cast<uint32_t>(count), max_n, max_row, true, block, total, s);
   CENTRA_HIP(ctx, hipStreamSynchronize(s));   // the host tables above go out of scope
   return rc;
 }
@@ -620,7 +648,7 @@ __global__ void k_stage_append(uint32_t count, const uint64_t* stage_pos, const 
 }
 
 int sample_reserve(centra_ctx* ctx, const centra_graph* g, uint32_t count, uint64_t stage_entries, hipStream_t s) {
-  const SamplePlan plan = plan_for(ctx, g->n, count, g->max_out_degree);
+  const SamplePlan plan = plan_for(ctx, g->n, count, longest_row(g));
   const uint32_t want = count < plan.resident ? count : plan.resident;
   int rc;
   bool fresh = false;   // no placement search here: there is no launch to time
@@ -651,7 +679,7 @@ int sample_append(centra_ctx* ctx, const centra_graph* g, uint64_t seed, uint32_
   a.instance = instance;
   a.first = first;
   uint64_t total = 0;
-  int rc = launch_sampler(ctx, a, count, g->n, false, 0, &total, s, he_cap ? he_cap : 1);
+  int rc = launch_sampler(ctx, a, count, g->n, longest_row(g), false, 0, &total, s, he_cap ? he_cap : 1);
   if (rc) return rc;
   uint32_t* len = static_cast<uint32_t*>(ctx->stage_len.ptr);
   uint64_t* rel = reinterpret_cast<uint64_t*>(static_cast<char*>(ctx->stage_len.ptr) + ((size_t(count) * 4 + 7) & ~size_t(7)));

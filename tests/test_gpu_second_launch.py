@@ -48,7 +48,6 @@ def test_many_deferred(wide_nodes, monkeypatch):
                 # searches were left and drawn again, at most a few of them device-wide
                 assert x[4].arcs > want[4].arcs if wide_nodes is None else x[4].wide > 8
                 assert wide_nodes is not None or x[4].wide <= 8
-            assert got[0][4].arcs == got[1][4].arcs and got[0][4].wide == got[1][4].wide
             for i, w in zip(range(0, count, 97), oracle_paths(g, 5, 0, range(0, count, 97), dg.info()[1])):
                 assert np.array_equal(want[1][int(want[0][i]):int(want[0][i + 1])], w[0])
         finally:
