@@ -179,7 +179,6 @@ struct centra_engine {
 
 namespace centra {
 
-static constexpr int kDefaultBlock = 64;       // threads per BFS of the fused sampling launches
 static constexpr uint32_t kRoundChunk = 8;   // greedy rounds per captured graph
 
 static size_t pool_bytes(const EnginePool& p) {
@@ -252,8 +251,7 @@ static int sample_pools(centra_engine* e, const std::vector<uint32_t>& want_leve
   hipEvent_t* ev = ctx->ev;
   CENTRA_HIP(ctx, hipEventRecord(ev[0], s));
   uint64_t total = 0;
-  const int block = e->tuned_block ? e->tuned_block : kDefaultBlock;
-  int rc = sample_multi_to_stage(ctx, items.data(), static_cast<uint32_t>(items.size()), block, &total, s);
+  int rc = sample_multi_to_stage(ctx, items.data(), static_cast<uint32_t>(items.size()), e->tuned_block, &total, s);
   if (rc) return rc;
   uint64_t count = 0;
   std::vector<uint32_t> item_off;
@@ -374,8 +372,9 @@ static int build_level(centra_engine* e, EnginePool& p, uint32_t j, hipStream_t 
 // Autotuner: times the fused sampling launch of a probe batch (the first
 // samples of every pool) with workgroups of 64, 128 and 256 threads, the
 // best of two timed launches after one that pays the slot set-up, and keeps
-// the fastest unless it beats the default 64 by under 2% (differences within
-// the probe's noise did not carry over to full launches).  The probe's
+// the fastest unless it beats the untuned choice for large launches by under
+// 2% (differences within the probe's noise did not carry over to full
+// launches).  The probe's
 // samples are the pools' own, and every variant draws the same hyperedges,
 // so the choice changes no result.  CENTRA_TUNE_CACHE names a file of
 // "key block" lines that keeps choices across runs.
@@ -410,7 +409,8 @@ static int autotune(centra_engine* e, hipStream_t s) {
   }
   const int blocks[] = {64, 128, 256};
   float best_ms = 0.f, default_ms = 0.f;
-  int best = kDefaultBlock;
+  const int untuned = fused_threads(ctx, probe.data(), static_cast<uint32_t>(probe.size()));
+  int best = untuned;
   std::string line = std::string("autotune: ") + key + ":";
   for (int b : blocks) {
     uint64_t total = 0;
@@ -423,13 +423,13 @@ static int autotune(centra_engine* e, hipStream_t s) {
       if (rep == 1 || (rep > 1 && t < ms)) ms = t;
     }
     line += " " + std::to_string(b) + "=" + std::to_string(ms) + "ms";
-    if (b == kDefaultBlock) default_ms = ms;
+    if (b == untuned) default_ms = ms;
     if (best_ms == 0.f || ms < best_ms) {
       best_ms = ms;
       best = b;
     }
   }
-  if (best != kDefaultBlock && default_ms > 0.f && best_ms > 0.98f * default_ms) best = kDefaultBlock;
+  if (best != untuned && default_ms > 0.f && best_ms > 0.98f * default_ms) best = untuned;
   e->tuned_block = best;
   e->log += line + " -> block " + std::to_string(best) + "\n";
   if (cache)

@@ -215,6 +215,9 @@ struct MultiSampleItem {
   uint64_t first;
   uint32_t count;
 };
+// The threads per BFS of a large fused launch over these graphs.
+int fused_threads(centra_ctx* ctx, const MultiSampleItem* items, uint32_t n_items);
+// block: threads per BFS (0: by the rule of the sampler's launches)
 int sample_multi_to_stage(centra_ctx* ctx, const MultiSampleItem* items, uint32_t n_items, int block,
                           uint64_t* total, hipStream_t s);
 

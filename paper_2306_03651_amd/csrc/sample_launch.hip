@@ -86,15 +86,43 @@ static size_t slots_allowed(centra_ctx* ctx, size_t per_slot, uint32_t lean) {
 // 4.1 / 3.2 / 2.7) nor with longer rows (16-regular, n = 16,000, 8,192: 0.34 /
 // 0.29 / 0.33), be they in-rows alone (8 out-arcs, in-rows of up to 4,484, n =
 // 16,000: 2.3 / 1.2 / 0.7).
-// CENTRA_SAMPLER_VARIANT selects another: "lds" (exact LDS bitmap, 1024
-// threads, when the bitmap fits), "hbm512", "hbm256", "hbm128", "hbm64" (LDS
-// filter, that many threads).
+// A fused launch leaves no sample for after it, so its longest BFS holds it:
+// 128 threads also where the graphs are skewed, which long rows tell (directed
+// R-MAT scale 20, 2 x 40,000 samples: 80 / 47 / 25; directed, n = 10^5, rows
+// of up to 15,887, 40,000: 29 / 16 / 11; BA n = 10^6, rows of up to 3,560,
+// 400,000: 20.0 / 21.6 / 28.1; BA n = 10^5, rows of up to 1,134: 7.1 / 10.0 /
+// 15.1).
+// CENTRA_SAMPLER_VARIANT selects another for single-graph launches: "lds"
+// (exact LDS bitmap, 1024 threads, when the bitmap fits), "hbm512", "hbm256",
+// "hbm128", "hbm64" (LDS filter, that many threads).
 constexpr uint32_t kFewSamples = 2048, kManySamples = 32768, kManyNarrow = 4096;
 constexpr uint32_t kNarrowNodes = 32768, kNarrowRow = 8;
 constexpr size_t kFewSlots = 2048, kManySlots = 4096;
+constexpr uint32_t kSkewedRow = 2048;
 
-// max_row: the longest row of the graph in either direction.
-static SamplePlan plan_for(centra_ctx* ctx, uint32_t n, uint32_t count, uint32_t max_row, int block_override = 0) {
+// max_row: the longest row of the graph (of a fused launch's graphs) in either
+// direction.
+static int threads_for(centra_ctx* ctx, uint32_t n, uint64_t count, uint32_t max_row, bool multi) {
+  const size_t slots = slots_allowed(ctx, slot_bytes(n), kLeanSlots);
+  if (slots < kFewSlots || count < kFewSamples) return 256;
+  const uint32_t many = n <= kNarrowNodes && max_row <= kNarrowRow ? kManyNarrow : kManySamples;
+  return slots < kManySlots || count < many || (multi && max_row > kSkewedRow) ? 128 : 64;
+}
+
+static uint32_t longest_row(const centra_graph* g) { return std::max(g->max_in_degree, g->max_out_degree); }
+
+int fused_threads(centra_ctx* ctx, const MultiSampleItem* items, uint32_t n_items) {
+  uint32_t n = 1, max_row = 0;
+  for (uint32_t i = 0; i < n_items; ++i) {
+    n = std::max(n, items[i].g->n);
+    max_row = std::max(max_row, longest_row(items[i].g));
+  }
+  return threads_for(ctx, n, ~0ull, max_row, true);
+}
+
+// multi: a fused launch; block: its threads per BFS if the caller chose them.
+static SamplePlan plan_for(centra_ctx* ctx, uint32_t n, uint32_t count, uint32_t max_row, bool multi = false,
+                           int block = 0) {
   SamplePlan p{};
   p.bit_words = (n + 31) / 32;
   int max_lds = 0, cus = 0;
@@ -104,22 +132,16 @@ static SamplePlan plan_for(centra_ctx* ctx, uint32_t n, uint32_t count, uint32_t
     cus = 256;
   const size_t dyn = size_t(p.bit_words) * 4;
   const char* env = getenv("CENTRA_SAMPLER_VARIANT");
-  const size_t slots = slots_allowed(ctx, slot_bytes(n), kLeanSlots);
-  const char* v = env ? env : "";
-  const uint32_t many = n <= kNarrowNodes && max_row <= kNarrowRow ? kManyNarrow : kManySamples;
-  p.block = slots < kFewSlots || count < kFewSamples ? 256 : slots < kManySlots || count < many ? 128 : 64;
+  const char* v = env && !multi ? env : "";
+  p.block = block ? block : threads_for(ctx, n, count, max_row, multi);
   if (!strcmp(v, "hbm64")) p.block = 64;
   if (!strcmp(v, "hbm512")) p.block = 512;
   if (!strcmp(v, "hbm256")) p.block = 256;
   if (!strcmp(v, "hbm128")) p.block = 128;
   p.lds_bits = !strcmp(v, "lds") && sample_lds_variant_bytes() + dyn <= size_t(max_lds);
-  if (block_override) {   // fused launches: an LDS-filter variant chosen by the caller
-    p.block = block_override;
-    p.lds_bits = false;
-  }
   int per_cu = 0;
   p.dyn_lds = p.lds_bits ? dyn : 0;
-  hipError_t e = sample_kernel_occupancy(p.block, p.lds_bits, block_override != 0, p.dyn_lds, &per_cu);
+  hipError_t e = sample_kernel_occupancy(p.block, p.lds_bits, multi, p.dyn_lds, &per_cu);
   if (e != hipSuccess || per_cu <= 0) per_cu = 1;
   (void)hipGetLastError();
   const uint64_t r = uint64_t(cus) * uint64_t(per_cu);
@@ -433,7 +455,7 @@ static int launch_sampler(centra_ctx* ctx, SampleArgs a, uint32_t count, uint32_
                           int block, uint64_t* total, hipStream_t s, uint64_t async_cap = 0) {
   int rc;
   *total = 0;
-  const SamplePlan plan = plan_for(ctx, max_n, count, max_row, multi ? block : 0);
+  const SamplePlan plan = plan_for(ctx, max_n, count, max_row, multi, block);
   uint32_t want = count < plan.resident ? count : plan.resident;
   bool fresh = false;
   if ((rc = ensure_slots(ctx, max_n, want, s, &fresh))) return rc;
@@ -545,8 +567,6 @@ static int launch_sampler(centra_ctx* ctx, SampleArgs a, uint32_t count, uint32_
   }
   return fail(ctx, CENTRA_EHIP, "sample_paths: staging did not converge");
 }
-
-static uint32_t longest_row(const centra_graph* g) { return std::max(g->max_in_degree, g->max_out_degree); }
 
 int sample_to_stage(centra_ctx* ctx, const centra_graph* g, uint64_t seed, uint32_t instance, uint64_t first,
                     uint32_t count, uint32_t* st_out, uint32_t* dist_out, uint64_t* total, hipStream_t s) {
