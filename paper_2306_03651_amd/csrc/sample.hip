@@ -552,8 +552,8 @@ __device__ __forceinline__ uint32_t append(bool has, uint32_t v, uint32_t le, co
 // of a table with no more slots than a round has arcs the last entries take
 // hundreds of probes each, and those were most of a flooding BFS's time
 // (directed, n = 10^5, 8 out-arcs each, long in-rows, 20,000 samples, all on
-// their workgroups: 64 threads 33.7 ms -> 17, 128 22.3 -> 11, 256 19.6 -> 7,
-// 512 12.1 -> 5.2).
+// their workgroups: 64 threads 33.7 -> 16.8 ms, 128 22.3 -> 10.2, 256 19.6 ->
+// 5.9, 512 12.1 -> 4.7).
 template <int BLOCK>
 struct Dups {
   static constexpr uint32_t kSlots = Round<BLOCK>::kSlots;
@@ -562,24 +562,12 @@ struct Dups {
   const Visited& vis;
   uint32_t n;   // nodes in the table (workgroups of one wave)
 
-  // Looks up the nodes v[k] in slots i[k] (kUnseen: none; every entry of the
-  // table is some thread's).
+  // Nodes v[k] with places p[k] (0: none) and sums x[k]: adds the sum to the
+  // count of a node of the new level, claims an unvisited one with it.
   template <int N>
-  __device__ __forceinline__ void look_up(const uint32_t (&v)[N], const uint32_t (&i)[N], uint32_t le, uint32_t* q,
-                                          uint32_t& qn, uint64_t& mx, uint64_t& added) {
-    uint32_t p[N];
-    uint64_t x[N], old[N];
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-      p[k] = 0;
-      x[k] = 0;
-      if (i[k] != kUnseen) {
-        x[k] = sh.dsum[i[k]];
-        sh.dkey[i[k]] = kUnseen;
-        sh.dsum[i[k]] = 0;
-        p[k] = vis.place(v[k]);
-      }
-    }
+  __device__ __forceinline__ void settle(const uint32_t (&v)[N], const uint32_t (&p)[N], const uint64_t (&x)[N],
+                                         uint32_t le, uint32_t* q, uint32_t& qn, uint64_t& mx, uint64_t& added) {
+    uint64_t old[N];
 #pragma unroll
     for (int k = 0; k < N; ++k) old[k] = p[k] >= le && p[k] != kUnseen ? wg_ld_u64(&vis.sig[p[k]]) : 0ull;
 #pragma unroll
@@ -595,75 +583,60 @@ struct Dups {
     }
     __syncthreads();   // the table is empty, the counts are in place
   }
-  // Adds c for node v; returns its slot if it was not in the table, else
-  // kUnseen.  (A round enters at most as many nodes as the table has slots,
-  // so a free one is found.)
-  __device__ __forceinline__ uint32_t put(uint32_t v, uint64_t c) {
-    uint32_t h = __umulhi(v * 0x9E3779B1u, kSlots);
+  // Adds c for node v; true if it was not in the table, *slot its place there.
+  // (A round enters at most as many nodes as the table has slots, so a free
+  // one is found.)
+  __device__ __forceinline__ bool put(uint32_t v, uint64_t c, uint32_t* slot = nullptr) {
+    uint32_t h = static_cast<uint32_t>(uint64_t(v * 0x9E3779B1u) * kSlots >> 32);
     uint32_t was;
     for (;;) {
       was = atomicCAS(&sh.dkey[h], kUnseen, v);
       if (was == kUnseen || was == v) break;
-      h = h + 1 == kSlots ? 0u : h + 1;
+      h = (h + 1) % kSlots;
     }
     atomicAdd(reinterpret_cast<unsigned long long*>(&sh.dsum[h]), static_cast<unsigned long long>(c));
-    return was == kUnseen ? h : kUnseen;
+    if (slot) *slot = h;
+    return was == kUnseen;
   }
-  // A round's arcs: bit k of dup set, node v[k] with contribution c[k] (all
-  // clear for no round); last: no round follows in the level.  Uniform.
-  __device__ __forceinline__ void round(uint32_t dup, const uint32_t (&v)[PER], const uint64_t (&c)[PER], bool last,
-                                        uint32_t le, uint32_t* q, uint32_t& qn, uint64_t& mx, uint64_t& added) {
-    if constexpr (BLOCK == kWave) {
-      // the table is looked up before more than three quarters of it would be
-      // taken, and at the level's end
-      constexpr uint32_t kMost = kSlots - kSlots / 4;
-      constexpr int kOwn = kSlots / BLOCK;
-      uint32_t d = dup, cnt = 0;
+  // One wave: looks the table's nodes up and empties it.
+  __device__ __forceinline__ void flush(uint32_t le, uint32_t* q, uint32_t& qn, uint64_t& mx, uint64_t& added) {
+    constexpr int kOwn = kSlots / BLOCK;
+    __syncthreads();   // the entries and the new nodes are in place
+    uint32_t v[kOwn], p[kOwn];
+    uint64_t x[kOwn];
 #pragma unroll
-      for (int k = 0; k < PER; ++k) cnt += static_cast<uint32_t>(__popcll(__ballot((dup >> k) & 1u)));
-      // a round that alone would fill more than that goes in two halves
-      uint32_t later = 0, cnt_later = 0;
-      if (cnt > kMost) {
-        later = dup >> (PER / 2) << (PER / 2);
-        d = dup ^ later;
-#pragma unroll
-        for (int k = PER / 2; k < PER; ++k) cnt_later += static_cast<uint32_t>(__popcll(__ballot((dup >> k) & 1u)));
-        cnt -= cnt_later;
-      }
-      for (bool end = false;;) {   // (one place to look up and one to enter: code size)
-        if (n && (end || n + cnt > kMost)) {
-          __syncthreads();   // the entries and the new nodes are in place
-          uint32_t w[kOwn], i[kOwn];
-#pragma unroll
-          for (int k = 0; k < kOwn; ++k) {
-            i[k] = k * BLOCK + threadIdx.x;
-            w[k] = sh.dkey[i[k]];
-            if (w[k] == kUnseen) i[k] = kUnseen;
-          }
-          look_up(w, i, le, q, qn, mx, added);
-          n = 0;
-        }
-        if (end) break;
-        if (cnt) {
-          bool entered[PER];
-#pragma unroll
-          for (int k = 0; k < PER; ++k) entered[k] = ((d >> k) & 1u) && put(v[k], c[k]) != kUnseen;
-#pragma unroll
-          for (int k = 0; k < PER; ++k) n += static_cast<uint32_t>(__popcll(__ballot(entered[k])));
-        }
-        end = !cnt_later;
-        if (end && !last) break;
-        d = later;
-        cnt = cnt_later;
-        cnt_later = 0;
-      }
-    } else {
-      uint32_t i[PER];
-#pragma unroll
-      for (int k = 0; k < PER; ++k) i[k] = (dup >> k) & 1u ? put(v[k], c[k]) : kUnseen;
-      __syncthreads();   // the entries and the new nodes are in place
-      look_up(v, i, le, q, qn, mx, added);
+    for (int k = 0; k < kOwn; ++k) {
+      const uint32_t i = k * BLOCK + threadIdx.x;
+      v[k] = sh.dkey[i];
+      x[k] = sh.dsum[i];
+      sh.dkey[i] = kUnseen;
+      sh.dsum[i] = 0;
+      p[k] = v[k] != kUnseen ? vis.place(v[k]) : 0u;
     }
+    n = 0;
+    settle(v, p, x, le, q, qn, mx, added);
+  }
+  // Several waves: a round's arcs (bit k of dup set, node v[k] with
+  // contribution c[k]) entered and looked up.
+  __device__ __forceinline__ void round(uint32_t dup, const uint32_t (&v)[PER], const uint64_t (&c)[PER], uint32_t le,
+                                        uint32_t* q, uint32_t& qn, uint64_t& mx, uint64_t& added) {
+    uint32_t i[PER], p[PER];
+    uint64_t x[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+      if (!((dup >> k) & 1u) || !put(v[k], c[k], &i[k])) i[k] = kUnseen;
+    __syncthreads();   // the entries and the new nodes are in place
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      p[k] = 0;
+      x[k] = 0;
+      if (i[k] == kUnseen) continue;
+      x[k] = sh.dsum[i[k]];
+      sh.dkey[i[k]] = kUnseen;
+      sh.dsum[i[k]] = 0;
+      p[k] = vis.place(v[k]);
+    }
+    settle(v, p, x, le, q, qn, mx, added);
   }
 };
 
@@ -1141,7 +1114,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK <= 512 ? 4 : 1) void k_sample_paths(Sa
           }
           base += R;
         }
-        uint32_t dup = 0;   // bit k: arc k's target had its bit set
+        uint32_t dup = 0, n_dup = 0;   // bit k: arc k's target had its bit set
         if (!first) {
 #pragma unroll
           for (int k = 0; k < PER; ++k) {
@@ -1154,10 +1127,34 @@ __global__ __launch_bounds__(BLOCK, BLOCK <= 512 ? 4 : 1) void k_sample_paths(Sa
               mx = add[k] > mx ? add[k] : mx;
               added = sat_add(added, add[k]);
             }
-            if (arc && !fresh) dup |= 1u << k;
+            const bool again = arc && !fresh;
+            if (again) dup |= 1u << k;
+            if (BLOCK == kWave) n_dup += static_cast<uint32_t>(__popcll(__ballot(again)));
           }
         }
-        if (BLOCK == kWave || !first) dups.round(dup, v, add, !more, le, q, qn, mx, added);
+        if constexpr (BLOCK == kWave) {
+          // the table is looked up before more than kMost of its slots would
+          // be taken, and at the level's end; a round that alone would take
+          // more goes in two halves
+          constexpr uint32_t kMost = Round<BLOCK>::kSlots - Round<BLOCK>::kSlots / 8;
+          const bool many = n_dup > kMost;
+          const uint32_t later = many ? dup >> (PER / 2) << (PER / 2) : 0u;
+          dup ^= later;
+          for (bool flush = dups.n && dups.n + n_dup > kMost, half = many;;) {
+            if (flush) dups.flush(le, q, qn, mx, added);
+            bool entered[PER];
+#pragma unroll
+            for (int k = 0; k < PER; ++k) entered[k] = ((dup >> k) & 1u) && dups.put(v[k], add[k]);
+#pragma unroll
+            for (int k = 0; k < PER; ++k) dups.n += static_cast<uint32_t>(__popcll(__ballot(entered[k])));
+            dup = half ? later : 0u;
+            if (!half && !(!more && dups.n)) break;
+            half = false;
+            flush = true;
+          }
+        } else if (!first) {
+          dups.round(dup, v, add, le, q, qn, mx, added);
+        }
         if (!more) break;
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
