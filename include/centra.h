@@ -666,7 +666,10 @@ CENTRA_API int centra_progressive_resumable(centra_ctx *ctx, const centra_graph 
  * retiring certified queries and those at m_max.  realtime != 0: query
  * arrival times are seconds from the start of the run, admission waits for
  * them (continuous batching: arrivals join the running queries at the next
- * tick); realtime == 0: every query has arrived at the start (batch mode).
+ * tick; the only active query, before its next level is drawn, waits for the
+ * next arrival if that is of its pool and due within 3 ms, so that both go
+ * through the levels left together); realtime == 0: every query has arrived
+ * at the start (batch mode).
  * Admission reserves, for each pool with an active query, the memory of
  * the pool with every level of its schedule built and a greedy run's state
  * per level (projected from the mean hyperedge size of its first samples,

@@ -1074,13 +1074,13 @@ int centra_engine_submit(centra_engine* e, uint32_t pool_id, uint32_t k, uint32_
   return CENTRA_OK;
 }
 
-// In a realtime run, a tick that drew samples for one query alone lasts at
-// least this long: queries that arrive within a few ms of each other are meant
-// to share their ticks (one fused launch per level), and a lone one would
-// otherwise be through its levels before the next is there (a level takes 0.3
-// to 1.2 ms; it took 1.7 ms, so no query finishes later than it did).  Ticks
-// answered from cached levels are not held.
-constexpr double kLonePaceS = 1.5e-3;
+// In a realtime run, the query that arrives next is waited for, if it is of the
+// pool of the only active query and due this soon, before that one draws its
+// next level: they then go through the levels that are left together.  Nothing
+// else is held: the wait ends with the arrival, and a query without such a
+// neighbour goes from level to level at once (8 levels of a pool on 300 nodes:
+// 5.8 ms, 12.1 with every tick but the last drawn out to 1.5 ms).
+constexpr double kJoinS = 3e-3;
 
 int centra_engine_run(centra_engine* e, int realtime, void* stream) {
   if (!e) return CENTRA_EINVAL;
@@ -1098,13 +1098,17 @@ int centra_engine_run(centra_engine* e, int realtime, void* stream) {
     const double now = realtime ? now_s() - e->run_t0 : 1e300;
     bool progress = false;
     const uint64_t drawn = e->st.samples;
-    const double begun = now_s();
     if ((rc = tick(e, now, &progress, s))) break;
-    if (realtime && e->st.samples != drawn) {
-      uint32_t active = 0;
-      for (const EngineQuery& q : e->queries) active += q.state == 1;
-      const double rest = begun + kLonePaceS - now_s();
-      if (active == 1 && rest > 0) std::this_thread::sleep_for(std::chrono::duration<double>(rest));
+    if (realtime && e->st.samples != drawn && e->next_queued < e->queries.size()) {
+      const EngineQuery& next = e->queries[e->next_queued];
+      uint32_t active = 0, of_pool = 0;
+      for (const EngineQuery& q : e->queries) {
+        active += q.state == 1;
+        of_pool += q.state == 1 && q.pool == next.pool;
+      }
+      const double wait = next.arrival - (now_s() - e->run_t0);
+      if (active == 1 && of_pool == 1 && wait > 0 && wait <= kJoinS)
+        std::this_thread::sleep_for(std::chrono::duration<double>(wait));
     }
     if (!progress) {
       if (!realtime) {
