@@ -30,7 +30,11 @@
 // the index: a sample is one read at its rank.  A sample over arcs reads six
 // scattered lines (directory, prefix, source, target, list offset, list), and
 // those reads are what bounds it: 2M samples, undirected R-MAT scale 18, 238
-// us against 50 us with the triangles (which take 0.7 ms to lay out, once).
+// us against 50 us with the triangles.  They cost a caller of few samples
+// nothing: such an index needs no directory, whose memory alone takes longer
+// to get and to give back than the triangles take to write (index without / with
+// them, ms: scale 14, 2.8M triangles: 0.57 / 0.56; scale 18, 83M: 5.9 / 5.4;
+// scale 20, 424M: 32.0 / 31.0).
 // The first list that fits is taken; CENTRA_TRIANGLE_LIST=0 forces the walk and
 // CENTRA_TRIANGLE_LIST=compact the compact list (for tests of those paths).
 //
@@ -60,7 +64,10 @@ __device__ __forceinline__ uint32_t upper(const uint32_t* idx, uint32_t lo, uint
   return lo;
 }
 
-constexpr uint32_t kHeavy = 64;   // an arc walked by one lane has at most this many steps
+// An arc walked by one lane has at most this many steps (index of undirected
+// R-MAT scale 18 / 20, ms, with 64: 7.6 / 37.1, 32: 7.1 / 35.0, 16: 6.9 / 34.0,
+// 8: 7.0 / 34.2; the laying out as it was).
+constexpr uint32_t kHeavy = 16;
 constexpr uint64_t kDirBuckets = 1ull << 22;   // rank directory size bound (16 MB)
 
 // The two lists of arc e = (a, b): walk [w0, w1), search [s0, s1); empty
@@ -230,15 +237,36 @@ __global__ void k_tri_sample(uint32_t count, uint64_t first, uint64_t seed, uint
   he_nodes[3ull * x + 2] = c;
 }
 
-// Rank r's triangle for every r, from the list (the sampler's search; the
-// ranks ascend, so it stays in the caches).
-__global__ void k_tri_expand(uint64_t T, const uint64_t* prefix, const uint32_t* dir, uint64_t W, const uint32_t* src,
-                             const uint32_t* col_idx, const uint64_t* list_off, const uint32_t* tri_c, uint32_t* abc) {
-  for (uint64_t r = blockIdx.x * uint64_t(blockDim.x) + threadIdx.x; r < T; r += uint64_t(gridDim.x) * blockDim.x) {
-    const uint32_t e = static_cast<uint32_t>(arc_of(prefix, dir, W, 0, r));
-    abc[3 * r] = src[e];
-    abc[3 * r + 1] = col_idx[e];
-    abc[3 * r + 2] = tri_c[list_off[e] + (r - prefix[e])];
+// The triangles of arcs [kLayArcs b, kLayArcs (b + 1)) by workgroup b, a thread
+// per rank (few arcs each: consecutive arcs of a hub hold thousands).
+constexpr uint32_t kLayArcs = 64, kLayBlock = 256;
+
+__global__ __launch_bounds__(kLayBlock) void k_tri_lay(uint64_t n_arcs, const uint64_t* prefix, const uint32_t* src,
+                                                       const uint32_t* col_idx, const uint64_t* list_off,
+                                                       const uint32_t* tri_c, uint32_t* abc) {
+  __shared__ uint64_t pre[kLayArcs], off[kLayArcs];
+  __shared__ uint32_t sa[kLayArcs], sb[kLayArcs];
+  const uint64_t e0 = uint64_t(blockIdx.x) * kLayArcs, e1 = e0 + kLayArcs < n_arcs ? e0 + kLayArcs : n_arcs;
+  const uint64_t r0 = prefix[e0], r1 = prefix[e1];
+  if (r0 == r1) return;   // uniform
+  if (threadIdx.x < kLayArcs) {
+    const uint64_t e = e0 + threadIdx.x;
+    pre[threadIdx.x] = e < e1 ? prefix[e] : r1;
+    if (e < e1) {
+      off[threadIdx.x] = list_off[e];
+      sa[threadIdx.x] = src[e];
+      sb[threadIdx.x] = col_idx[e];
+    }
+  }
+  __syncthreads();
+  for (uint64_t r = r0 + threadIdx.x; r < r1; r += kLayBlock) {
+    uint32_t l = 0;   // the last with pre[l] <= r: the one that holds r
+#pragma unroll
+    for (uint32_t step = kLayArcs / 2; step; step >>= 1)
+      if (pre[l + step] <= r) l += step;
+    abc[3 * r] = sa[l];
+    abc[3 * r + 1] = sb[l];
+    abc[3 * r + 2] = tri_c[off[l] + (r - pre[l])];
   }
 }
 
@@ -343,55 +371,52 @@ int triangle_index(centra_ctx* ctx, centra_graph* g, uint64_t* T, hipStream_t s)
   }
   ctx->err.clear();   // a refused list is not an error: samples walk instead
   g->tri_dir_w = 0;
-  if (total) {
-    // the rank directory (optional: without it samples search the whole prefix)
-    // Test hook: CENTRA_TRIANGLE_DIR_BUCKETS lowers the bucket bound, so
-    // that small graphs get buckets wider than one rank.
-    uint64_t max_buckets = kDirBuckets;
-    if (const char* nb_env = getenv("CENTRA_TRIANGLE_DIR_BUCKETS")) {
-      const unsigned long long v = strtoull(nb_env, nullptr, 0);
-      if (v >= 1 && v < max_buckets) max_buckets = v;
-    }
-    const uint64_t W = (total + max_buckets - 1) / max_buckets;
-    const uint64_t nb = (total + W - 1) / W;
-    if (A < (1ull << 32) && ensure(ctx, g->tri_dir, (nb + 1) * 4, false, s) == CENTRA_OK) {
-      hipLaunchKernelGGL(k_tri_dir, grid_a, dim3(256), 0, s, A, prefix, total, W, nb,
-                         static_cast<uint32_t*>(g->tri_dir.ptr));
-      if (hipGetLastError() == hipSuccess && hipStreamSynchronize(s) == hipSuccess) {
-        g->tri_dir_w = W;
-      } else {
-        release(ctx, g->tri_dir);
-        ctx->err.clear();
-        (void)hipGetLastError();
-      }
+  // Test hook: CENTRA_TRIANGLE_DIR_BUCKETS lowers the directory's bucket
+  // bound, so that small graphs get buckets wider than one rank.
+  uint64_t max_buckets = kDirBuckets;
+  const char* nb_env = getenv("CENTRA_TRIANGLE_DIR_BUCKETS");
+  if (nb_env) {
+    const unsigned long long v = strtoull(nb_env, nullptr, 0);
+    if (v >= 1 && v < max_buckets) max_buckets = v;
+  }
+  const uint64_t W = total ? (total + max_buckets - 1) / max_buckets : 1;
+  const uint64_t nb = (total + W - 1) / W;
+  // The triangles themselves, where the test hooks ask for no other path.
+  // Under a budget they must not take more than what they replace.
+  const size_t list_b = g->tri_c.bytes + g->tri_cap.bytes + (nb + 1) * 4 + g->tri_src.bytes + g->tri_prefix.bytes;
+  if (list && total && A < (1ull << 32) && !mode && !nb_env && total * 12 <= room &&
+      (!ctx->budget || total * 12 <= list_b) && ensure(ctx, g->tri_abc, total * 12, false, s) == CENTRA_OK) {
+    hipLaunchKernelGGL(k_tri_lay, dim3(static_cast<unsigned>((A + kLayArcs - 1) / kLayArcs)), dim3(kLayBlock), 0, s, A,
+                       static_cast<const uint64_t*>(prefix), static_cast<const uint32_t*>(src), g->col_idx, list_off,
+                       static_cast<const uint32_t*>(list), static_cast<uint32_t*>(g->tri_abc.ptr));
+    if (hipGetLastError() == hipSuccess && hipStreamSynchronize(s) == hipSuccess) {
+      // a large list goes; a small one, and what is kept by arc (20 bytes
+      // each), only under a budget: giving them back takes longer (1 ms at
+      // scale 18) than laying out
+      DevBuf* old[] = {&g->tri_c, &g->tri_cap, &g->tri_src, &g->tri_prefix};
+      for (DevBuf* b : old)
+        if (ctx->budget || (b == &g->tri_c && b->bytes > total_b / 1024)) release(ctx, *b);
+      list_off = nullptr;
     } else {
-      ctx->err.clear();
+      release(ctx, g->tri_abc);
+      (void)hipGetLastError();
+    }
+  }
+  if (total && !g->tri_abc.ptr && A < (1ull << 32) && ensure(ctx, g->tri_dir, (nb + 1) * 4, false, s) == CENTRA_OK) {
+    // the rank directory (optional: without it samples search the whole prefix)
+    hipLaunchKernelGGL(k_tri_dir, grid_a, dim3(256), 0, s, A, prefix, total, W, nb,
+                       static_cast<uint32_t*>(g->tri_dir.ptr));
+    if (hipGetLastError() == hipSuccess && hipStreamSynchronize(s) == hipSuccess) {
+      g->tri_dir_w = W;
+    } else {
+      release(ctx, g->tri_dir);
+      (void)hipGetLastError();
     }
   }
   if (total == 0) {
     release(ctx, g->tri_c);
     release(ctx, g->tri_cap);
     list_off = nullptr;
-  }
-  // The triangles themselves, where the test hooks ask for no other path.
-  // Under a budget they must not take more than what they replace.
-  const size_t list_b = g->tri_c.bytes + g->tri_cap.bytes + g->tri_dir.bytes + g->tri_src.bytes + g->tri_prefix.bytes;
-  if (list && total && g->tri_dir_w && !mode && !getenv("CENTRA_TRIANGLE_DIR_BUCKETS") && total * 12 <= room &&
-      (!ctx->budget || total * 12 <= list_b) && ensure(ctx, g->tri_abc, total * 12, false, s) == CENTRA_OK) {
-    const uint64_t blocks = (total + 255) / 256;
-    hipLaunchKernelGGL(k_tri_expand, dim3(static_cast<unsigned>(blocks < 65536 ? blocks : 65536)), dim3(256), 0, s,
-                       total, static_cast<const uint64_t*>(prefix), static_cast<const uint32_t*>(g->tri_dir.ptr),
-                       g->tri_dir_w, static_cast<const uint32_t*>(src), g->col_idx, list_off,
-                       static_cast<const uint32_t*>(list), static_cast<uint32_t*>(g->tri_abc.ptr));
-    if (hipGetLastError() == hipSuccess && hipStreamSynchronize(s) == hipSuccess) {
-      DevBuf* old[] = {&g->tri_c, &g->tri_cap, &g->tri_dir, &g->tri_src, &g->tri_prefix};
-      for (DevBuf* b : old) release(ctx, *b);
-      g->tri_dir_w = 0;
-      list_off = nullptr;
-    } else {
-      release(ctx, g->tri_abc);
-      (void)hipGetLastError();
-    }
   }
   ctx->err.clear();
   g->tri_list_off = list_off;
