@@ -368,10 +368,11 @@ CENTRA_API int centra_check(centra_ctx *ctx, void *stream);
  * of a workgroup's share, at least 2^17 and 1/128 of the graph's arcs, at
  * most 2^21; a flood of a skewed graph's reachable set; long narrow searches
  * such as grids stay), is left by its workgroup and redrawn after the launch
- * (same hyperedge): up to 8 such samples by a device-wide BFS each, level by
- * level with the whole GPU, more of them by a second launch with 512 threads
- * each, from which those past a budget of 2^21 entries or with wider levels
- * go to the device-wide BFS.  kernel_ms, arcs and nodes are those of the
+ * (same hyperedge): up to 8 such samples, or more if that is estimated to be
+ * the shorter way, by a device-wide BFS each, level by level with the whole
+ * GPU; others by a second launch with 512 threads each, from which those past
+ * its budget (2^17 to 2^21 entries) or with wider levels go to the
+ * device-wide BFS.  kernel_ms, arcs and nodes are those of the
  * workgroup kernel (both launches, the partial work of BFSs that were left
  * included); `wide` counts the device-wide BFSs, wide_ms is their wall time
  * (launches and the per-level synchronisation) and wide_arcs the CSR entries

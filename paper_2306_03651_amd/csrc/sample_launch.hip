@@ -223,22 +223,32 @@ static int ensure_slots(centra_ctx* ctx, uint32_t gn, uint32_t want, hipStream_t
 // samples, three BFSs of some 2 million entries each: 28.6 ms with the
 // largest budget, 14.0 with this one.)
 //
-// Up to kWideFew of them go through the device-wide BFS (wide_samples in
-// sample.hip), which takes the whole GPU for each, 0.3 ms (n = 10^5) to 2.4
-// (n = 4 10^6), so the budget is also at least a share of the graph's arcs
-// (R-MAT scale 22, 20,000 samples: 9.2 ms without, 4.0 with; an eighth less of
-// it is as good, twice as much costs scale 20 a ninth).  More of them, of
-// graphs where many BFSs are long, are drawn by a second launch with
-// kSecondBlock threads each, from which only those past the largest budget go
-// to the device-wide BFS.  (BA n = 10^6 of 2 edges per node, 100,000 samples,
-// 1,240 deferred: 1,080 ms all device-wide, 47 with the second launch, 56 with
-// the largest budget; 256 threads in the second launch 49.)
+// A few of them go through the device-wide BFS (wide_samples in sample.hip),
+// which takes the whole GPU for each, 0.2 ms (n = 65,536) to 2.4 (n = 4 10^6),
+// so the budget is also at least a share of the graph's arcs (R-MAT scale 22,
+// 20,000 samples: 9.2 ms without, 4.0 with; half the share as good, twice as
+// much costs scale 20 a ninth).  More of them, of graphs where many BFSs are
+// long, are drawn by a second launch with kSecondBlock threads each, from which
+// only those past its budget go to the device-wide BFS.  (BA n = 10^6 of 2
+// edges per node, 100,000 samples, 1,240 deferred: 1,080 ms all device-wide, 47
+// with the second launch, 56 with the largest budget in the first; 256 threads
+// in the second launch 49.)
+//
+// Where both are near, the second launch is a bet: it takes up to 4.5 ns per
+// entry of its budget, and gains nothing on floods that end on the device-wide
+// BFS all the same (undirected R-MAT scale 18, 100,000 samples, 30 deferred:
+// 9.4 ms in vain, the device-wide BFSs 10.3; directed, n = 10^6, long in-rows,
+// 25 deferred: 5.4 ms instead of 23.9).  So it is taken where the device-wide
+// BFSs would take more than half its time, and may then spend a quarter of
+// theirs, or as much as a whole BFS of the graph if that is less than theirs.
 constexpr uint32_t kWideNodes = 65536;
 constexpr uint64_t kWideArcsPerItem = 4096;
 constexpr uint64_t kWideArcsMin = uint64_t(1) << 17, kWideArcsMax = uint64_t(1) << 21;
 constexpr uint64_t kWideArcsShare = 128;   // of the graph's arcs
 constexpr uint32_t kWideFew = 8;
 constexpr int kSecondBlock = 512;
+constexpr double kSecondArcMs = 4.5e-6;   // per entry, one BFS
+constexpr double kWideMs = 0.2, kWideNodeMs = 0.6e-6;   // per device-wide BFS, and per node of the graph
 constexpr uint32_t kWideCap = 4096;
 constexpr uint32_t kWideGroup = 64;   // deferred samples advanced together
 
@@ -416,10 +426,19 @@ static int place_slots(centra_ctx* ctx, const SampleArgs& a, const SamplePlan& p
   return CENTRA_OK;
 }
 
+// The scan budget of a second launch for n deferred samples of the graph; 0:
+// none, they go to the device-wide BFS.
+static uint64_t second_budget(const SampleArgs& a, uint32_t n) {
+  const double wide = n * (kWideMs + kWideNodeMs * a.n), whole = kSecondArcMs * double(a.n_arcs);
+  if (n <= kWideFew || wide <= 0.5 * std::min(whole, kSecondArcMs * double(kWideArcsMax))) return 0;
+  if (whole <= wide) return kWideArcsMax;
+  return std::min(kWideArcsMax, std::max(kWideArcsMin, static_cast<uint64_t>(0.25 * wide / kSecondArcMs)));
+}
+
 // Draws a launch's n deferred samples (in a.defer_list) by a launch of their
 // own; what this one defers is in a.defer_list on return (the other half of
 // the list).
-static int second_launch(centra_ctx* ctx, SampleArgs& a, uint32_t n, hipStream_t s) {
+static int second_launch(centra_ctx* ctx, SampleArgs& a, uint32_t n, uint64_t budget, hipStream_t s) {
   int per_cu = 0, cus = 0;
   if (sample_kernel_occupancy(kSecondBlock, false, false, 0, &per_cu) != hipSuccess || per_cu <= 0) per_cu = 1;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess || cus <= 0)
@@ -432,7 +451,7 @@ static int second_launch(centra_ctx* ctx, SampleArgs& a, uint32_t n, hipStream_t
   a.count = n;
   a.items = a.defer_list;
   a.defer_list += kWideCap;
-  a.defer_arcs = kWideArcsMax;
+  a.defer_arcs = budget;
   a.stage_chunk = 0;
   fill_u64(a.work, 0, 1, s);
   fill_u32(a.defer_count, 0, 1, s);
@@ -516,8 +535,8 @@ static int launch_sampler(centra_ctx* ctx, SampleArgs a, uint32_t count, uint32_
     if (hipEventElapsedTime(&ms, ctx->ev[6], ctx->ev[7]) != hipSuccess) ms = 0.f;
     auto deferred = [&]() { return static_cast<uint32_t>(std::min<uint64_t>(stats[3] & 0xFFFFFFFFull, kWideCap)); };
     uint32_t n_wide = wide ? deferred() : 0u;
-    if (n_wide > kWideFew) {
-      if ((rc = second_launch(ctx, a, n_wide, s))) return rc;
+    if (const uint64_t budget = second_budget(a, n_wide)) {
+      if ((rc = second_launch(ctx, a, n_wide, budget, s))) return rc;
       CENTRA_HIP(ctx, hipMemcpyAsync(ctr, ctx->work_ctr.ptr, kCtrBytes, hipMemcpyDeviceToHost, s));
       CENTRA_HIP(ctx, hipStreamSynchronize(s));
       if ((rc = check_flags(ctx, s, "sample_paths (second launch)"))) return rc;
