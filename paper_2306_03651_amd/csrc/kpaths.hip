@@ -32,7 +32,13 @@ constexpr uint32_t kMaxKappa = CENTRA_MAX_KAPPA;
 // way together), and the walk is kept in registers (the loops over it are
 // unrolled; indexed by a variable it lay in scratch memory).  BA n = 10^6, 2M
 // walks, kappa = 5: 594 us one search after the other, 346 us in lockstep.
-template <int kMax>
+//
+// Walks of more than 8 nodes take one step's code over and over, its indexes
+// constant all the same: 16 steps laid out are more than the compiler unrolls,
+// and the walk lay in scratch memory again (2M walks, kappa = 9 / 16: BA n =
+// 10^6, 1,564 / 3,915 us one search after the other, 2,319 / 6,410 laid out, 815
+// / 1,586 so; random 4-regular, n = 10^5: 654 / 1,531, 834 / 2,269, 377 / 655).
+template <int kMax, int kSteps>
 __global__ __launch_bounds__(256) void k_kpath(uint32_t count, uint64_t first, uint64_t seed, uint32_t instance,
                                                uint32_t n, uint32_t kappa, const uint32_t* row_ptr,
                                                const uint32_t* col_idx, uint32_t* lens, uint32_t* stage) {
@@ -41,10 +47,10 @@ __global__ __launch_bounds__(256) void k_kpath(uint32_t count, uint64_t first, u
   WordStream st(seed, first + x, instance, 6);
   const uint32_t s = static_cast<uint32_t>(bounded(st, n));
   const uint32_t l = 1 + static_cast<uint32_t>(bounded(st, kappa));
-  uint32_t walk[kMax];   // the walk before its current node v (no self loops: v is not in its own row)
+  uint32_t walk[kMax] = {};   // the walk before its current node v (no self loops: v is not in its own row)
   uint32_t len = 0, v = s;
   uint32_t* out = stage + size_t(x) * kappa;
-#pragma unroll
+#pragma unroll kSteps
   for (int step = 0; step < kMax; ++step) {
     if (static_cast<uint32_t>(step) >= l) break;
     const uint32_t lo = row_ptr[v], hi = row_ptr[v + 1];
@@ -53,19 +59,20 @@ __global__ __launch_bounds__(256) void k_kpath(uint32_t count, uint64_t first, u
     uint32_t left = hi - lo;
     const uint32_t head = step && left ? col_idx[lo] : 0u;
 #pragma unroll
-    for (int i = 0; i < step; ++i) {
+    for (int i = 0; i < kMax; ++i) {
       pos[i] = lo;
       val[i] = head;
     }
     if (step) {
       while (left > 1) {
         const uint32_t h = left / 2;
-        uint32_t c[kMax];
+        uint32_t c[kMax] = {};
 #pragma unroll
-        for (int i = 0; i < step; ++i) c[i] = col_idx[pos[i] + h];
+        for (int i = 0; i < kMax; ++i)
+          if (i < step) c[i] = col_idx[pos[i] + h];
 #pragma unroll
-        for (int i = 0; i < step; ++i) {
-          const bool up = c[i] <= walk[i];
+        for (int i = 0; i < kMax; ++i) {
+          const bool up = i < step && c[i] <= walk[i];
           pos[i] = up ? pos[i] + h : pos[i];
           val[i] = up ? c[i] : val[i];
         }
@@ -74,8 +81,8 @@ __global__ __launch_bounds__(256) void k_kpath(uint32_t count, uint64_t first, u
     }
     uint32_t np = 0;
 #pragma unroll
-    for (int i = 0; i < step; ++i) {
-      const bool in = hi > lo && val[i] == walk[i];
+    for (int i = 0; i < kMax; ++i) {
+      const bool in = i < step && hi > lo && val[i] == walk[i];
       np += in ? 1u : 0u;
       pos[i] = in ? pos[i] : kUnseen;
     }
@@ -88,11 +95,12 @@ __global__ __launch_bounds__(256) void k_kpath(uint32_t count, uint64_t first, u
     for (;;) {
       uint32_t at = r;
 #pragma unroll
-      for (int i = 0; i < step; ++i) at += pos[i] <= idx ? 1u : 0u;
+      for (int i = 0; i < kMax; ++i) at += i < step && pos[i] <= idx ? 1u : 0u;
       if (at == idx) break;
       idx = at;
     }
-    walk[step] = v;
+#pragma unroll
+    for (int i = 0; i < kMax; ++i) walk[i] = i == step ? v : walk[i];
     v = col_idx[idx];
     out[step] = v;
     len = step + 1;
@@ -128,7 +136,7 @@ int kpath_count(centra_ctx* ctx, const centra_graph* g, uint32_t kappa, uint64_t
   if (timed) CENTRA_HIP(ctx, hipEventRecord(ctx->ev[4], s));
   if (count) {
     // registers for the walk's nodes: the least of the built sizes that holds kappa
-    auto* f = kappa <= 4 ? &k_kpath<4> : kappa <= 8 ? &k_kpath<8> : &k_kpath<kMaxKappa>;
+    auto* f = kappa <= 4 ? &k_kpath<4, 4> : kappa <= 8 ? &k_kpath<8, 8> : &k_kpath<kMaxKappa, 1>;
     hipLaunchKernelGGL(f, grid_of(count), dim3(256), 0, s, count, first, seed, instance, g->n, kappa, g->row_ptr,
                        g->col_idx, lens, static_cast<uint32_t*>(ctx->kp_stage.ptr));
   }
