@@ -496,13 +496,26 @@ constexpr uint32_t kBatchMinK = 12;            // rounds from which batches pay
 // samples of BA n = 10^6: 3.7 in batches, 2.3 by rounds).
 constexpr uint64_t kBatchMaxM = 2u << 20;
 constexpr uint32_t kBatchMinPicks = 8;         // a batch with fewer is the last
+// A batch reads all its candidates' rows, a round its pick's alone, so batches
+// pay while the rows are short against the rounds spared: entries per round
+// (us, k = 50, rounds / batches: BA n = 10^5, 400,000 path samples, 321,000
+// entries: 853 / 714, 800,000 samples, 645,000 entries: 985 / 1,115; synthetic, n
+// = 200,000, 500,000 samples of 16, 499,000: 2,002 / 1,578; n = 20,000, 10^6 of
+// 4, 573,000: 1,250 / 1,135; n = 2,000, 500,000 of 4, 593,000: 1,074 / 1,226; k =
+// 12, BA, 80,000: 325 / 310, 321,000: 418 / 519).
+constexpr uint64_t kBatchEntries = 12288;
+// And the candidates must not overlap so much that few of them stay above tau:
+// entries per sample, over the 64 of them (k = 50: n = 2,000, 50,000 samples of 4
+// nodes, 1.2: 622 / 435; n = 200,000, 200,000 of 16, 1.0: 1,610 / 899; n = 20,000,
+// 200,000 of 16, 2.1: 1,169 / 1,283; n = 8,000, 20,000 of 64, 9.4: 824 / 923).
+constexpr uint64_t kBatchOverlap = 2;
 
 // Device state of a batch.  Row i = c * n_seg + g is candidate c's in segment
 // g; pre is the prefix of the rows' lengths.
 struct BatchState {
   uint64_t tau;
   uint32_t r;          // rounds done
-  uint32_t fail;       // a node twice in a hyperedge, or more masks than the list holds
+  uint32_t fail;       // a node twice in a hyperedge, more masks than the list holds, or rows too long
   uint32_t done;       // no positive gain is left
   uint32_t n_cand, n_list, pad;
   uint32_t node[kCands];
@@ -512,7 +525,8 @@ struct BatchState {
 };
 
 struct BatchArgs {
-  uint32_t n, n_seg, k;
+  uint32_t n, n_seg, k, r;   // r: rounds done before
+  uint64_t m;
   const uint64_t* seg_off;
   const uint32_t* inc;
   const uint64_t* he_off;
@@ -668,11 +682,15 @@ __global__ __launch_bounds__(kBatchBlock) void k_batch_cands(BatchArgs a) {
     a.st->n_cand = n_cand;
     a.st->n_list = 0;
     a.st->done = mx ? 0u : 1u;
+    if (total > kBatchEntries * (a.k - a.r) || total > kBatchOverlap * a.m) a.st->fail = 1;
   }
 }
 
 __global__ __launch_bounds__(256) void k_batch_mask(BatchArgs a) {
   __shared__ uint64_t pre[kBatchRows + 1];
+  // (uniform; a workgroup that sees the fault another has found leaves too:
+  // the masks are not used)
+  if (__syncthreads_or(a.st->fail != 0)) return;
   batch_entries(a, pre, [&](uint32_t s, uint32_t c) {
     if (a.covered[s >> 5] >> (s & 31u) & 1u) return;
     const uint64_t old = atomicOr(reinterpret_cast<unsigned long long*>(&a.mask[s]), 1ull << c);
@@ -686,6 +704,7 @@ __global__ __launch_bounds__(256) void k_batch_list(BatchArgs a) {
   __shared__ uint64_t pre[kBatchRows + 1], red[2 * Coll<256>::kHalf];
   __shared__ uint32_t base;
   Coll<256> co{red, 0};
+  if (__syncthreads_or(a.st->fail != 0)) return;
   for (uint32_t i = threadIdx.x; i <= kBatchRows; i += 256) pre[i] = a.st->pre[i];
   __syncthreads();
   const uint64_t total = pre[kBatchRows];
@@ -788,11 +807,12 @@ __global__ __launch_bounds__(kCoverBlock) void k_batch_cover(BatchArgs a) {
   __shared__ AggTable tab;
   __shared__ uint64_t pre[kBatchRows + 1], hbeg[kCoverBlock];
   __shared__ uint32_t hoff[kCoverBlock], scan[kCoverBlock / kWave + 1];
+  const uint64_t chosen = a.st->chosen;
+  if (!chosen) return;   // uniform
   for (uint32_t i = threadIdx.x; i <= kBatchRows; i += kCoverBlock) pre[i] = a.st->pre[i];
   agg_init(tab);
-  const uint64_t chosen = a.st->chosen;
   __syncthreads();
-  const uint64_t total_e = chosen ? pre[kBatchRows] : 0ull;
+  const uint64_t total_e = pre[kBatchRows];
   const uint64_t stride = uint64_t(gridDim.x) * kCoverBlock;
   for (uint64_t e0 = uint64_t(blockIdx.x) * kCoverBlock; e0 < total_e; e0 += stride) {   // uniform trip count
     const uint64_t e = e0 + threadIdx.x;
@@ -1318,7 +1338,9 @@ static int greedy_batches(centra_ctx* ctx, BatchArgs a, uint64_t m, const uint32
   fill_u32(reinterpret_cast<uint32_t*>(a.st), 0, 16, s);   // r and fail among them
   fill_u64(a.mask, 0, m, s);
   uint32_t r = 0;
+  a.m = m;
   while (r < a.k) {
+    a.r = r;
     hipLaunchKernelGGL(k_batch_top, dim3(kTopBlocks), dim3(kTopBlock), 0, s, a, r == 0 ? 1 : 0);
     hipLaunchKernelGGL(k_batch_cands, dim3(1), dim3(kBatchBlock), 0, s, a);
     hipLaunchKernelGGL(k_batch_mask, dim3(512), dim3(256), 0, s, a);
