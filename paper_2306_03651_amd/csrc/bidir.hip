@@ -742,6 +742,10 @@ constexpr uint32_t kBiFewSlots = 1024;
 // and queues, 40 bytes per node per slot, at most half of the device's
 // memory (the context budget can lower that).
 constexpr uint32_t kBiLeanSlots = 1792;   // slots beyond which memory is only taken if much is left
+// 32nds of the device for more: a node has twice the state of the path
+// sampler's (BA n = 10^6, 100,000 samples: 6.1 ms with 3,584 slots, which take
+// 14.8 of them; 6.9 with the 2,900 that 12 hold)
+constexpr uint32_t kBiSlotParts = 15;
 
 static size_t most_bidir_slots(centra_ctx* ctx, uint32_t n) {
   const size_t most = slot_mem_cap(ctx) / (size_t(n) * 40);
@@ -755,7 +759,7 @@ static int ensure_bidir_slots(centra_ctx* ctx, uint32_t n, uint32_t want, hipStr
   DevBuf* bufs[] = {&ctx->bi_rec_f, &ctx->bi_rec_b, &ctx->bi_q_f, &ctx->bi_q_b};
   size_t have = 0;
   for (DevBuf* b : bufs) have += b->bytes;
-  uint32_t slots = slots_that_fit(ctx, size_t(nn) * 40, want, kBiLeanSlots, have);
+  uint32_t slots = slots_that_fit(ctx, size_t(nn) * 40, want, kBiLeanSlots, kBiSlotParts, have);
   if (ctx->bi_slots >= slots && ctx->bi_n >= nn) return CENTRA_OK;
   int rc;
   for (;;) {   // halve the slot count while the device cannot hold the state

@@ -201,7 +201,8 @@ int stage_to_output(centra_ctx* ctx, uint32_t count, uint64_t base, uint64_t* he
 // The balanced bidirectional sampler (bidir.hip): samples [first,
 // first+count) into the staging area, as sample_to_stage.
 size_t slot_mem_cap(centra_ctx* ctx);   // (sample_launch.hip)
-uint32_t slots_that_fit(centra_ctx* ctx, size_t per_slot, uint32_t want, uint32_t lean, size_t have);
+uint32_t slots_that_fit(centra_ctx* ctx, size_t per_slot, uint32_t want, uint32_t lean, uint32_t parts,
+                        size_t have);
 int sample_bidir_to_stage(centra_ctx* ctx, const centra_graph* g, uint64_t seed, uint32_t instance,
                           uint64_t first, uint32_t count, uint32_t* st_out, uint32_t* dist_out,
                           uint64_t* total, hipStream_t s);

@@ -21,6 +21,7 @@ namespace centra {
 // filter in LDS) run several workgroups of 64 to 512 threads per CU.
 constexpr uint32_t kMaxSlots = 8192;
 constexpr uint32_t kLeanSlots = 3072;   // slots beyond which memory is only taken if much is left
+constexpr uint32_t kSlotParts = 12;     // 32nds of the device that those may take
 
 // Byte offsets of a launch's counters in work_ctr: the two words that every
 // workgroup adds to on lines of their own; then arcs, nodes, entries, and
@@ -55,11 +56,11 @@ size_t slot_mem_cap(centra_ctx* ctx) {
 // Slots that a launch may have by the rules of memory alone, whatever else is
 // allocated.  Up to `lean` of them may take half of the device, or the whole
 // budget.  More hide more latency but leave less memory to whatever is
-// allocated next, so they may take three eighths of the device, or an eighth
+// allocated next, so they may take `parts` 32nds of the device, or an eighth
 // of the budget.
-static size_t slots_allowed(centra_ctx* ctx, size_t per_slot, uint32_t lean) {
+static size_t slots_allowed(centra_ctx* ctx, size_t per_slot, uint32_t lean, uint32_t parts) {
   const size_t cap = slot_mem_cap(ctx), most = ctx->budget && ctx->budget < cap ? ctx->budget : cap;
-  const size_t room = ctx->budget ? std::min(cap / 4 * 3, ctx->budget / 8) : cap / 4 * 3;
+  const size_t room = ctx->budget ? std::min(cap / 16 * parts, ctx->budget / 8) : cap / 16 * parts;
   return std::max(std::min<size_t>(lean, most / per_slot), room / per_slot);
 }
 
@@ -103,7 +104,7 @@ constexpr uint32_t kSkewedRow = 2048;
 // max_row: the longest row of the graph (of a fused launch's graphs) in either
 // direction.
 static int threads_for(centra_ctx* ctx, uint32_t n, uint64_t count, uint32_t max_row, bool multi) {
-  const size_t slots = slots_allowed(ctx, slot_bytes(n), kLeanSlots);
+  const size_t slots = slots_allowed(ctx, slot_bytes(n), kLeanSlots, kSlotParts);
   if (slots < kFewSlots || count < kFewSamples) return 256;
   const uint32_t many = n <= kNarrowNodes && max_row <= kNarrowRow ? kManyNarrow : kManySamples;
   return slots < kManySlots || count < many || (multi && max_row > kSkewedRow) ? 128 : 64;
@@ -154,8 +155,8 @@ static SamplePlan plan_for(centra_ctx* ctx, uint32_t n, uint32_t count, uint32_t
 // only while three eighths of the device remain free (a context that draws
 // from both samplers on n = 2 10^6 would otherwise ask for the whole device),
 // and no more than the budget holds.
-uint32_t slots_that_fit(centra_ctx* ctx, size_t per_slot, uint32_t want, uint32_t lean, size_t have) {
-  const size_t most = std::max<size_t>(1, slots_allowed(ctx, per_slot, lean));
+uint32_t slots_that_fit(centra_ctx* ctx, size_t per_slot, uint32_t want, uint32_t lean, uint32_t parts, size_t have) {
+  const size_t most = std::max<size_t>(1, slots_allowed(ctx, per_slot, lean, parts));
   if (want > most) want = static_cast<uint32_t>(most);
   if (ctx->budget) {
     const size_t others = ctx->allocated - have;
@@ -189,7 +190,7 @@ static int ensure_slots(centra_ctx* ctx, uint32_t gn, uint32_t want, hipStream_t
   DevBuf* bufs[] = {&ctx->slot_map, &ctx->slot_sig, &ctx->slot_q, &ctx->slot_starts, &ctx->slot_pinfo};
   size_t have = 0;
   for (DevBuf* b : bufs) have += b->bytes;
-  uint32_t slots = slots_that_fit(ctx, slot_bytes(n), want, kLeanSlots, have);
+  uint32_t slots = slots_that_fit(ctx, slot_bytes(n), want, kLeanSlots, kSlotParts, have);
   if (ctx->slots >= slots && ctx->slot_n >= n) return CENTRA_OK;
   int rc;
   for (;;) {   // halve the slot count while the device cannot hold the state
