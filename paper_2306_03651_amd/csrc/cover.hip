@@ -1124,9 +1124,9 @@ uint32_t greedy_part_words() { return kArgGrid; }
 // and spreads the concatenation of their hyperedges over its lanes.
 constexpr int kSoloBlock = 1024;
 constexpr size_t kSoloLds = 144 << 10;      // of the 160 KB of a CU
-// hyperedge entries, and one and a half more per sample, per round that one
-// workgroup is given
-constexpr uint64_t kSoloEntries = 12288;
+// hyperedge entries per round that one workgroup is given, and samples whose
+// offsets the L2 holds beside the rest; each further one counts as two entries
+constexpr uint64_t kSoloEntries = 12288, kSoloNear = 65536;
 constexpr int kSoloUnroll = 4;              // hyperedge entries a lane has in flight
 
 struct SoloShared {
@@ -1237,13 +1237,15 @@ __global__ __launch_bounds__(kSoloBlock) void k_greedy_solo_multi(const GreedyDe
 size_t greedy_solo_lds(uint32_t n, uint64_t m) { return size_t(n) * 4 + ((m + 31) / 32 + 1) * 4; }
 
 // One workgroup where the state fits its LDS and the hyperedges' nodes, of
-// which a round of kernels takes many at once, and the samples, whose offsets
-// are scattered reads, do not outweigh the rounds (whole cover call, us, one
-// workgroup against rounds; n = 2,000, m = 10,000: 40,000 entries, k = 20: 291,
-// 446; 300,000 entries, k = 50: 627, 760; k = 20: 501, 487; 500,000 samples of
-// one node, k = 50: 720, 662; of 4, k = 200: 3,198, 2,367).
+// which a round of kernels takes many at once, and, where they are many, the
+// samples, whose offsets are scattered reads, do not outweigh the rounds (whole
+// cover call, us, one workgroup against rounds; n = 2,000, m = 10,000: 40,000
+// entries, k = 20: 291, 446; 300,000 entries, k = 50: 627, 760; k = 20: 501, 487;
+// n = m = 30,000, 120,000 entries, k = 11: 228, 316; 500,000 samples of one node,
+// k = 50: 720, 662; of 4, k = 200: 3,198, 2,367).
 bool greedy_solo(uint32_t n, uint64_t m, uint64_t entries, uint32_t k) {
-  return greedy_solo_lds(n, m) <= kSoloLds && entries + 3 * m / 2 <= uint64_t(k) * kSoloEntries;
+  return greedy_solo_lds(n, m) <= kSoloLds &&
+         entries + 2 * (m > kSoloNear ? m - kSoloNear : 0) <= uint64_t(k) * kSoloEntries;
 }
 
 template <typename F>

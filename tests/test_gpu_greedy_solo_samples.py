@@ -10,8 +10,8 @@ from tests.test_gpu_greedy_batch_rule import cover
 pytestmark = pytest.mark.gpu
 
 
-# samples of one node: the entries and one and a half times the samples, at k * 12,288 and past it
-@pytest.mark.parametrize("m,k", [(4915, 1), (4916, 1), (54_067, 11), (54_068, 11), (58_982, 12), (58_983, 12)])
+# samples of one node: with two more entries for each past 65,536, at k * 12,288 and past it
+@pytest.mark.parametrize("m,k", [(65_536, 6), (65_537, 5), (88_746, 11), (88_747, 11), (92_842, 12), (92_843, 12)])
 @pytest.mark.parametrize("n", [7, 500])
 def test_one_node_each(n, m, k):
     rng = np.random.default_rng(m)
