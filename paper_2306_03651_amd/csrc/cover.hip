@@ -677,20 +677,18 @@ __global__ __launch_bounds__(kBatchBlock) void k_batch_cands(BatchArgs a) {
   a.st->beg[tid] = rb;
   a.st->pre[tid] = before;
   if (tid == 0) {
-    a.st->pre[kBatchRows] = total;
+    const bool fail = total > kBatchEntries * (a.k - a.r) || total > kBatchOverlap * a.m;
+    a.st->pre[kBatchRows] = fail ? 0 : total;   // (then there is nothing to read)
+    if (fail) a.st->fail = 1;
     a.st->tau = tau;
     a.st->n_cand = n_cand;
     a.st->n_list = 0;
     a.st->done = mx ? 0u : 1u;
-    if (total > kBatchEntries * (a.k - a.r) || total > kBatchOverlap * a.m) a.st->fail = 1;
   }
 }
 
 __global__ __launch_bounds__(256) void k_batch_mask(BatchArgs a) {
   __shared__ uint64_t pre[kBatchRows + 1];
-  // (uniform; a workgroup that sees the fault another has found leaves too:
-  // the masks are not used)
-  if (__syncthreads_or(a.st->fail != 0)) return;
   batch_entries(a, pre, [&](uint32_t s, uint32_t c) {
     if (a.covered[s >> 5] >> (s & 31u) & 1u) return;
     const uint64_t old = atomicOr(reinterpret_cast<unsigned long long*>(&a.mask[s]), 1ull << c);
@@ -704,7 +702,6 @@ __global__ __launch_bounds__(256) void k_batch_list(BatchArgs a) {
   __shared__ uint64_t pre[kBatchRows + 1], red[2 * Coll<256>::kHalf];
   __shared__ uint32_t base;
   Coll<256> co{red, 0};
-  if (__syncthreads_or(a.st->fail != 0)) return;
   for (uint32_t i = threadIdx.x; i <= kBatchRows; i += 256) pre[i] = a.st->pre[i];
   __syncthreads();
   const uint64_t total = pre[kBatchRows];
@@ -807,12 +804,11 @@ __global__ __launch_bounds__(kCoverBlock) void k_batch_cover(BatchArgs a) {
   __shared__ AggTable tab;
   __shared__ uint64_t pre[kBatchRows + 1], hbeg[kCoverBlock];
   __shared__ uint32_t hoff[kCoverBlock], scan[kCoverBlock / kWave + 1];
-  const uint64_t chosen = a.st->chosen;
-  if (!chosen) return;   // uniform
   for (uint32_t i = threadIdx.x; i <= kBatchRows; i += kCoverBlock) pre[i] = a.st->pre[i];
   agg_init(tab);
+  const uint64_t chosen = a.st->chosen;
   __syncthreads();
-  const uint64_t total_e = pre[kBatchRows];
+  const uint64_t total_e = chosen ? pre[kBatchRows] : 0ull;
   const uint64_t stride = uint64_t(gridDim.x) * kCoverBlock;
   for (uint64_t e0 = uint64_t(blockIdx.x) * kCoverBlock; e0 < total_e; e0 += stride) {   // uniform trip count
     const uint64_t e = e0 + threadIdx.x;
