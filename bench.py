@@ -659,7 +659,7 @@ def main():
         roofline.update({"arcs_per_path": round(st.arcs / max(1, st.samples), 1),
                          "nodes_per_path": round(st.nodes / max(1, st.samples), 1),
                          "entries_per_path": round(st.hyperedge_nodes / max(1, st.samples), 3),
-                         "visited_set": "lds bitmap" if st.lds_bitmap else "lds bloom filter + hbm records",
+                         "visited_set": "lds bitmap" if st.lds_bitmap else "lds filter + hbm map",
                          "concurrent_bfs": st.slots, "wide_samples": st.wide,
                          "wide_ms_per_step": round(st.wide_ms / max(1, args.steps), 2),
                          "wide_arcs_per_wide_sample": round(st.wide_arcs / max(1, st.wide))})

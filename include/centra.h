@@ -66,8 +66,8 @@ CENTRA_API uint32_t centra_abi_version(void);
  * Contexts are independent: different contexts may be used from different
  * host threads at the same time.  *out receives the context.
  * Placement: the sampler's speed depends on where the device allocator puts
- * the pages of that state's per-BFS node maps (the same launch varies by
- * several percent from one allocation to the next, and not within one).
+ * the pages of that state's per-BFS node maps (the same launch varies by up
+ * to a quarter from one allocation to the next, and not within one).
  * When a synchronous sampling call first allocates at least 4 GiB of
  * maps on a context, the context times a launch of the call's first
  * 65,536 work items on each of up to four allocations of them, holding two

@@ -9,8 +9,8 @@
 // bit-identical to a sequential implementation.
 //
 // State of a slot, in HBM: the visited nodes in level order (their ids and
-// counts sigma', contiguous), a bitmap of the places where levels start, and a map from nodes
-// to places in that order (Visited, below): one 8-byte word per node, stamp
+// counts sigma', contiguous), a bitmap of the places where levels start, and a
+// map from nodes to places in that order (Visited, below): one 8-byte word per node, stamp
 // << 32 | place, where the stamp numbers the BFSs of the context in launch
 // and work order.  A slot's map carries only stamps older than its current
 // BFS's unless that BFS visited the node, so nothing is ever reset between
@@ -32,9 +32,11 @@
 // uses no global atomic in a BFS, looks nodes up in bulk (Hits, Dups), and
 // keeps its code within the instruction cache (41 KB of 64; 83 KB before,
 // when every launch and most steps waited for instructions).  Measured, with
-// 16-byte records claimed by returning 64-bit global atomics before: BA n =
-// 10^6, 400,000 samples, 26.7 -> 15.2 ms; grid 128 x 128, 10,000 samples,
-// 13.9 -> 7.6 ms; directed R-MAT scale 20, 200,000 samples, 32-49 -> 22 ms.
+// 16-byte records claimed by returning 64-bit global atomics before, from one
+// box and placement of the state to another: BA n = 10^6, 400,000 samples,
+// 26.7-31 -> 15.2-17.6 ms; grid 128 x 128, 10,000 samples, 13.9-14.4 ->
+// 7.7-8.2 ms; directed R-MAT scale 20, 200,000 samples, 32-49 -> 14.3 ms (21 while
+// all deferred samples went one after another through the device-wide BFS).
 //
 // Early stop.  After levels 0..L are complete, every visited in-neighbour
 // of an unvisited node is at level L (a lower one would have put the node
