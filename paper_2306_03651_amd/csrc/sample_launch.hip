@@ -87,12 +87,13 @@ static size_t slots_allowed(centra_ctx* ctx, size_t per_slot, uint32_t lean, uin
 // 4.1 / 3.2 / 2.7) nor with longer rows (16-regular, n = 16,000, 8,192: 0.34 /
 // 0.29 / 0.33), be they in-rows alone (8 out-arcs, in-rows of up to 4,484, n =
 // 16,000: 2.3 / 1.2 / 0.7).
-// A fused launch leaves no sample for after it, so its longest BFS holds it:
-// 128 threads also where the graphs are skewed, which long rows tell (directed
-// R-MAT scale 20, 2 x 40,000 samples: 80 / 47 / 25; directed, n = 10^5, rows
-// of up to 15,887, 40,000: 29 / 16 / 11; BA n = 10^6, rows of up to 3,560,
-// 400,000: 20.0 / 21.6 / 28.1; BA n = 10^5, rows of up to 1,134: 7.1 / 10.0 /
-// 15.1).
+// A fused or stream-ordered launch leaves no sample for after it, so its
+// longest BFS holds it: 128 threads also where the graphs are skewed, which
+// long rows tell (fused, directed R-MAT scale 20, 2 x 40,000 samples: 80 / 47 /
+// 25; directed, n = 10^5, rows of up to 15,887, 40,000: 29 / 16 / 11; BA n =
+// 10^6, rows of up to 3,560, 400,000: 20.0 / 21.6 / 28.1; BA n = 10^5, rows of up
+// to 1,134: 7.1 / 10.0 / 15.1; stream-ordered, R-MAT scale 20, 400,000: 68 / 43
+// / 26; scale 14, rows of up to 2,443, 40,000: 0.81 / 0.54).
 // CENTRA_SAMPLER_VARIANT selects another for single-graph launches: "lds"
 // (exact LDS bitmap, 1024 threads, when the bitmap fits), "hbm512", "hbm256",
 // "hbm128", "hbm64" (LDS filter, that many threads).
@@ -102,12 +103,12 @@ constexpr size_t kFewSlots = 2048, kManySlots = 4096;
 constexpr uint32_t kSkewedRow = 2048;
 
 // max_row: the longest row of the graph (of a fused launch's graphs) in either
-// direction.
-static int threads_for(centra_ctx* ctx, uint32_t n, uint64_t count, uint32_t max_row, bool multi) {
+// direction; defers: long BFSs are left for after the launch.
+static int threads_for(centra_ctx* ctx, uint32_t n, uint64_t count, uint32_t max_row, bool defers) {
   const size_t slots = slots_allowed(ctx, slot_bytes(n), kLeanSlots, kSlotParts);
   if (slots < kFewSlots || count < kFewSamples) return 256;
   const uint32_t many = n <= kNarrowNodes && max_row <= kNarrowRow ? kManyNarrow : kManySamples;
-  return slots < kManySlots || count < many || (multi && max_row > kSkewedRow) ? 128 : 64;
+  return slots < kManySlots || count < many || (!defers && max_row > kSkewedRow) ? 128 : 64;
 }
 
 static uint32_t longest_row(const centra_graph* g) { return std::max(g->max_in_degree, g->max_out_degree); }
@@ -118,12 +119,13 @@ int fused_threads(centra_ctx* ctx, const MultiSampleItem* items, uint32_t n_item
     n = std::max(n, items[i].g->n);
     max_row = std::max(max_row, longest_row(items[i].g));
   }
-  return threads_for(ctx, n, ~0ull, max_row, true);
+  return threads_for(ctx, n, ~0ull, max_row, false);
 }
 
-// multi: a fused launch; block: its threads per BFS if the caller chose them.
-static SamplePlan plan_for(centra_ctx* ctx, uint32_t n, uint32_t count, uint32_t max_row, bool multi = false,
-                           int block = 0) {
+// multi: a fused launch; block: its threads per BFS if the caller chose them;
+// async: a stream-ordered launch.
+static SamplePlan plan_for(centra_ctx* ctx, uint32_t n, uint32_t count, uint32_t max_row, bool async,
+                           bool multi = false, int block = 0) {
   SamplePlan p{};
   p.bit_words = (n + 31) / 32;
   int max_lds = 0, cus = 0;
@@ -134,7 +136,7 @@ static SamplePlan plan_for(centra_ctx* ctx, uint32_t n, uint32_t count, uint32_t
   const size_t dyn = size_t(p.bit_words) * 4;
   const char* env = getenv("CENTRA_SAMPLER_VARIANT");
   const char* v = env && !multi ? env : "";
-  p.block = block ? block : threads_for(ctx, n, count, max_row, multi);
+  p.block = block ? block : threads_for(ctx, n, count, max_row, !async && !multi);
   if (!strcmp(v, "hbm64")) p.block = 64;
   if (!strcmp(v, "hbm512")) p.block = 512;
   if (!strcmp(v, "hbm256")) p.block = 256;
@@ -475,7 +477,7 @@ static int launch_sampler(centra_ctx* ctx, SampleArgs a, uint32_t count, uint32_
                           int block, uint64_t* total, hipStream_t s, uint64_t async_cap = 0) {
   int rc;
   *total = 0;
-  const SamplePlan plan = plan_for(ctx, max_n, count, max_row, multi, block);
+  const SamplePlan plan = plan_for(ctx, max_n, count, max_row, async_cap != 0, multi, block);
   uint32_t want = count < plan.resident ? count : plan.resident;
   bool fresh = false;
   if ((rc = ensure_slots(ctx, max_n, want, s, &fresh))) return rc;
@@ -688,7 +690,7 @@ __global__ void k_stage_append(uint32_t count, const uint64_t* stage_pos, const 
 }
 
 int sample_reserve(centra_ctx* ctx, const centra_graph* g, uint32_t count, uint64_t stage_entries, hipStream_t s) {
-  const SamplePlan plan = plan_for(ctx, g->n, count, longest_row(g));
+  const SamplePlan plan = plan_for(ctx, g->n, count, longest_row(g), true);
   const uint32_t want = count < plan.resident ? count : plan.resident;
   int rc;
   bool fresh = false;   // no placement search here: there is no launch to time
