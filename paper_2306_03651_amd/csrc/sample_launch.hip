@@ -154,9 +154,11 @@ static SamplePlan plan_for(centra_ctx* ctx, uint32_t n, uint32_t count, uint32_t
 
 // Slots for a launch that has a use for `want`, where the state held now
 // takes `have` bytes: as many as the rules allow, more than `lean` of them
-// only while three eighths of the device remain free (a context that draws
-// from both samplers on n = 2 10^6 would otherwise ask for the whole device),
-// and no more than the budget holds.
+// only while a quarter of the device remains free (a context that draws from
+// both samplers on n = 2 10^6 would otherwise ask for the whole device; with
+// three eighths, one on n = 10^6 has 2,700 bidirectional searches at once beside
+// the path sampler's state and takes 58.5 ms for 800,000 samples, not 48.2), and
+// no more than the budget holds.
 uint32_t slots_that_fit(centra_ctx* ctx, size_t per_slot, uint32_t want, uint32_t lean, uint32_t parts, size_t have) {
   const size_t most = std::max<size_t>(1, slots_allowed(ctx, per_slot, lean, parts));
   if (want > most) want = static_cast<uint32_t>(most);
@@ -174,7 +176,7 @@ uint32_t slots_that_fit(centra_ctx* ctx, size_t per_slot, uint32_t want, uint32_
       (void)hipGetLastError();
       return lean;
     }
-    const size_t keep = slot_mem_cap(ctx) / 4 * 3;
+    const size_t keep = slot_mem_cap(ctx) / 2;
     const size_t room = free_b + have > keep ? free_b + have - keep : 0;
     want = std::max<uint32_t>(lean, std::min<size_t>(want, room / per_slot));
   }
